@@ -1,6 +1,6 @@
 // Instantiated apply configurations and the generic launcher.
 #pragma once
-#include "apply_impl.h"
+#include "apply_plane.h"
 
 namespace vpp {
 
@@ -24,9 +24,13 @@ namespace vpp {
     X(3, 1, 4, 4, 2)          \
     X(3, 1, 4, 2, 2)          \
     X(3, 1, 8, 2, 2)          \
+    X(3, 1, 8, 4, 4)          \
     X(4, 1, 4, 2, 2)          \
     X(4, 1, 2, 2, 2)          \
-    X(4, 1, 4, 4, 1)
+    X(4, 1, 4, 4, 1)          \
+    X(4, 1, 4, 3, 2)          \
+    X(4, 1, 4, 4, 3)          \
+    X(4, 1, 6, 4, 2)
 
 // Configurations also instantiated with the mass shift mu M of the level-set
 // filter operators (variant 4: the mass term sits in cell_operator; variant 1:
@@ -61,7 +65,7 @@ template <int K, typename T, int V, int TX, int TY, int TZ, int HV, bool DOT, bo
 inline hipError_t launch_hv(const ApplyArgs<T>& a, hipStream_t s)
 {
     const int nblocks = a.m.ntile[0] * a.m.ntile[1] * a.m.ntile[2];
-    constexpr int threads = V == 1 ? (K + 1) * TX * TY * TZ : (V == 2 ? 2 : 1) * TX * TY * TZ;
+    constexpr int threads = V == 1 ? PlaneGeo<K, TX, TY, TZ>::NTH : (V == 2 ? 2 : 1) * TX * TY * TZ;
     hipLaunchKernelGGL((kernel_ptr<K, T, V, TX, TY, TZ, HV, DOT, MASS>()), dim3(nblocks), dim3(threads), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.tiles_only) return e;

@@ -13,10 +13,8 @@
 //   variant 2, half a cell per thread (k = 3): an even/odd lane pair holds a
 //              cell's z-planes, z sweeps by DPP lane swaps;
 //   variant 1, plane per thread: k+1 threads share a cell, each holding one
-//              x-plane of (k+1)^2 values; y/z sweeps are in registers and the
-//              x sweeps exchange planes through LDS (all k), or for k = 3,
-//              where a cell's four threads form one lane quad, by DPP quad
-//              permutations.
+//              plane of (k+1)^2 values, an x-plane for the y and z sweeps and a
+//              z-plane for the x sweeps, the planes turned through LDS (all k).
 // Nodes that only this tile touches are written with plain stores; nodes on
 // planes shared with neighbouring tiles are written as per-tile partials and
 // summed, in a fixed order, by the assembly kernel (apply_misc.hip), so the
@@ -430,13 +428,26 @@ __device__ __forceinline__ constexpr bool owned_pos(int a0, int a1, int a2)
     return a0 < K && a1 < K && a2 < K;
 }
 
+// Where the write-out finds a cell's local result (a0, a1, a2) in LDS.  col()
+// is the handle of cell c of the tile, zero() that of a column of zeros, which
+// stands in for a neighbour cell below the tile.
+template <int N, typename T, int NC>
+struct ColSlots {   // slot q of cell c at q * (NC + 1) + c
+    const T* s;
+    __device__ __forceinline__ int col(int c) const { return c; }
+    __device__ __forceinline__ int zero() const { return NC; }
+    __device__ __forceinline__ T get(int a0, int a1, int a2, int h) const
+    {
+        return VPP_LD(&s[(a0 + N * (a1 + N * a2)) * (NC + 1) + h], BC_SLOT);
+    }
+};
+
 // Per-tile data of the upper-face write-out.
-template <typename T>
+template <typename T, typename S>
 struct FaceCtx {
     const MeshArgs& m;
     const TileCoord& tc;
-    const T* slot;
-    int cs;
+    const S& slot;
     const T* __restrict__ xt;
     T* __restrict__ yt;
     T* __restrict__ part;
@@ -447,10 +458,10 @@ struct FaceCtx {
 // The (cell, local index) pairs of the tile touching block coordinate c along
 // one direction: on the face (c == E) only the last cell with index K; else
 // cell c / K with index c % K, plus cell c / K - 1 with index K when c is a
-// multiple of K above 0 (the second pair reads the zero column ZERO otherwise).
+// multiple of K above 0 (otherwise the second cell is -1: no contribution).
 template <int K>
-__device__ __forceinline__ void contributors(int c, bool face, int ncell, int stride, int zero, int& cell0,
-                                             int& q0, int& cell1, int& q1)
+__device__ __forceinline__ void contributors(int c, bool face, int ncell, int stride, int& cell0, int& q0,
+                                             int& cell1, int& q1)
 {
     if (face) {
         cell0 = (ncell - 1) * stride;
@@ -471,10 +482,9 @@ __device__ __forceinline__ void contributors(int c, bool face, int ncell, int st
 // written later, so every node is written once: z face first, then y, then x),
 // for a tile cut by the mesh's upper boundary (runtime extents); complete
 // tiles use upper_face_full.
-template <int K, typename T, int TX, int TY, int TZ, int FACE, int NTH = TX * TY * TZ>
-__device__ __forceinline__ double upper_face(const FaceCtx<T>& f, bool dot)
+template <int K, typename T, int TX, int TY, int TZ, int FACE, int NTH, typename S>
+__device__ __forceinline__ double upper_face(const FaceCtx<T, S>& f, bool dot)
 {
-    constexpr int N = K + 1, NT = TX * TY * TZ;
     const int E0 = f.tc.ext[0] - 1;
     const int E1 = f.tc.ext[1] - 1;
     const int E2 = f.tc.ext[2] - 1;
@@ -508,13 +518,12 @@ __device__ __forceinline__ double upper_face(const FaceCtx<T>& f, bool dot)
         const int c1 = FACE == 0 ? ia : (FACE == 1 ? E1 : ib);
         const int c2 = FACE == 2 ? E2 : ib;
         int x0, p0, x1, p1, y0, r0, y1, r1, z0, s0, z1, s1;
-        contributors<K>(c0, FACE == 0, nc0, 1, NT, x0, p0, x1, p1);
-        contributors<K>(c1, FACE == 1 || (FACE == 0 && c1 == E1), nc1, TX, NT, y0, r0, y1, r1);
-        contributors<K>(c2, FACE == 2 || (FACE != 2 && c2 == E2), nc2, TX * TY, NT, z0, s0, z1, s1);
-        const int zero = NT;
+        contributors<K>(c0, FACE == 0, nc0, 1, x0, p0, x1, p1);
+        contributors<K>(c1, FACE == 1 || (FACE == 0 && c1 == E1), nc1, TX, y0, r0, y1, r1);
+        contributors<K>(c2, FACE == 2 || (FACE != 2 && c2 == E2), nc2, TX * TY, z0, s0, z1, s1);
         auto rd = [&](int cx_, int qx, int cy_, int qy, int cz_, int qz) -> T {
             const bool ok = cx_ >= 0 && cy_ >= 0 && cz_ >= 0;
-            return VPP_LD(&f.slot[(qx + N * (qy + N * qz)) * f.cs + (ok ? cx_ + cy_ + cz_ : zero)], BC_SLOT);
+            return f.slot.get(qx, qy, qz, ok ? f.slot.col(cx_ + cy_ + cz_) : f.slot.zero());
         };
         T v = rd(x0, p0, y0, r0, z0, s0);
         v += rd(x1, p1, y0, r0, z0, s0);
@@ -553,11 +562,10 @@ __device__ __forceinline__ double upper_face(const FaceCtx<T>& f, bool dot)
 // the tile and (c / K - 1, K) when c % K == 0 and c > 0; on the face (c == E)
 // only the second exists.  Along FACE only the last cell with index K holds the
 // node, so every node sums at most four slots.
-template <int K, typename T, int TX, int TY, int TZ, int FACE, int NTH = TX * TY * TZ>
-__device__ __forceinline__ double upper_face_full(const FaceCtx<T>& f, const int (&fb)[3], const bool (&dlo)[3],
+template <int K, typename T, int TX, int TY, int TZ, int FACE, int NTH, typename S>
+__device__ __forceinline__ double upper_face_full(const FaceCtx<T, S>& f, const int (&fb)[3], const bool (&dlo)[3],
                                                   const bool (&dhi)[3], bool dot)
 {
-    constexpr int N = K + 1, NT = TX * TY * TZ;
     constexpr int E0 = K * TX, E1 = K * TY, E2 = K * TZ;
     constexpr int NA = FACE == 0 ? E1 + 1 : E0;
     constexpr int NB = FACE == 2 ? E1 : E2 + 1;
@@ -596,9 +604,9 @@ __device__ __forceinline__ double upper_face_full(const FaceCtx<T>& f, const int
             const bool b0 = s & 1, b1 = (s >> 1) & 1, b2 = (s >> 2) & 1;
             if ((FACE == 0 && !b0) || (FACE == 1 && !b1) || (FACE == 2 && !b2)) continue;
             const int x0 = b0 ? cb[0] : ca[0], x1 = b1 ? cb[1] : ca[1], x2 = b2 ? cb[2] : ca[2];
-            const int p = (b0 ? K : qa[0]) + N * ((b1 ? K : qa[1]) + N * (b2 ? K : qa[2]));
             const bool ok = x0 >= 0 && x1 >= 0 && x2 >= 0;
-            v += VPP_LD(&f.slot[p * f.cs + (ok ? x0 * CST[0] + x1 * CST[1] + x2 * CST[2] : NT)], BC_SLOT);
+            v += f.slot.get(b0 ? K : qa[0], b1 ? K : qa[1], b2 ? K : qa[2],
+                            ok ? f.slot.col(x0 * CST[0] + x1 * CST[1] + x2 * CST[2]) : f.slot.zero());
         }
         const bool lo0 = FACE != 0 && c[0] == 0 && t0 > 0;
         const bool lo1 = FACE != 1 && c[1] == 0 && t1 > 0;
@@ -629,8 +637,8 @@ __device__ __forceinline__ double upper_face_full(const FaceCtx<T>& f, const int
 
 // Pass 2 of the write-out: the nodes of the tile block's three upper faces,
 // whose contributions all lie in the slot array, walked by NTH threads.
-template <int K, typename T, int TX, int TY, int TZ, int NTH = TX * TY * TZ>
-__device__ __forceinline__ double upper_faces(const MeshArgs& m, const TileCoord& tc, const T* slot, int cs,
+template <int K, typename T, int TX, int TY, int TZ, int NTH, typename S>
+__device__ __forceinline__ double upper_faces(const MeshArgs& m, const TileCoord& tc, const S& slot,
                                               const T* __restrict__ x, T* __restrict__ y, T* __restrict__ part,
                                               int64_t nshared, bool dot)
 {
@@ -641,7 +649,7 @@ __device__ __forceinline__ double upper_faces(const MeshArgs& m, const TileCoord
     const int cz_n = nbz * nxy;
     const int cy_n = nby * (m.nn[2] - nbz) * nx;
     const int ny_free = m.nn[1] - nby;
-    FaceCtx<T> fc{m, tc, slot, cs, x + tile0, y + tile0, part, (unsigned)nshared, nx, nxy, nbx, nby, nbz, ny_free};
+    FaceCtx<T, S> fc{m, tc, slot, x + tile0, y + tile0, part, (unsigned)nshared, nx, nxy, nbx, nby, nbz, ny_free};
     double dsum = 0.0;
     const bool full = tc.ext[0] == K * TX + 1 && tc.ext[1] == K * TY + 1 && tc.ext[2] == K * TZ + 1;
     if (full) {
@@ -747,7 +755,8 @@ __device__ __forceinline__ double flush_two_pass(const MeshArgs& m, const TileCo
                 }
     }
 
-    return dsum + upper_faces<K, T, TX, TY, TZ>(m, tc, slot, cs, x, y, part, nshared, dot);
+    const ColSlots<N, T, NT> slots{slot};
+    return dsum + upper_faces<K, T, TX, TY, TZ, NT>(m, tc, slots, x, y, part, nshared, dot);
 }
 
 // ---------------------------------------------------------------------------
@@ -796,353 +805,6 @@ __global__ void __launch_bounds__(TX * TY * TZ) apply_slot_kernel(ApplyArgs<T> a
     __syncthreads();
     const double d = flush_two_pass<K, T, TX, TY, TZ>(m, tc, slot, CS, u, active, lx, ly, lz, cx, cy, cz, a.x, a.y,
                                                       a.part, a.nshared, DOT);
-    if constexpr (DOT) {
-        const double s = block_sum<NT>(d);
-        if (threadIdx.x == 0) VPP_ST(&a.dot_part[blockIdx.x], BC_DOT, s);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Variant 1: one x-plane of a cell per thread; x sweeps through LDS.
-
-// Pass 1 of the write-out for a plane-per-thread cell: the owned positions
-// (every index below K) of this thread's x-plane a0 = ip, from its registers
-// plus the slots of the cells below it in the tile, as flush_two_pass does for
-// a whole cell (the thread of plane ip = K owns none).
-template <int K, typename T, int TX, int TY, int TZ>
-__device__ __forceinline__ double flush_plane_owned(const MeshArgs& m, const TileCoord& tc, const T* slot, int cs,
-                                                    const T (&o)[(K + 1) * (K + 1)], int ip, int lx, int ly, int lz,
-                                                    int cx, int cy, int cz, const T* __restrict__ x,
-                                                    T* __restrict__ y, T* __restrict__ part, int64_t nshared,
-                                                    bool dot)
-{
-    constexpr int N = K + 1, NC = TX * TY * TZ;
-    if (ip >= K) return 0.0;
-    const int c = lx + TX * (ly + TY * lz), zero = NC;
-    const int nx = m.nn[0], nxy = m.nn[0] * m.nn[1];
-    const int64_t tile0 = uniform_i64(node_index(m, tc.n0[0], tc.n0[1], tc.n0[2]));
-    const T* __restrict__ xt = x + tile0;
-    T* __restrict__ yt = y + tile0;
-    const int t0 = tc.t[0], t1 = tc.t[1], t2 = tc.t[2];
-    const int nbx = m.ntile[0] - 1, nby = m.ntile[1] - 1, nbz = m.ntile[2] - 1;
-    const int cz_n = nbz * nxy;
-    const int cy_n = nby * (m.nn[2] - nbz) * nx;
-    const int ny_free = m.nn[1] - nby;
-    const unsigned nsh = (unsigned)nshared;
-    const int nb0 = lx > 0 ? c - 1 : zero, nb1 = ly > 0 ? c - TX : zero, nb2 = lz > 0 ? c - TX * TY : zero;
-    const int nb01 = lx > 0 && ly > 0 ? c - 1 - TX : zero;
-    const int nb02 = lx > 0 && lz > 0 ? c - 1 - TX * TY : zero;
-    const int nb12 = ly > 0 && lz > 0 ? c - TX - TX * TY : zero;
-    const int nb012 = lx > 0 && ly > 0 && lz > 0 ? c - 1 - TX - TX * TY : zero;
-    const bool z0 = ip == 0;
-    const bool lo0 = z0 && lx == 0 && t0 > 0, hl1 = ly == 0 && t1 > 0, hl2 = lz == 0 && t2 > 0;
-    const int faces = cell_dirichlet_faces(m, cx, cy, cz);
-    const bool dir0 = z0 && (faces & 1), dl1 = faces & 4, dl2 = faces & 16;
-    const int i0 = K * cx + ip, j0 = K * cy, l0 = K * cz;
-    const unsigned lane_b = (unsigned)(K * lx + ip + nx * K * ly + nxy * K * lz) * (unsigned)sizeof(T);
-    const int fz = i0 + nx * j0 + nxy * (t2 - 1);
-    const int fy = cz_n + i0 + nx * ((t1 - 1) + nby * (l0 - t2));
-    const int fx = cz_n + cy_n + (t0 - 1) + nbx * ((j0 - t1) + ny_free * (l0 - t2));
-    auto pos = [](int b0, int b1, int b2) { return b0 + N * (b1 + N * b2); };
-    double dsum = 0.0;
-    // x at the owned positions of this plane (identity rows copy it, x . Ax
-    // needs it), all loads issued together rather than one round trip per row
-    T xd[K * K];
-    if (dot || dir0 || dl1 || dl2) {
-#pragma unroll
-        for (int a2 = 0; a2 < K; ++a2)
-#pragma unroll
-            for (int a1 = 0; a1 < K; ++a1) xd[a1 + K * a2] = VPP_LD(at_byte(xt + (nx * a1 + nxy * a2), lane_b), BC_X);
-    }
-#pragma unroll
-    for (int a2 = 0; a2 < K; ++a2)
-#pragma unroll
-        for (int a1 = 0; a1 < K; ++a1) {
-            const bool z1 = a1 == 0, z2 = a2 == 0;
-            T val = o[a1 + N * a2];
-            if (z0) val += VPP_LD(&slot[pos(K, a1, a2) * cs + nb0], BC_SLOT);
-            if (z1) val += VPP_LD(&slot[pos(ip, K, a2) * cs + nb1], BC_SLOT);
-            if (z2) val += VPP_LD(&slot[pos(ip, a1, K) * cs + nb2], BC_SLOT);
-            if (z0 && z1) val += VPP_LD(&slot[pos(K, K, a2) * cs + nb01], BC_SLOT);
-            if (z0 && z2) val += VPP_LD(&slot[pos(K, a1, K) * cs + nb02], BC_SLOT);
-            if (z1 && z2) val += VPP_LD(&slot[pos(ip, K, K) * cs + nb12], BC_SLOT);
-            if (z0 && z1 && z2) val += VPP_LD(&slot[pos(K, K, K) * cs + nb012], BC_SLOT);
-            const int row = nx * a1 + nxy * a2;   // uniform
-            const bool lo1 = z1 && hl1, lo2 = z2 && hl2;
-            if (dir0 || (z1 && dl1) || (z2 && dl2)) {
-                const T xv = xd[a1 + K * a2];
-                VPP_ST(at_byte(yt + row, lane_b), BC_Y, xv);
-                if (dot && !(lo0 || lo1 || lo2)) dsum += (double)xv * (double)xv;
-                continue;
-            }
-            T* dst = at_byte(yt + row, lane_b);
-            if (lo0 || lo1 || lo2) {
-                const int f = lo2 ? fz + nx * a1 : (lo1 ? fy + nx * nby * a2 : fx + nbx * (a1 + ny_free * a2));
-                const int rank = (lo0 ? 1 : 0) + (lo0 ? 2 : 1) * ((lo1 ? 1 : 0) + (lo1 ? 2 : 1) * (lo2 ? 1 : 0));
-                dst = part + ((unsigned)rank * nsh + (unsigned)f);
-            }
-            VPP_ST(dst, BC_OUT, val);
-            if (dot) dsum += (double)xd[a1 + K * a2] * (double)val;
-        }
-    return dsum;
-}
-
-// Value of lane L of this lane's quad (lanes 4q .. 4q+3), by a DPP quad
-// permutation: no LDS, no barrier.  Used where the k+1 = 4 threads of a cell
-// form one quad.
-template <int L>
-__device__ __forceinline__ double quad_bcast(double v)
-{
-    constexpr int ctrl = L * 0x55;   // quad_perm(L, L, L, L)
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-template <int L>
-__device__ __forceinline__ float quad_bcast(float v)
-{
-    constexpr int ctrl = L * 0x55;
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctrl, 0xF, 0xF, true));
-}
-
-// out = sum_i c[i] v_i over the four x-planes of the cell, v_i the value of
-// quad lane i.
-template <typename T>
-__device__ __forceinline__ T quad_dot(const T (&c)[4], T v)
-{
-    T s = c[0] * quad_bcast<0>(v);
-    s = fma(c[1], quad_bcast<1>(v), s);
-    s = fma(c[2], quad_bcast<2>(v), s);
-    return fma(c[3], quad_bcast<3>(v), s);
-}
-
-// Entry (r, i) of a 1D matrix for a runtime row r (COL: entry (i, r)).
-template <int K, Mat M, bool COL>
-__device__ __forceinline__ double pick(int r, int i)
-{
-    double v = 0.0;
-#pragma unroll
-    for (int rr = 0; rr < K + 1; ++rr)
-        if (r == rr) v = COL ? mat<K, M>(i, rr) : mat<K, M>(rr, i);
-    return v;
-}
-
-template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS = false>
-__global__ void __launch_bounds__((K + 1) * TX * TY * TZ) apply_plane_kernel(ApplyArgs<T> a)
-{
-    constexpr int N = K + 1, N2 = N * N, NC = TX * TY * TZ, NT = N * NC;
-    constexpr int BX = K * TX + 1, BY = K * TY + 1, BZ = K * TZ + 1;
-    constexpr int CS = N * N2 + 1;           // padded per-cell stride of the exchange buffers
-    constexpr int SS = NC + 1;               // slot column stride (column NC stays zero)
-    // k = 3: the four threads of a cell are one lane quad, and the x sweeps
-    // exchange planes by DPP quad permutations instead of through LDS
-    constexpr bool QUAD = N == 4;
-    static_assert(N * N2 * SS <= 2 * NC * CS, "slots must fit in the exchange buffers");
-    __shared__ T xb[2 * NC * CS];
-    VPP_BC_BEGIN(a.x, a.y, a.phi, a.part, a.dot_part, xb, (int64_t)a.m.nn[0] * a.m.nn[1] * a.m.nn[2],
-                 8 * a.nshared, (int64_t)gridDim.x, 2 * NC * CS);
-    if (a.done && *a.done) return;
-    const MeshArgs& m = a.m;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
-    const TileCoord tc = tile_coord<K, TX, TY, TZ>(m, tile);
-    const int cell = threadIdx.x / N, ip = threadIdx.x % N;
-    const int lx = cell % TX, ly = (cell / TX) % TY, lz = cell / (TX * TY);
-    const int cx = tc.t[0] * TX + lx, cy = tc.t[1] * TY + ly, cz = tc.t[2] * TZ + lz;
-    const bool active = cx < m.nc[0] && cy < m.nc[1] && cz < m.nc[2];
-    T* X1 = xb + cell * CS;
-    T* X2 = xb + (NC + cell) * CS;
-    const int64_t nx = m.nn[0], nxy = (int64_t)m.nn[0] * m.nn[1];
-    const int64_t base = active ? node_index(m, (int64_t)K * cx + ip, (int64_t)K * cy, (int64_t)K * cz) : 0;
-    T rS[N], rD[N], cS[N], cD[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        rS[i] = T(pick<K, MS, false>(ip, i));
-        rD[i] = T(pick<K, MD, false>(ip, i));
-        cS[i] = T(pick<K, MS, true>(ip, i));
-        cD[i] = T(pick<K, MD, true>(ip, i));
-    }
-    T wx = T(0);
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-        if (ip == i) wx = T(Tab<K>::t.w[i]);
-
-    // Coefficient: phi plane at x-node ip -> Gauss in (y,z) -> exchange -> Gauss in x.
-    T cw[N2];
-    if (active) {
-#pragma unroll
-        for (int l = 0; l < N; ++l)
-#pragma unroll
-            for (int j = 0; j < N; ++j) cw[j + N * l] = T(VPP_LD(&a.phi[base + nx * j + nxy * l], BC_PHI));
-        sweep2<K, MS, false, 0>(cw);
-        sweep2<K, MS, false, 1>(cw);
-        if constexpr (QUAD) {
-            // one value at a time (the scheduler would otherwise issue every
-            // permutation first and hold all results in registers)
-#pragma unroll
-            for (int q = 0; q < N2; ++q) {
-                cw[q] = quad_dot<T>(rS, cw[q]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) X1[ip * N2 + q] = cw[q];
-        }
-    }
-    if constexpr (!QUAD) {
-        __syncthreads();
-        if (active) {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) {
-                T s = rS[0] * X1[q];
-#pragma unroll
-                for (int i = 1; i < N; ++i) s = fma(rS[i], X1[i * N2 + q], s);
-                cw[q] = s;
-            }
-        }
-        __syncthreads();
-    }
-    if (active) {
-#pragma unroll
-        for (int q = 0; q < N2; ++q)
-            cw[q] = coef_scaled<HV>(m, cw[q]) * (wx * T(Tab<K>::t.w[q % N] * Tab<K>::t.w[q / N]));
-    }
-
-    // Operand plane at x-node ip (Dirichlet entries zeroed).
-    T uq[N2], gx[N2];
-    if (active) {
-        const int faces = cell_dirichlet_faces(m, cx, cy, cz);
-#pragma unroll
-        for (int l = 0; l < N; ++l)
-#pragma unroll
-            for (int j = 0; j < N; ++j) uq[j + N * l] = T(VPP_LD(&a.x[base + nx * j + nxy * l], BC_X));
-        // Dirichlet entries zeroed after every load has been issued
-        if (faces) {
-#pragma unroll
-            for (int l = 0; l < N; ++l)
-#pragma unroll
-                for (int j = 0; j < N; ++j)
-                    if (local_dirichlet<K>(faces, ip, j, l)) uq[j + N * l] = T(0);
-        }
-        sweep2<K, MS, false, 0>(uq);
-        sweep2<K, MS, false, 1>(uq);
-        if constexpr (QUAD) {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) {
-                const T v[4] = {quad_bcast<0>(uq[q]), quad_bcast<1>(uq[q]), quad_bcast<2>(uq[q]),
-                                quad_bcast<3>(uq[q])};
-                T s = rS[0] * v[0], d = rD[0] * v[0];
-#pragma unroll
-                for (int i = 1; i < 4; ++i) {
-                    s = fma(rS[i], v[i], s);
-                    d = fma(rD[i], v[i], d);
-                }
-                uq[q] = s;
-                gx[q] = d;
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) X1[ip * N2 + q] = uq[q];
-        }
-    }
-    if constexpr (!QUAD) {
-        __syncthreads();
-        if (active) {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) {
-                const T v0 = X1[q];
-                T s = rS[0] * v0, d = rD[0] * v0;
-#pragma unroll
-                for (int i = 1; i < N; ++i) {
-                    const T v = X1[i * N2 + q];
-                    s = fma(rS[i], v, s);
-                    d = fma(rD[i], v, d);
-                }
-                uq[q] = s;
-                gx[q] = d;
-            }
-        }
-        __syncthreads();
-    }
-    T o[N2];
-    if constexpr (QUAD) __syncthreads();   // bounds the scheduling region (register pressure)
-    if (active) {
-        T gy[N2];
-        // mass shift: mu hx hy hz wref u at this thread's Gauss points, added to
-        // the values that the transposed interpolation in x receives
-        T mv[MASS ? N2 : 1];
-        if constexpr (MASS) {
-            const T ms = T(m.mass) * wx;
-#pragma unroll
-            for (int q = 0; q < N2; ++q) mv[q] = ms * T(Tab<K>::t.w[q % N] * Tab<K>::t.w[q / N]) * uq[q];
-        }
-#pragma unroll
-        for (int q = 0; q < N2; ++q) gy[q] = uq[q];
-        sweep2<K, MDC, false, 0>(gy);
-        sweep2<K, MDC, false, 1>(uq);     // uq now holds the z derivative
-        const T r1 = T(m.rd[1]), r2 = T(m.rd[2]);
-#pragma unroll
-        for (int q = 0; q < N2; ++q) {
-            gx[q] *= cw[q];
-            gy[q] *= cw[q] * r1;
-            uq[q] *= cw[q] * r2;
-        }
-        sweep2<K, MDC, true, 0>(gy);
-        sweep2<K, MDC, true, 1>(uq);
-        if constexpr (MASS) {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) gy[q] += mv[q];
-        }
-        if constexpr (QUAD) {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) {
-                o[q] = quad_dot<T>(cS, gy[q] + uq[q]) + quad_dot<T>(cD, gx[q]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) {
-                X1[ip * N2 + q] = gy[q] + uq[q];
-                X2[ip * N2 + q] = gx[q];
-            }
-        }
-    }
-    if constexpr (!QUAD) {
-        __syncthreads();
-        if (active) {
-#pragma unroll
-            for (int q = 0; q < N2; ++q) {
-                T s = cS[0] * X1[q];
-                s = fma(cD[0], X2[q], s);
-#pragma unroll
-                for (int i = 1; i < N; ++i) {
-                    s = fma(cS[i], X1[i * N2 + q], s);
-                    s = fma(cD[i], X2[i * N2 + q], s);
-                }
-                o[q] = s;
-            }
-        }
-    }
-    if (active) {
-        sweep2<K, MS, true, 0>(o);
-        sweep2<K, MS, true, 1>(o);
-    }
-    // exchange of the cell results through slots (no atomics), on the x buffers
-    __syncthreads();
-    T* slot = xb;
-    for (int q = threadIdx.x; q < N * N2; q += NT) VPP_ST(&slot[q * SS + NC], BC_SLOT, T(0));
-    if (active) {
-#pragma unroll
-        for (int l = 0; l < N; ++l)
-#pragma unroll
-            for (int j = 0; j < N; ++j) VPP_ST(&slot[(ip + N * (j + N * l)) * SS + cell], BC_SLOT, o[j + N * l]);
-    }
-    __syncthreads();
-    double d = 0.0;
-    if (active)
-        d = flush_plane_owned<K, T, TX, TY, TZ>(m, tc, slot, SS, o, ip, lx, ly, lz, cx, cy, cz, a.x, a.y, a.part,
-                                                a.nshared, DOT);
-    d += upper_faces<K, T, TX, TY, TZ, NT>(m, tc, slot, SS, a.x, a.y, a.part, a.nshared, DOT);
     if constexpr (DOT) {
         const double s = block_sum<NT>(d);
         if (threadIdx.x == 0) VPP_ST(&a.dot_part[blockIdx.x], BC_DOT, s);
@@ -1450,7 +1112,8 @@ __global__ void __launch_bounds__(2 * TX * TY * TZ) apply_half_kernel(ApplyArgs<
     if (active)
         dsum = flush_half_owned<K, T, TX, TY, TZ>(m, tc, slot, CS, v, pl, lx, ly, lz, cx, cy, cz, a.x, a.y, a.part,
                                                   a.nshared, DOT);
-    dsum += upper_faces<K, T, TX, TY, TZ, NTH>(m, tc, slot, CS, a.x, a.y, a.part, a.nshared, DOT);
+    const ColSlots<N, T, NC> slots{slot};
+    dsum += upper_faces<K, T, TX, TY, TZ, NTH>(m, tc, slots, a.x, a.y, a.part, a.nshared, DOT);
     if constexpr (DOT) {
         const double sum = block_sum<NTH>(dsum);
         if (threadIdx.x == 0) VPP_ST(&a.dot_part[blockIdx.x], BC_DOT, sum);

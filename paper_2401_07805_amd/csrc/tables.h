@@ -77,31 +77,49 @@ constexpr Tables<K> make_tables()
         g[1] = -c_sqrt(3.0 / 7.0); g[2] = 0.0; g[3] = c_sqrt(3.0 / 7.0);
     }
     for (int i = 0; i < N; ++i) t.gll[i] = 0.5 * (g[i] + 1.0);
-    // Lagrange values / derivatives by the product formula.
+    // Lagrange values / derivatives by the product formula, on [-1,1] (where the
+    // points are exactly symmetric and their differences lose nothing to the
+    // shift); the derivatives on [0,1] are twice those.
     for (int q = 0; q < N; ++q)
         for (int a = 0; a < N; ++a) {
             double v = 1.0;
             for (int b = 0; b < N; ++b)
-                if (b != a) v *= (t.gx[q] - t.gll[b]) / (t.gll[a] - t.gll[b]);
+                if (b != a) v *= (x[q] - g[b]) / (g[a] - g[b]);
             t.S[q][a] = v;
             double d = 0.0;
             for (int m = 0; m < N; ++m) {
                 if (m == a) continue;
-                double p = 1.0 / (t.gll[a] - t.gll[m]);
+                double p = 2.0 / (g[a] - g[m]);
                 for (int b = 0; b < N; ++b)
-                    if (b != a && b != m) p *= (t.gx[q] - t.gll[b]) / (t.gll[a] - t.gll[b]);
+                    if (b != a && b != m) p *= (x[q] - g[b]) / (g[a] - g[b]);
                 d += p;
             }
             t.D[q][a] = d;
             double dc = 0.0;
             for (int m = 0; m < N; ++m) {
                 if (m == a) continue;
-                double p = 1.0 / (t.gx[a] - t.gx[m]);
+                double p = 2.0 / (x[a] - x[m]);
                 for (int b = 0; b < N; ++b)
-                    if (b != a && b != m) p *= (t.gx[q] - t.gx[b]) / (t.gx[a] - t.gx[b]);
+                    if (b != a && b != m) p *= (x[q] - x[b]) / (x[a] - x[b]);
                 dc += p;
             }
             t.Dc[q][a] = dc;
+        }
+    // The points are symmetric about 1/2, so S is even and D, Dc are odd under
+    // (q, a) -> (N-1-q, N-1-a); made exact here, since the sweeps keep their
+    // constants in scalar registers and equal magnitudes then share one (the
+    // k = 4 apply held 44 distinct ones, spilled and read back lane by lane:
+    // 394 v_readlane of 3966 vector instructions).
+    for (int q = 0; q < N; ++q)
+        for (int a = 0; a < N; ++a) {
+            const int qm = N - 1 - q, am = N - 1 - a;
+            if (q * N + a > qm * N + am) continue;
+            const double v = 0.5 * (t.S[q][a] + t.S[qm][am]);
+            const double d = 0.5 * (t.D[q][a] - t.D[qm][am]);
+            const double dc = 0.5 * (t.Dc[q][a] - t.Dc[qm][am]);
+            t.S[q][a] = t.S[qm][am] = v;
+            t.D[q][a] = d; t.D[qm][am] = -d;
+            t.Dc[q][a] = dc; t.Dc[qm][am] = -dc;
         }
     // Exact structural zeros/ones: for odd N the middle Gauss point is the middle
     // GLL node, so that row of S is a unit vector.
