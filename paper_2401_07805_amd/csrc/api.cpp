@@ -69,11 +69,29 @@ struct DeviceGuard {
     }
 };
 
-LaunchCfg default_config(int k)
+// Kernel configuration of a new problem, by degree, precision and number of
+// cells (vpp_tune measures instead).  Measured hot, one apply, us, FP64 / FP32:
+//  k = 2: the plane kernel gives a small mesh three times the waves of the
+//    cell-per-thread one, each with a third of the serial work (24^3 cells: 11.1
+//    against 12.7 / 10.8 against 12.9); a mesh that fills the GPU prefers the
+//    latter's fewer LDS accesses (32^3: 12.9 against 13.1 in FP64 but still 11.1
+//    against 13.0 in FP32; 48^3: 17.9 against 22.5 / 14.9 against 16.6).
+//  k = 3: small tiles until there are enough of them for every CU (20^3: 4x4x2
+//    13.6 against 17.3 with 8x4x4), then the fewer shared nodes of 8x4x4 (32^3:
+//    19.7 against 20.5, 64^3: 80 against 88 / 52 against 56).
+//  k = 4: the same, in multiples of the 12 cells of a wave (16^3: 4x3x2 16.1
+//    against 17.6 with 4x4x3; 32^3: 35.4 against 38.9; in FP32 6x4x2 23.1
+//    against 24.1 with 4x4x3).
+LaunchCfg default_config(int k, int prec, int64_t ncell)
 {
-    if (k == 2) return LaunchCfg{4, {8, 8, 4}};
-    if (k == 3) return LaunchCfg{1, {4, 4, 2}};
-    return LaunchCfg{1, {4, 2, 2}};
+    const bool f32 = prec == VPP_FP32;
+    if (k == 2) {
+        if (ncell <= (f32 ? 50000 : 20000)) return LaunchCfg{1, {8, 4, 2}};
+        return f32 ? LaunchCfg{4, {16, 8, 4}} : LaunchCfg{4, {8, 8, 4}};
+    }
+    if (k == 3) return ncell <= 16000 ? LaunchCfg{1, {4, 4, 2}} : LaunchCfg{1, {8, 4, 4}};
+    if (ncell <= 8000) return LaunchCfg{1, {4, 3, 2}};
+    return f32 ? LaunchCfg{1, {6, 4, 2}} : LaunchCfg{1, {4, 4, 3}};
 }
 
 template <typename T>
@@ -1078,18 +1096,19 @@ vpp_status vpp_create(const vpp_desc* d, vpp_problem* out)
     p->ncell = ncell;
     p->NQ = ncell * (k + 1) * (k + 1) * (k + 1);
     p->m = make_mesh_args(*d);
-    p->cfg = default_config(p->k);
+    p->cfg = default_config(p->k, VPP_FP64, ncell);
+    p->cfg32 = default_config(p->k, VPP_FP32, ncell);
     if (arith_law(*d)) {
         LaunchCfg ac[4];
         if (list_arith_configs(p->k, ac, 4) < 1) {
             delete p;
             return fail(VPP_ERR_UNSUPPORTED, "no kernel configuration with the arithmetic density mean");
         }
-        p->cfg = ac[0];
+        p->cfg = p->cfg32 = ac[0];
     }
     set_tiles(p->m, p->cfg);
     p->m32 = p->m;
-    p->cfg32 = p->cfg;
+    set_tiles(p->m32, p->cfg32);
     vpp_status s;
     if ((s = dev_alloc(&p->phi64, N, "phi")) || (s = dev_alloc(&p->phi32, N, "phi32")) ||
         (s = dev_alloc(&p->diag, N, "diag")) || (s = dev_alloc(&p->inv64, N, "invdiag")) ||
