@@ -15,7 +15,7 @@ LIB_DEBUG = os.path.join(HERE, "libvpp_debug.so")
 # template-heavy units compile in parallel
 APPLY_UNITS = [f"apply_{p}_k{k}.hip" for p in ("f64", "f32") for k in (2, 3, 4)]
 SOURCES = [*APPLY_UNITS, "apply_f64.hip", "apply_f32.hip", "apply_misc.hip", "blas.hip", "adjoint.hip",
-           "closest_point.hip", "levelset.hip", "noalloc.hip", "amr.hip", "api.cpp"]
+           "closest_point.hip", "levelset.hip", "reinit.hip", "noalloc.hip", "amr.hip", "api.cpp"]
 # the sources whose code changes under VPP_BOUNDS_CHECK (the instrumented
 # kernels and the entry point that reads their counters); the debug library
 # links the release objects of the others

@@ -287,13 +287,13 @@ static MeshArgs make_mesh_args(const vpp_desc& d)
 // Scratch of the apply for the current configurations of both precisions: the
 // partials of shared-face nodes (8 ranks x shared nodes, FP64-sized) and one
 // partial dot product per tile.
-// Cell-major scratch of the kernels that sum per-cell contributions into the
-// nodes (dJ/dphi, the filter right-hand sides, the reinitialization pieces):
-// nvec arrays of cell_values entries.  The calls using it are ordered by an
-// event, also when they run on different streams.
-static vpp_status cell_scratch_begin(vpp_problem p, int nvec, hipStream_t s, double** out)
+// Scratch of `need` doubles: the cell-major arrays (cell_values entries each) of
+// the kernels that sum per-cell contributions into the nodes (dJ/dphi, the
+// filter right-hand sides, the reinitialization's diagonal and right-hand side)
+// and the partials of the reinitialization operator.  The calls using it are
+// ordered by an event, also when they run on different streams.
+static vpp_status scratch_begin(vpp_problem p, size_t need, hipStream_t s, double** out)
 {
-    const size_t need = (size_t)nvec * (size_t)cell_values(p->k, p->m);
     if (need > p->cellbuf_n) {
         if (p->cellbuf) {
             VPP_HIP(hipDeviceSynchronize());   // a previous call may still read it
@@ -309,6 +309,11 @@ static vpp_status cell_scratch_begin(vpp_problem p, int nvec, hipStream_t s, dou
     else VPP_HIP(hipStreamWaitEvent(s, p->cell_evt, 0));
     *out = p->cellbuf;
     return VPP_OK;
+}
+
+static vpp_status cell_scratch_begin(vpp_problem p, int nvec, hipStream_t s, double** out)
+{
+    return scratch_begin(p, (size_t)nvec * (size_t)cell_values(p->k, p->m), s, out);
 }
 
 static vpp_status cell_scratch_end(vpp_problem p, hipStream_t s)
@@ -1445,8 +1450,7 @@ static vpp_status ensure_reinit_work(vpp_problem p)
         (st = dev_alloc(&w->p, n, "reinit p")) || (st = dev_alloc(&w->q, n, "reinit q")) ||
         (st = dev_alloc(&w->x, n, "reinit x")) || (st = dev_alloc(&w->diag, n, "reinit diag")) ||
         (st = dev_alloc(&w->invd, n, "reinit inverse diag")) || (st = dev_alloc(&w->inv32, n, "reinit inverse diag")) ||
-        (st = dev_alloc(&w->red, kRedDoubles, "reinit partials")) ||
-        (st = dev_alloc(&w->dot, kMaxRedBlocks, "reinit dot partials")) || (st = dev_alloc(&w->rr, 1, "norm")) ||
+        (st = dev_alloc(&w->red, kRedDoubles, "reinit partials")) || (st = dev_alloc(&w->rr, 1, "norm")) ||
         (st = dev_alloc(&w->st, 1, "reinit state"))) {
         free_reinit(w);
         return st;
@@ -1458,6 +1462,29 @@ static vpp_status ensure_reinit_work(vpp_problem p)
     }
     p->rw = w;
     return VPP_OK;
+}
+
+// Arguments of the reinitialization kernels: natural conditions on every face
+// (no identity rows, whatever the problem's faces), tiles of its operator.
+static ReinitArgs reinit_geometry(vpp_problem p, const double* n0, const double* n1, const double* n2,
+                                  const vpp_reinit_opts* o)
+{
+    ReinitArgs ra{rhs_geometry(p), o->eps, 1.0 / o->dtau, n0, n1, n2};
+    ra.g.m.bcmask = 0;
+    set_tiles(ra.g.m, reinit_config(p->k, ra.g.m));
+    return ra;
+}
+
+// Doubles of scratch of the operator: partials of the shared nodes, then one
+// partial of x . y per tile.
+static size_t reinit_scratch(const MeshArgs& m) { return 8 * (size_t)shared_stride(m) + (size_t)tile_count(m); }
+
+// The kernels index the partials with 32 bits (as ensure_apply_scratch checks
+// for the apply); a mesh past that has outgrown the memory for the step's vectors.
+static vpp_status reinit_tiles_ok(const MeshArgs& m)
+{
+    if (8 * shared_stride(m) < (int64_t(1) << 32)) return VPP_OK;
+    return fail(VPP_ERR_UNSUPPORTED, "mesh too large for 32-bit partial indices of the reinitialization operator");
 }
 
 vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, const double* n1, const double* n2,
@@ -1475,21 +1502,20 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
     hipStream_t s = p->stream;
     ReinitWork& w = *p->rw;
     const int64_t n = p->N;
-    ReinitArgs ra{rhs_geometry(p), o->eps, 1.0 / o->dtau, n0, n1, n2};
-    // natural conditions on every face: no identity rows, whatever the problem's faces
-    ra.g.m.bcmask = 0;
-    MeshArgs m1 = ra.g.m;
-    m1.ntile[0] = m1.ntile[1] = m1.ntile[2] = 1;
-    const int one[3] = {1, 1, 1};
-    const SharedEnum none = shared_enum(m1, p->k, one);   // no shared nodes: q is used as it is
-    const int gdot = (int)std::max<int64_t>(1, std::min<int64_t>(kMaxRedBlocks, (n + 1023) / 1024));
+    const ReinitArgs ra = reinit_geometry(p, n0, n1, n2, o);
+    const SharedEnum shared = shared_enum(ra.g.m, p->k, reinit_config(p->k, ra.g.m).tile);
+    const int64_t stride = shared_stride(ra.g.m);
+    const int ntiles = tile_count(ra.g.m);
     double* cv;
-    if ((st = cell_scratch_begin(p, 1, s, &cv))) return st;
+    if ((st = reinit_tiles_ok(ra.g.m))) return st;
+    if ((st = scratch_begin(p, std::max((size_t)cell_values(p->k, p->m), reinit_scratch(ra.g.m)), s, &cv))) return st;
+    double* const dot_part = cv + 8 * stride;
+    const ReinitApplyArgs plain{ra, w.x, w.q, cv, stride, nullptr, nullptr, false};
     VPP_HIP(launch_reinit_rhs(p->k, ra, psi, w.b, cv, s));
     VPP_HIP(launch_reinit_diag(p->k, ra, w.diag, cv, s));
     VPP_HIP(launch_fix_diagonal(ra.g.m, w.diag, w.invd, w.inv32, s));
     VPP_HIP(hipMemcpyAsync(w.x, psi, n * sizeof(double), hipMemcpyDeviceToDevice, s));
-    VPP_HIP(launch_reinit_apply(p->k, ra, w.x, w.q, cv, s));
+    VPP_HIP(launch_reinit_apply(p->k, plain, s));
     CgState* hs = w.hst;
     std::memset(hs, 0, sizeof(CgState));
     VPP_HIP(hipMemcpyAsync(w.st, hs, sizeof(CgState), hipMemcpyHostToDevice, s));
@@ -1523,10 +1549,11 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
         for (int done = 0; done < o->max_iter + chunk;) {
             for (int it = 0; it < chunk; ++it, ++done) {
                 const int par = done & 1;
-                VPP_HIP(launch_reinit_apply(p->k, ra, w.p, w.q, cv, s));
-                VPP_HIP(launch_dot_partials(w.p, w.q, n, w.dot, gdot, s));
-                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, w.dot, gdot, ra.g.m, none, nullptr, 0,
-                                                          w.r, w.q, w.invd, n, s));
+                // tile kernel (with p.q partials); the update assembles the shared nodes
+                const ReinitApplyArgs a{ra, w.p, w.q, cv, stride, dot_part, &w.st->halt[par], true};
+                VPP_HIP(launch_reinit_apply(p->k, a, s));
+                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, dot_part, ntiles, ra.g.m, shared, cv,
+                                                          stride, w.r, w.q, w.invd, n, s));
                 VPP_HIP(launch_cg_pupdate<double>(w.st, par, w.red, w.x, w.r, w.p, w.invd, n, s));
             }
             VPP_HIP(hipMemcpyAsync(hs, w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
@@ -1540,7 +1567,7 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
         else inf.status = VPP_ERR_NOT_CONVERGED;
     }
     // true residual, then the new level set
-    VPP_HIP(launch_reinit_apply(p->k, ra, w.x, w.q, cv, s));
+    VPP_HIP(launch_reinit_apply(p->k, plain, s));
     VPP_HIP(launch_residual(w.b, w.q, nullptr, n, w.red, w.rr, s));
     if ((st = cell_scratch_end(p, s))) return st;
     VPP_HIP(hipMemcpyAsync(w.hrr, w.rr, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1562,8 +1589,7 @@ static vpp_status reinit_args(vpp_problem p, const double* n0, const double* n1,
     VPP_ALIGNED(8, n0, n1, n2);
     if (!(o->eps > 0.0) || !std::isfinite(o->eps) || !(o->dtau > 0.0) || !std::isfinite(o->dtau))
         return fail(VPP_ERR_INVALID_ARG, "reinitialization eps and dtau must be positive and finite");
-    *ra = ReinitArgs{rhs_geometry(p), o->eps, 1.0 / o->dtau, n0, n1, n2};
-    ra->g.m.bcmask = 0;
+    *ra = reinit_geometry(p, n0, n1, n2, o);
     return VPP_OK;
 }
 
@@ -1580,8 +1606,10 @@ vpp_status vpp_reinit_apply(vpp_problem p, const double* n0, const double* n1, c
     DeviceGuard dg(p->desc.device);
     hipStream_t s = (hipStream_t)stream;
     double* cv;
-    if ((st = cell_scratch_begin(p, 1, s, &cv))) return st;
-    VPP_HIP(launch_reinit_apply(p->k, ra, x, y, cv, s));
+    if ((st = reinit_tiles_ok(ra.g.m))) return st;
+    if ((st = scratch_begin(p, reinit_scratch(ra.g.m), s, &cv))) return st;
+    const ReinitApplyArgs a{ra, x, y, cv, shared_stride(ra.g.m), nullptr, nullptr, false};
+    VPP_HIP(launch_reinit_apply(p->k, a, s));
     return cell_scratch_end(p, s);
 }
 

@@ -164,8 +164,22 @@ struct ReinitArgs {
     const double* n1;
     const double* n2;
 };
+// y = A x on tiles (reinit_config's; r.g.m holds their counts): the tile kernel
+// (interior nodes of y, partials of the shared nodes, per-tile partials of x . y
+// if dot_part), then, unless tiles_only, the assembly of the shared nodes.
+struct ReinitApplyArgs {
+    ReinitArgs r;
+    const double* x;
+    double* y;
+    double* part;       // 8 nshared doubles
+    int64_t nshared;    // shared_stride
+    double* dot_part;   // optional: one partial of x . y per tile
+    const int* done;    // optional: return at once when *done != 0
+    bool tiles_only;
+};
+LaunchCfg reinit_config(int k, const MeshArgs& m);
+hipError_t launch_reinit_apply(int k, const ReinitApplyArgs& a, hipStream_t s);
 // cv: cell_values(k, m) doubles of scratch each.
-hipError_t launch_reinit_apply(int k, const ReinitArgs& r, const double* x, double* y, double* cv, hipStream_t s);
 hipError_t launch_reinit_diag(int k, const ReinitArgs& r, double* diag, double* cv, hipStream_t s);
 hipError_t launch_reinit_rhs(int k, const ReinitArgs& r, const double* psi, double* b, double* cv, hipStream_t s);
 // part[b] = partial of x . y over the elements workgroup b visits (nblocks <= 1024).

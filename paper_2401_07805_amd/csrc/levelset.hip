@@ -1,7 +1,7 @@
 // Right-hand sides of the level-set filter systems (Eqs. normal_vector and
 // normal_vector_regularized, curvature and curvature_regularized), and the
-// operator, diagonal and right-hand side of one semi-implicit step of
-// Eq. reinitialization (further below):
+// diagonal and right-hand side of one semi-implicit step of
+// Eq. reinitialization (further below; its operator is in reinit.hip):
 //   normal:    b_d = (n_bar_d, v) with n_bar = grad phi_h / |grad phi_h| at every
 //              Gauss point (zero where the gradient vanishes), d = x, y, z;
 //   curvature: b = (kappa_bar, v) with kappa_bar = -div n_h at every Gauss point,
@@ -212,31 +212,6 @@ __device__ __forceinline__ void normal_at_gauss(const ReinitArgs& r, int cx, int
     }
 }
 
-// One nodal normal component at the Gauss points of a cell.
-template <int K, int D>
-__device__ __forceinline__ void normal_comp_at_gauss(const ReinitArgs& r, int cx, int cy, int cz,
-                                                     double (&nd)[(K + 1) * (K + 1) * (K + 1)])
-{
-    load_nodes<K>(r.g.m, D == 0 ? r.n0 : (D == 1 ? r.n1 : r.n2), cx, cy, cz, nd);
-    sweep3<K, MS, false, 0>(nd);
-    sweep3<K, MS, false, 1>(nd);
-    sweep3<K, MS, false, 2>(nd);
-}
-
-template <int K, int D>
-__device__ __forceinline__ void add_directional(const double (&u)[(K + 1) * (K + 1) * (K + 1)],
-                                                const double (&n)[(K + 1) * (K + 1) * (K + 1)], double ih,
-                                                double (&s)[(K + 1) * (K + 1) * (K + 1)])
-{
-    constexpr int N3 = (K + 1) * (K + 1) * (K + 1);
-    double g[N3];
-#pragma unroll
-    for (int q = 0; q < N3; ++q) g[q] = u[q];
-    sweep3<K, MDC, false, D>(g);
-#pragma unroll
-    for (int q = 0; q < N3; ++q) s[q] = fma(n[q] * ih, g[q], s[q]);
-}
-
 // out += Dc_D^T (w n ih) at the Gauss points.
 template <int K, int D>
 __device__ __forceinline__ void add_flux(const double (&w)[(K + 1) * (K + 1) * (K + 1)],
@@ -250,45 +225,6 @@ __device__ __forceinline__ void add_flux(const double (&w)[(K + 1) * (K + 1) * (
     sweep3<K, MDC, true, D>(g);
 #pragma unroll
     for (int q = 0; q < N3; ++q) out[q] += g[q];
-}
-
-template <int K>
-__global__ void __launch_bounds__(64) reinit_apply_kernel(ReinitArgs r, const double* __restrict__ x,
-                                                          double* __restrict__ cv)
-{
-    constexpr int N = K + 1, N3 = N * N * N;
-    const MeshArgs& m = r.g.m;
-    int cx, cy, cz;
-    if (!cell_of(m, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, cx, cy, cz)) return;
-    // One normal component is live at a time (interpolated again for the
-    // flux pass): holding all three at the Gauss points left one wave per SIMD.
-    double u[N3], s[N3], out[N3], nd[N3];
-    load_nodes<K>(m, x, cx, cy, cz, u);
-    sweep3<K, MS, false, 0>(u);
-    sweep3<K, MS, false, 1>(u);
-    sweep3<K, MS, false, 2>(u);
-#pragma unroll
-    for (int q = 0; q < N3; ++q) s[q] = 0.0;
-    normal_comp_at_gauss<K, 0>(r, cx, cy, cz, nd);
-    add_directional<K, 0>(u, nd, r.g.ih[0], s);
-    normal_comp_at_gauss<K, 1>(r, cx, cy, cz, nd);
-    add_directional<K, 1>(u, nd, r.g.ih[1], s);
-    normal_comp_at_gauss<K, 2>(r, cx, cy, cz, nd);
-    add_directional<K, 2>(u, nd, r.g.ih[2], s);
-#pragma unroll
-    for (int q = 0; q < N3; ++q) {
-        const double w = r.g.vol * wref<K>(q % N, (q / N) % N, q / (N * N));
-        out[q] = r.idtau * w * u[q];
-        s[q] *= r.eps * w;
-    }
-    normal_comp_at_gauss<K, 0>(r, cx, cy, cz, nd);
-    add_flux<K, 0>(s, nd, r.g.ih[0], out);
-    normal_comp_at_gauss<K, 1>(r, cx, cy, cz, nd);
-    add_flux<K, 1>(s, nd, r.g.ih[1], out);
-    normal_comp_at_gauss<K, 2>(r, cx, cy, cz, nd);
-    add_flux<K, 2>(s, nd, r.g.ih[2], out);
-    transpose_interp<K>(out);
-    store_cell<K>(m, cx, cy, cz, out, cv);
 }
 
 // Transposed sweep along DIR with the product table T0(q,a) T1(q,a) of the
@@ -479,13 +415,6 @@ hipError_t launch_curvature_rhs(int k, const RhsGeo& g, const double* n0, const 
     const MeshArgs& m = g.m;
     VPP_CELLS(curvature_rhs_kernel, g, n0, n1, n2, cv)
     return launch_node_sum(k, m, cv, b, s);
-}
-
-hipError_t launch_reinit_apply(int k, const ReinitArgs& r, const double* x, double* y, double* cv, hipStream_t s)
-{
-    const MeshArgs& m = r.g.m;
-    VPP_CELLS(reinit_apply_kernel, r, x, cv)
-    return launch_node_sum(k, m, cv, y, s);
 }
 
 hipError_t launch_reinit_diag(int k, const ReinitArgs& r, double* diag, double* cv, hipStream_t s)

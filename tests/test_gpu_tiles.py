@@ -1,0 +1,84 @@
+"""Tile edges of the plane-per-thread kernels (apply variant 1 and the
+reinitialization operator) and of the default configurations: meshes one cell
+below, at and one above each instantiated tile, and one with several tiles per
+direction, against the FP64 oracle.  Bars as elsewhere: FP64 1e-12, FP32 2e-6
+(relative 2-norm)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from gpu_util import dev, host, rel, say
+
+pytestmark = pytest.mark.gpu
+
+vpp = pytest.importorskip("paper_2401_07805_amd")
+
+
+def edge_boxes(tile):
+    t = np.array(tile)
+    return [tuple(int(v) for v in b) for b in (np.maximum(t - 1, 1), t, t + 1, np.minimum(2 * t + 1, (9, 9, 9)))]
+
+
+@pytest.mark.parametrize("k", [2, 3, 4])
+def test_plane_apply_tile_edges(k):
+    cfgs = [c for c in vpp.config_candidates(k) if c["variant"] == 1]
+    assert cfgs
+    for cfg in cfgs:
+        for nc in edge_boxes(cfg["tile"]):
+            m = W.Mesh(ncells=nc, degree=k, bc=(0, 1, 1, 0, 0, 1), extent=(1.0, 0.8, 1.1), rho_l=1000.0, rho_g=1.0)
+            phi = W.droplet_phi(m, 0.3, 0.1)
+            x = W.uniform_vectors(5, 1, m.ndofs)[0]
+            yref = oracle.Operator(m, phi=phi).matvec(x)
+            p = vpp.Problem.from_mesh(m)
+            p.set_phi(dev(phi))
+            p.set_config(cfg["variant"], cfg["tile"])
+            say("plane apply", k, cfg, nc)
+            assert rel(host(p.apply(dev(x))), yref) < 1e-12, (cfg, nc)
+            y32 = host(p.apply(dev(x).float()).double())
+            assert rel(y32, yref) < 2e-6, (cfg, nc)
+
+
+# around the tiles 8x4x2 (k = 2), 4x4x2 and 4x4x4 (k = 3), 4x3x2 (k = 4)
+@pytest.mark.parametrize("k,ncells", [(2, (1, 1, 1)), (2, (7, 3, 1)), (2, (8, 4, 2)), (2, (9, 5, 3)), (2, (17, 9, 5)),
+                                      (3, (1, 1, 1)), (3, (4, 4, 2)), (3, (5, 5, 3)), (3, (3, 9, 5)),
+                                      (4, (1, 1, 1)), (4, (4, 3, 2)), (4, (5, 4, 3)), (4, (3, 2, 5))])
+def test_reinit_apply_tile_edges(k, ncells):
+    m = W.Mesh(ncells=ncells, degree=k, bc=(0,) * 6, extent=(1.0, 0.9, 1.2))
+    normal = W.normal_field(m, (0.47, 0.52, 0.5))
+    x = W.uniform_vectors(6, 1, m.ndofs)[0]
+    ref = oracle.reinit_matrix(m, normal, 0.08, 0.05) @ x
+    p = vpp.Problem.from_mesh(m)
+    say("reinit apply", k, ncells)
+    assert rel(host(p.reinit_apply(dev(x), [dev(c) for c in normal], 0.08, 0.05)), ref) < 1e-12
+
+
+def test_reinit_apply_large_k3_tile():
+    """The k = 3 tile of meshes above 50,000 cells: sampled rows."""
+    m = W.Mesh(ncells=(41, 37, 34), degree=3, bc=(0,) * 6)
+    normal = W.normal_field(m, (0.47, 0.52, 0.5))
+    x = W.uniform_vectors(7, 1, m.ndofs)[0]
+    rows = np.random.default_rng(3).choice(m.ndofs, 60, replace=False)
+    ax, _, _ = oracle.reinit_rows(m, normal, 0.05, 0.04, x, x, rows)
+    p = vpp.Problem.from_mesh(m)
+    say("reinit apply 41x37x34 Q3")
+    y = host(p.reinit_apply(dev(x), [dev(c) for c in normal], 0.05, 0.04))
+    assert np.abs(y[rows] - ax).max() < 1e-12 * np.abs(ax).max()
+
+
+@pytest.mark.parametrize("k,ncells", [(2, (28, 27, 26)), (2, (28, 27, 27)), (3, (25, 26, 24)), (3, (26, 25, 25)),
+                                      (4, (20, 20, 20)), (4, (20, 21, 20))])
+def test_default_configuration_rule(k, ncells):
+    """Both sides of the rule's lines: the default gives the tuner's candidates' result."""
+    m = W.Mesh(ncells=ncells, degree=k, bc=(0, 1, 1, 0, 0, 1), rho_l=1000.0, rho_g=1.0)
+    phi = W.droplet_phi(m, 0.3, 0.1)
+    x = dev(W.uniform_vectors(8, 1, m.ndofs)[0])
+    p = vpp.Problem.from_mesh(m)
+    p.set_phi(dev(phi))
+    say("default", k, ncells, p.config_for("fp64"), p.config_for("fp32"))
+    y, y32 = host(p.apply(x)), host(p.apply(x.float()).double())
+    other = [c for c in vpp.config_candidates(k) if c["variant"] == 1 and c != p.config_for("fp64")]
+    other = other or [c for c in vpp.config_candidates(k) if c != p.config_for("fp64")]
+    p.set_config(other[0]["variant"], other[0]["tile"])
+    ref = host(p.apply(x))
+    assert rel(y, ref) < 1e-12 and rel(y32, ref) < 2e-6
