@@ -399,8 +399,7 @@ vpp_status vpp_batch_apply(vpp_batch b, const double* const* x, double* const* y
  * one iteration being one persistent batched apply and two batched vector
  * launches over every such system that has not stopped (systems that have
  * stopped are skipped), recorded in a hipGraph of check_every iterations; each
- * system's reductions are summed in the order of a single solve on the batch's
- * tiles.  Systems of larger meshes fill the GPU on their own and are solved
+ * system's reductions are summed in a fixed order.  Systems of larger meshes fill the GPU on their own and are solved
  * one after another with vpp_cg_solve (and the problem's tuned kernels), after
  * the lockstep group.  VPP_MIXED: every system is solved with vpp_cg_solve, one
  * after another.  Synchronizes.

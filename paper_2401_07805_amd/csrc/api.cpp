@@ -131,6 +131,7 @@ struct CgWork {
     double* rr = nullptr;         // device scalar for residual norms
     double* red = nullptr;        // per-workgroup partial sums of the reductions
     double* hrr = nullptr;        // pinned host mirror
+    unsigned *map64 = nullptr, *map32 = nullptr;   // shared-node maps of the tiles of cfg and cfg32
     hipGraphExec_t g64 = nullptr, g32 = nullptr;
     int graph_iters = 0;
     LaunchCfg graph_cfg{-1, {0, 0, 0}};
@@ -153,6 +154,7 @@ struct ReinitWork {
     double *b = nullptr, *r = nullptr, *p = nullptr, *q = nullptr, *x = nullptr;
     double *diag = nullptr, *invd = nullptr, *red = nullptr, *dot = nullptr, *rr = nullptr, *hrr = nullptr;
     float* inv32 = nullptr;
+    unsigned* map = nullptr;       // shared-node map of the reinitialization operator's tiles
     CgState* st = nullptr;
     CgState* hst = nullptr;
 };
@@ -190,7 +192,7 @@ static void free_reinit(ReinitWork* w)
     if (!w) return;
     dev_free(w->b); dev_free(w->r); dev_free(w->p); dev_free(w->q); dev_free(w->x);
     dev_free(w->diag); dev_free(w->invd); dev_free(w->red); dev_free(w->dot); dev_free(w->rr);
-    dev_free(w->inv32); dev_free(w->st);
+    dev_free(w->inv32); dev_free(w->map); dev_free(w->st);
     if (w->hst) (void)hipHostFree(w->hst);
     if (w->hrr) (void)hipHostFree(w->hrr);
     delete w;
@@ -235,6 +237,8 @@ struct vpp_batch_s {
     double* cg_rr = nullptr;           // device, one residual norm per system
     double* cg_hrr = nullptr;          // pinned mirror
     CgSystem<double>* cg_sys = nullptr;
+    unsigned* cg_map = nullptr;        // shared-node maps of the lockstep problems, one after another
+    int* cg_owner = nullptr;           // system of each workgroup of the batched vector launches
     int cg_blocks = 0;                 // workgroups of the batched vector launches
     hipGraphExec_t cg_graph = nullptr;
     int cg_graph_iters = 0;
@@ -403,6 +407,7 @@ static void free_graphs(CgWork& w)
 static void free_work(CgWork& w)
 {
     free_graphs(w);
+    dev_free(w.map64); dev_free(w.map32);
     dev_free(w.x); dev_free(w.b); dev_free(w.r); dev_free(w.p); dev_free(w.q);
     dev_free(w.x32); dev_free(w.r32); dev_free(w.p32); dev_free(w.q32); dev_free(w.xb);
     dev_free(w.st); dev_free(w.st32); dev_free(w.rr); dev_free(w.red);
@@ -460,9 +465,8 @@ static vpp_status build_cg_graph(vpp_problem p, int iters, hipGraphExec_t* out)
                                 true};
             err = launch_apply_f64(p->cfg, p->k, a, s);
             if (err == hipSuccess)
-                err = launch_cg_assemble_update<double>(w.st, par, w.red, p->dot_part, tile_count(p->m), p->m,
-                                                        shared_enum(p->m, p->k, p->cfg.tile), p->part, stride,
-                                                        w.r, w.q, p->inv64, p->N, s);
+                err = launch_cg_assemble_update<double>(w.st, par, w.red, p->dot_part, tile_count(p->m), w.map64,
+                                                        p->part, stride, w.r, w.q, p->inv64, p->N, s);
             if (err == hipSuccess)
                 err = launch_cg_pupdate<double>(w.st, par, w.red, w.x, w.r, w.p, p->inv64, p->N, s);
         } else {
@@ -472,9 +476,8 @@ static vpp_status build_cg_graph(vpp_problem p, int iters, hipGraphExec_t* out)
                                p->dot_part, nullptr, &w.st32->halt[par], true};
             err = launch_apply_f32(p->cfg32, p->k, a, s);
             if (err == hipSuccess)
-                err = launch_cg_assemble_update<float>(w.st32, par, w.red, p->dot_part, tile_count(p->m32), p->m32,
-                                                       shared_enum(p->m32, p->k, p->cfg32.tile), part, stride,
-                                                       w.r32, w.q32, p->inv32, p->N, s);
+                err = launch_cg_assemble_update<float>(w.st32, par, w.red, p->dot_part, tile_count(p->m32), w.map32,
+                                                       part, stride, w.r32, w.q32, p->inv32, p->N, s);
             if (err == hipSuccess)
                 err = launch_cg_pupdate<float>(w.st32, par, w.red, w.x32, w.r32, w.p32, p->inv32, p->N, s);
         }
@@ -508,8 +511,16 @@ static vpp_status ensure_graphs(vpp_problem p, int iters, bool mixed)
         w.graph_cfg32 = p->cfg32;
     }
     vpp_status s;
-    if (!w.g64 && (s = build_cg_graph<double>(p, iters, &w.g64))) return s;
-    if (mixed && !w.g32 && (s = build_cg_graph<float>(p, iters, &w.g32))) return s;
+    if (!w.g64) {
+        if (!w.map64 && (s = dev_alloc(&w.map64, (size_t)p->N, "cg shared-node map"))) return s;
+        VPP_HIP(launch_shared_map(shared_enum(p->m, p->k, p->cfg.tile), p->m.bcmask, w.map64, p->stream));
+        if ((s = build_cg_graph<double>(p, iters, &w.g64))) return s;
+    }
+    if (mixed && !w.g32) {
+        if (!w.map32 && (s = dev_alloc(&w.map32, (size_t)p->N, "cg shared-node map"))) return s;
+        VPP_HIP(launch_shared_map(shared_enum(p->m32, p->k, p->cfg32.tile), p->m32.bcmask, w.map32, p->stream));
+        if ((s = build_cg_graph<float>(p, iters, &w.g32))) return s;
+    }
     return VPP_OK;
 }
 
@@ -1460,6 +1471,18 @@ static vpp_status ensure_reinit_work(vpp_problem p)
         free_reinit(w);
         return fail(VPP_ERR_OUT_OF_MEMORY, "reinit host mirrors");
     }
+    // shared nodes of the operator's tiles (no Dirichlet faces)
+    MeshArgs m = p->m;
+    const LaunchCfg c = reinit_config(p->k, m);
+    set_tiles(m, c);
+    if ((st = dev_alloc(&w->map, n, "reinit shared-node map"))) {
+        free_reinit(w);
+        return st;
+    }
+    if (launch_shared_map(shared_enum(m, p->k, c.tile), 0, w->map, p->stream) != hipSuccess) {
+        free_reinit(w);
+        return fail(VPP_ERR_HIP, "reinit shared-node map");
+    }
     p->rw = w;
     return VPP_OK;
 }
@@ -1503,7 +1526,6 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
     ReinitWork& w = *p->rw;
     const int64_t n = p->N;
     const ReinitArgs ra = reinit_geometry(p, n0, n1, n2, o);
-    const SharedEnum shared = shared_enum(ra.g.m, p->k, reinit_config(p->k, ra.g.m).tile);
     const int64_t stride = shared_stride(ra.g.m);
     const int ntiles = tile_count(ra.g.m);
     double* cv;
@@ -1552,8 +1574,8 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
                 // tile kernel (with p.q partials); the update assembles the shared nodes
                 const ReinitApplyArgs a{ra, w.p, w.q, cv, stride, dot_part, &w.st->halt[par], true};
                 VPP_HIP(launch_reinit_apply(p->k, a, s));
-                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, dot_part, ntiles, ra.g.m, shared, cv,
-                                                          stride, w.r, w.q, w.invd, n, s));
+                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, dot_part, ntiles, w.map, cv, stride, w.r,
+                                                          w.q, w.invd, n, s));
                 VPP_HIP(launch_cg_pupdate<double>(w.st, par, w.red, w.x, w.r, w.p, w.invd, n, s));
             }
             VPP_HIP(hipMemcpyAsync(hs, w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
@@ -2051,8 +2073,6 @@ extern "C" vpp_status vpp_amr_cg_solve(vpp_amr a, const double* b, double* x, co
     hipStream_t s = a->stream;
     ReinitWork& w = *a->w;
     const int64_t n = a->n;
-    const int one[3] = {1, 1, 1};
-    const SharedEnum none = shared_enum(a->args.mc, a->k, one);   // no shared nodes: q is used as it is
     const int gdot = (int)std::max<int64_t>(1, std::min<int64_t>(kMaxRedBlocks, (n + 1023) / 1024));
     VPP_HIP(launch_amr_apply(a->k, a->args, a->phi, x, w.q, s));
     CgState* hs = w.hst;
@@ -2090,8 +2110,7 @@ extern "C" vpp_status vpp_amr_cg_solve(vpp_amr a, const double* b, double* x, co
                 const int par = done & 1;
                 VPP_HIP(launch_amr_apply(a->k, a->args, a->phi, w.p, w.q, s));
                 VPP_HIP(launch_dot_partials(w.p, w.q, n, w.dot, gdot, s));
-                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, w.dot, gdot, a->args.mc, none, nullptr, 0,
-                                                          w.r, w.q, a->inv64, n, s));
+                VPP_HIP(launch_cg_update<double>(w.st, par, w.red, w.dot, gdot, w.r, w.q, a->inv64, n, s));
                 VPP_HIP(launch_cg_pupdate<double>(w.st, par, w.red, x, w.r, w.p, a->inv64, n, s));
             }
             VPP_HIP(hipMemcpyAsync(hs, w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
@@ -2439,7 +2458,7 @@ static void batch_cg_free(vpp_batch b)
     dev_free(b->cg_probs);
     dev_free(b->cg_x); dev_free(b->cg_r); dev_free(b->cg_p); dev_free(b->cg_q);
     dev_free(b->cg_tx); dev_free(b->cg_tp); dev_free(b->cg_tq);
-    dev_free(b->cg_st); dev_free(b->cg_red); dev_free(b->cg_dot); dev_free(b->cg_rr); dev_free(b->cg_sys);
+    dev_free(b->cg_st); dev_free(b->cg_red); dev_free(b->cg_dot); dev_free(b->cg_rr); dev_free(b->cg_sys); dev_free(b->cg_owner); dev_free(b->cg_map);
     if (b->cg_hst) (void)hipHostFree(b->cg_hst);
     if (b->cg_hrr) (void)hipHostFree(b->cg_hrr);
     b->cg_hst = nullptr;
@@ -2499,6 +2518,31 @@ static vpp_status batch_cg_setup(vpp_batch b)
     }
     std::vector<double*> tx(S), tp(S), tq(S);
     std::vector<CgSystem<double>> sys(S);
+    // Packets per thread of the vector launches: enough that all their workgroups
+    // are resident at once (about five per CU; each spends some 4 us on its
+    // system's table, state and partial sums before its first packet: 7448
+    // workgroups of one packet per thread took 42 us for the update of 16 systems
+    // of 16^3-40^3 Q2 cells)
+    int64_t all = 0;
+    for (const BatchProblem& P : tab) all += (int64_t)P.nrhs * P.m.nn[0] * P.m.nn[1] * P.m.nn[2];
+    const int64_t resident = (int64_t)5 * device_cu_count() * 256 * 2;
+    const int packets = (int)std::max<int64_t>(1, std::min<int64_t>(16, (all + resident - 1) / resident));
+    // shared-node maps, each starting on a 16-byte boundary
+    std::vector<int64_t> map_off;
+    int64_t map_n = 0;
+    for (const BatchProblem& P : tab) {
+        map_off.push_back(map_n);
+        map_n += ((int64_t)P.m.nn[0] * P.m.nn[1] * P.m.nn[2] + 3) & ~int64_t(3);
+    }
+    if ((st = dev_alloc(&b->cg_map, (size_t)map_n, "batch cg shared-node maps"))) {
+        batch_cg_free(b);
+        return st;
+    }
+    for (size_t t = 0; t < tab.size(); ++t)
+        if (launch_shared_map(tab[t].se, tab[t].m.bcmask, b->cg_map + map_off[t], b->stream) != hipSuccess) {
+            batch_cg_free(b);
+            return fail(VPP_ERR_HIP, "batch cg shared-node maps");
+        }
     int blk = 0;
     for (size_t t = 0, sidx = 0; t < tab.size(); ++t)
         for (int j = 0; j < tab[t].nrhs; ++j, ++sidx) {
@@ -2511,8 +2555,7 @@ static vpp_status batch_cg_setup(vpp_batch b)
             CgSystem<double>& y = sys[sidx];
             y.st = b->cg_st + sidx;
             y.red = b->cg_red + sidx * kRedDoubles;
-            y.e = P.se;
-            y.bcmask = P.m.bcmask;
+            y.map = b->cg_map + map_off[t];
             y.part = b->d_part + P.part_begin + (int64_t)j * 8 * P.nshared;
             y.stride = P.nshared;
             y.dot_part = b->cg_dot + P.dot_begin + j * P.ntiles;
@@ -2524,10 +2567,16 @@ static vpp_status batch_cg_setup(vpp_batch b)
             y.invd = prob->inv64;
             y.n = prob->N;
             y.blk_begin = blk;
-            y.nblk = cg_update_blocks(y.n);
+            y.nblk = cg_update_blocks(y.n, packets);
             blk += y.nblk;
         }
     b->cg_blocks = blk;
+    std::vector<int> owner;
+    for (size_t i = 0; i < S; ++i) owner.insert(owner.end(), sys[i].nblk, (int)i);
+    if ((st = upload(&b->cg_owner, owner, "batch cg workgroup table"))) {
+        batch_cg_free(b);
+        return st;
+    }
     if (hipMemcpy(b->cg_probs, tab.data(), tab.size() * sizeof(BatchProblem), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(b->cg_tx, tx.data(), S * sizeof(double*), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(b->cg_tp, tp.data(), S * sizeof(double*), hipMemcpyHostToDevice) != hipSuccess ||
@@ -2555,7 +2604,7 @@ static vpp_status batch_cg_graph(vpp_batch b, int iters)
         ba.any_mass = batch_any_mass(b);
         err = launch_batch_apply(b->cfg, b->k, ba, b->cg_nblocks, b->cg_nsys, true, b->stream);
         if (err == hipSuccess)
-            err = launch_cg_batch_step(b->cg_sys, b->cg_nsys, b->cg_blocks, par, b->d_queue, b->stream);
+            err = launch_cg_batch_step(b->cg_sys, b->cg_owner, b->cg_blocks, par, b->d_queue, b->stream);
     }
     hipError_t e2 = hipStreamEndCapture(b->stream, &g);
     if (err != hipSuccess) {

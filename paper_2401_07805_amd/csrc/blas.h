@@ -37,14 +37,24 @@ constexpr int kRedDoubles = 2 * kMaxRedBlocks;
 template <typename T>
 hipError_t launch_cg_init(CgState* st, double* red, const T* b, const T* q, T* r, T* p, const T* invd, int64_t n,
                           hipStream_t s);
+// Map of the shared nodes for the CG update, one entry per node (n = prod e.nn):
+// built once per tile configuration, so that the update finds a node's partials
+// by one 4-byte load.  (Decoding the position per packet instead, by reciprocal
+// divisions, took 240 vector instructions per 16 bytes: 18.3 us per update at
+// 64^3 Q2 against 16.8.)
+hipError_t launch_shared_map(const SharedEnum& e, int bcmask, unsigned* map, hipStream_t s);
 // CG update after a tiles-only apply q = A p: p.Ap from the ndot per-workgroup
 // partials dot_part; the values of q on shared nodes assembled from the partial
-// array part (stride `stride`, enumeration e); alpha = rz / pAp,
-// r -= alpha q, and per-workgroup partials of r.r and r.(D^-1 r).
+// array part (at least one entry; stride `stride`, positions by map); alpha =
+// rz / pAp, r -= alpha q, and per-workgroup partials of r.r and r.(D^-1 r).
 template <typename T>
 hipError_t launch_cg_assemble_update(CgState* st, int par, double* red, const double* dot_part, int ndot,
-                                     const MeshArgs& m, const SharedEnum& e, const T* part, int64_t stride, T* r,
-                                     const T* q, const T* invd, int64_t n, hipStream_t s);
+                                     const unsigned* map, const T* part, int64_t stride, T* r, const T* q,
+                                     const T* invd, int64_t n, hipStream_t s);
+// The same for a vector of length n without shared nodes (q = A p complete).
+template <typename T>
+hipError_t launch_cg_update(CgState* st, int par, double* red, const double* dot_part, int ndot, T* r, const T* q,
+                            const T* invd, int64_t n, hipStream_t s);
 // Stop decision, x += alpha p (alpha as in the update) and p = D^-1 r + beta p.
 template <typename T>
 hipError_t launch_cg_pupdate(CgState* st, int par, const double* red, T* x, const T* r, T* p, const T* invd,
@@ -55,8 +65,7 @@ template <typename T>
 struct CgSystem {
     CgState* st;
     double* red;              // kRedDoubles partials of this system's reductions
-    SharedEnum e;             // shared-node enumeration of the batched apply's tiles
-    int bcmask;
+    const unsigned* map;      // shared-node map of the batched apply's tiles
     const T* part;            // the batched apply's shared-node partials of this system
     int64_t stride;
     const double* dot_part;   // the batched apply's per-tile partials of p.Ap (ndot)
@@ -68,15 +77,17 @@ struct CgSystem {
     const T* invd;
     int64_t n;
     int blk_begin;            // first workgroup of this system in the batched launches
-    int nblk;                 // its workgroup count, cg_update_blocks(n)
+    int nblk;                 // its workgroup count, cg_update_blocks
 };
 
-// Workgroups of the single-system update and search-direction update.
-int cg_update_blocks(int64_t n);
-// The update and the search-direction update of every system of sys[0..nsys)
-// (device table) as two launches of total_blocks workgroups; the first also
-// resets the batched apply's work counter *queue (if not null).
-hipError_t launch_cg_batch_step(const CgSystem<double>* sys, int nsys, int total_blocks, int par, int* queue,
+// Workgroups of a system of n unknowns in the batched vector launches, at
+// `packets` 16-byte packets per thread.
+int cg_update_blocks(int64_t n, int packets);
+// The update and the search-direction update of every system of the device
+// table sys as two launches of total_blocks workgroups (owner[b]: system of
+// workgroup b); the first also resets the batched apply's work counter *queue
+// (if not null).
+hipError_t launch_cg_batch_step(const CgSystem<double>* sys, const int* owner, int total_blocks, int par, int* queue,
                                 hipStream_t s);
 
 // r = b - q in FP64 (r may be null) and *rr = r.r.

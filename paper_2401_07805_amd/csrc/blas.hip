@@ -23,6 +23,9 @@
 // halt[1-par] (propagating a stop it sees), so no kernel reads a flag that the
 // same kernel writes.  Once a stop is set every later kernel returns at once.
 #include "blas.h"
+
+#include <algorithm>
+
 #include "shared_nodes.h"
 
 namespace vpp {
@@ -97,16 +100,29 @@ static int grid_for(int64_t n)
     return (int)(want < 1 ? 1 : (want > kMaxRedBlocks ? kMaxRedBlocks : want));
 }
 
-// Number of workgroups of the fused update and of the search-direction update
-// (which sums the former's partials): one packet per thread up to the
-// partial-array capacity, since the shared-node lookups make the fused update
-// latency-bound rather than bandwidth-bound.
+// Workgroups of the update: one packet per thread up to three workgroups per
+// CU (48^3 Q2 9.2 us, 64^3 16.8, 80^3 27.6; with four 9.7, 16.9, 29.0).
 template <typename T>
 static int grid_update(int64_t n)
 {
-    const int64_t packets = (n + Pack<T>::W - 1) / Pack<T>::W;
-    const int64_t want = (packets + BT - 1) / BT;
-    return (int)(want < 1 ? 1 : (want > kMaxRedBlocks ? kMaxRedBlocks : want));
+    const int64_t per = (int64_t)BT * Pack<T>::W;
+    return (int)std::min<int64_t>(768, std::max<int64_t>(1, (n + per - 1) / per));
+}
+
+// Workgroups of the search-direction update, whose threads take their packets
+// in batches of kBatch: two per CU while a batch covers the vector (48^3 Q2 8.3
+// us, with four 8.7), then four (64^3 15.9 us, with two 17.2), in whole batches
+// once there are two per thread (64^3 Q3 FP32 25.6 us against 27.3).
+constexpr int kBatch = 4;
+template <typename T>
+static int grid_pupdate(int64_t n)
+{
+    const int64_t per = (int64_t)BT * Pack<T>::W;
+    const int64_t all = std::max<int64_t>(1, (n + per - 1) / per);   // workgroups at one packet per thread
+    if (all <= 512 * kBatch) return (int)std::min<int64_t>(all, 512);
+    if (all <= 1024 * (kBatch + 1)) return 1024;
+    const int64_t its = ((all + 1023) / 1024 + kBatch - 1) / kBatch * kBatch;
+    return (int)((all + its - 1) / its);
 }
 
 // r = b - q (q may be null: zero initial guess), p = D^-1 r; partials of r.r
@@ -147,35 +163,91 @@ __global__ void __launch_bounds__(BT) cg_init_finish_kernel(CgState* st, const d
 // the same fixed order by every workgroup.
 template <typename T>
 struct SharedParts {
-    SharedEnum e;
-    int bcmask;
+    const unsigned* map;   // per node: 0, or where its partials are (shared_map_entry)
     const T* part;
     int64_t stride;
     const double* dot_part;
     int ndot;
 };
 
-template <typename T>
-__device__ __forceinline__ T node_value(const SharedParts<T>& sp, const T* __restrict__ q, int64_t g)
+// Entry of the shared-node map: f << 2 | log2 of the number of partials (1, 2, 3;
+// f < 2^29, since 8 rank arrays are indexed with 32 bits), 0 for a node that
+// one tile holds alone or that is a Dirichlet node.
+__host__ __device__ inline unsigned shared_map_entry(int f, int cnt)
 {
-    int f, cnt;
-    if (!shared_lookup(sp.e, sp.bcmask, (int)g, f, cnt)) return q[g];
-    T v = sp.part[f] + sp.part[sp.stride + f];
-    for (int c = 2; c < cnt; ++c) v += sp.part[c * sp.stride + f];
-    return v;
+    return (unsigned)f << 2 | (cnt == 2 ? 1u : (cnt == 4 ? 2u : 3u));
 }
 
-// Body of the update for workgroup bid of nblk (one system); the workgroup
-// returns at once when the system has stopped.
+__global__ void __launch_bounds__(BT) shared_map_kernel(SharedEnum e, int bcmask, unsigned* __restrict__ map, int64_t n)
+{
+    for (int64_t g = (int64_t)blockIdx.x * BT + threadIdx.x; g < n; g += (int64_t)gridDim.x * BT) {
+        int f, cnt;
+        map[g] = shared_lookup(e, bcmask, (int)g, f, cnt) ? shared_map_entry(f, cnt) : 0u;
+    }
+}
+
+// q on W nodes with map entries mp: on shared ones the sum of the partials, in
+// rank order as the assembly kernel forms it.  Ranks 0 and 1 are loaded for
+// every node (a node that is not shared reads entry 0), so only the nodes of
+// two or three planes branch.
+template <typename T, int W>
+__device__ __forceinline__ void assemble_packet(const SharedParts<T>& sp, const unsigned (&mp)[W], T (&qv)[W])
+{
+    T s[W];
+    unsigned top = 0;
+#pragma unroll
+    for (int t = 0; t < W; ++t) {
+        const unsigned f = mp[t] >> 2;
+        s[t] = sp.part[f] + sp.part[sp.stride + f];
+        top = max(top, mp[t] & 3u);
+    }
+    if (top > 1) {
+#pragma unroll
+        for (int t = 0; t < W; ++t) {
+            if ((mp[t] & 3u) < 2) continue;
+            const T* const p = sp.part + (mp[t] >> 2);
+            const T p2 = p[2 * sp.stride], p3 = p[3 * sp.stride];
+            s[t] = (s[t] + p2) + p3;
+            if ((mp[t] & 3u) == 3) {
+                const T p4 = p[4 * sp.stride], p5 = p[5 * sp.stride], p6 = p[6 * sp.stride], p7 = p[7 * sp.stride];
+                s[t] = (((s[t] + p4) + p5) + p6) + p7;
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < W; ++t)
+        if (mp[t]) qv[t] = s[t];
+}
+
+// alpha = rz / p.Ap, with p.Ap summed from the ndot partials by every workgroup
+// in the same order; false when the system has stopped or breaks down here.
+template <typename T>
+__device__ __forceinline__ bool update_alpha(int bid, CgState* st, int par, const double* dot_part, int ndot, T& alpha)
+{
+    // the state read at once (before the barrier of the reduction, so the loads
+    // overlap it instead of following it)
+    const int halt = st->halt[par];
+    const double rz_par = st->rz[par];
+    if (halt) return false;
+    double pAp = 0.0, unused = 0.0;
+    for (int i = threadIdx.x; i < ndot; i += BT) pAp += dot_part[i];
+    block_sum2<BT>(pAp, unused);
+    if (bid == 0 && threadIdx.x == 0) st->pAp = pAp;
+    if (!(pAp > 0.0) || !isfinite(pAp)) {
+        if (bid == 0 && threadIdx.x == 0) st->breakdown = 1;
+        return false;
+    }
+    alpha = T(rz_par / pAp);
+    return true;
+}
+
+// Body of the update for workgroup bid of one system; the workgroup returns at
+// once when the system has stopped.
 template <typename T>
 __device__ __forceinline__ void assemble_update_body(int bid, int nblk, CgState* st, int par, double* red,
                                                      const SharedParts<T>& sp, T* __restrict__ r,
                                                      const T* __restrict__ q, const T* __restrict__ invd, int64_t n)
 {
-    // every state field this kernel needs, read at once (before the barrier of
-    // the reduction, so the loads overlap it instead of following it)
-    const int halt = st->halt[par];
-    const double rz_par = st->rz[par];
     float* hist = nullptr;
     int hit = 0, hcap = 0;
     int64_t hstride = 0;
@@ -187,71 +259,47 @@ __device__ __forceinline__ void assemble_update_body(int bid, int nblk, CgState*
         hcap = st->hist_cap;
         hstride = st->hist_stride;
     }
-    if (halt) return;
-    double pAp = 0.0, unused = 0.0;
-    for (int i = threadIdx.x; i < sp.ndot; i += BT) pAp += sp.dot_part[i];
-    block_sum2<BT>(pAp, unused);
-    if (bid == 0 && threadIdx.x == 0) st->pAp = pAp;
-    if (!(pAp > 0.0) || !isfinite(pAp)) {
-        if (bid == 0 && threadIdx.x == 0) st->breakdown = 1;
-        return;
-    }
-    const T alpha = T(rz_par / pAp);
-    double rr = 0.0, rz = 0.0;
     using P = Pack<T>;
-    const int64_t np = n / P::W;
+    constexpr int W = P::W;
+    struct alignas(4 * W) Map {
+        unsigned v[W];
+    };
+    const int64_t np = n / W;
+    // a packet's map entries are loaded one packet ahead (the first before the
+    // reduction), so that its partials' addresses do not wait for them
+    const int64_t S = (int64_t)nblk * BT;
+    int64_t c = (int64_t)bid * BT + threadIdx.x;
+    Map mp{};
+    if (c < np) mp = reinterpret_cast<const Map*>(sp.map)[c];
+    T alpha;
+    if (!update_alpha(bid, st, par, sp.dot_part, sp.ndot, alpha)) return;
+    double rr = 0.0, rz = 0.0;
     T* hrec = nullptr;
     if constexpr (sizeof(T) == 4)
         if (hist && hit < hcap) hrec = hist + (size_t)hit * (size_t)hstride;
-    for (int64_t c = (int64_t)bid * BT + threadIdx.x; c < np; c += (int64_t)nblk * BT) {
+    for (; c < np; c += S) {
         P rv = reinterpret_cast<const P*>(r)[c];
         const P dv = reinterpret_cast<const P*>(invd)[c];
         P qv = reinterpret_cast<const P*>(q)[c];
-        // shared nodes of the packet: all partial loads issued before any use;
-        // the row part of the lookup is shared unless the packet wraps a row
-        int f[P::W], cnt[P::W];
-        const int g0 = (int)(c * P::W);
-        const int rw = qdiv(g0, sp.e.nn[0], sp.e.inv_nn[0]);
-        const int i0 = g0 - rw * sp.e.nn[0];
-        if (i0 + P::W <= sp.e.nn[0]) {
-            const int l = qdiv(rw, sp.e.nn[1], sp.e.inv_nn[1]);
-            const SharedRow w = shared_row(sp.e, sp.bcmask, rw - l * sp.e.nn[1], l);
+        const Map now = mp;
+        if (c + S < np) mp = reinterpret_cast<const Map*>(sp.map)[c + S];
+        assemble_packet<T, W>(sp, now.v, qv.v);
 #pragma unroll
-            for (int j = 0; j < P::W; ++j)
-                if (!shared_in_row(sp.e, sp.bcmask, w, i0 + j, f[j], cnt[j])) cnt[j] = 0;
-        } else {
-#pragma unroll
-            for (int j = 0; j < P::W; ++j)
-                if (!shared_lookup(sp.e, sp.bcmask, g0 + j, f[j], cnt[j])) cnt[j] = 0;
-        }
-        // (loaded into pv first, then summed in rank order as a plain loop would)
-        T pv[P::W][8];
-#pragma unroll
-        for (int j = 0; j < P::W; ++j)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) pv[j][k] = k < cnt[j] ? sp.part[k * sp.stride + f[j]] : T(0);
-#pragma unroll
-        for (int j = 0; j < P::W; ++j)
-            if (cnt[j]) {
-                T v = pv[j][0] + pv[j][1];
-#pragma unroll
-                for (int k = 2; k < 8; ++k)
-                    if (k < cnt[j]) v += pv[j][k];
-                qv.v[j] = v;
-            }
-#pragma unroll
-        for (int j = 0; j < P::W; ++j) {
-            const T ri = fma(-alpha, qv.v[j], rv.v[j]);
-            rv.v[j] = ri;
+        for (int t = 0; t < W; ++t) {
+            const T ri = fma(-alpha, qv.v[t], rv.v[t]);
+            rv.v[t] = ri;
             rr += (double)ri * (double)ri;
-            rz += (double)ri * (double)(ri * dv.v[j]);
+            rz += (double)ri * (double)(ri * dv.v[t]);
         }
         reinterpret_cast<P*>(r)[c] = rv;
         if (hrec) reinterpret_cast<P*>(hrec)[c] = rv;
     }
     if (bid == 0)
-        for (int64_t i = np * P::W + threadIdx.x; i < n; i += BT) {
-            const T ri = fma(-alpha, node_value(sp, q, i), r[i]);
+        for (int64_t i = np * W + threadIdx.x; i < n; i += BT) {
+            const unsigned mp[1] = {sp.map[i]};
+            T qi[1] = {q[i]};
+            assemble_packet<T, 1>(sp, mp, qi);
+            const T ri = fma(-alpha, qi[0], r[i]);
             r[i] = ri;
             if (hrec) hrec[i] = ri;
             rr += (double)ri * (double)ri;
@@ -259,6 +307,42 @@ __device__ __forceinline__ void assemble_update_body(int bid, int nblk, CgState*
         }
     block_sum2<BT>(rr, rz);
     write_partials(red, rr, rz, bid);
+}
+
+// The update for a vector without shared nodes (q complete): plain packets.
+template <typename T>
+__global__ void __launch_bounds__(BT) cg_update_kernel(CgState* st, int par, double* red, const double* dot_part, int ndot,
+                                                       T* __restrict__ r, const T* __restrict__ q,
+                                                       const T* __restrict__ invd, int64_t n)
+{
+    T alpha;
+    if (!update_alpha(blockIdx.x, st, par, dot_part, ndot, alpha)) return;
+    using P = Pack<T>;
+    constexpr int W = P::W;
+    double rr = 0.0, rz = 0.0;
+    const int64_t np = n / W;
+    for (int64_t c = (int64_t)blockIdx.x * BT + threadIdx.x; c < np; c += (int64_t)gridDim.x * BT) {
+        P rv = reinterpret_cast<const P*>(r)[c];
+        const P dv = reinterpret_cast<const P*>(invd)[c];
+        const P qv = reinterpret_cast<const P*>(q)[c];
+#pragma unroll
+        for (int t = 0; t < W; ++t) {
+            const T ri = fma(-alpha, qv.v[t], rv.v[t]);
+            rv.v[t] = ri;
+            rr += (double)ri * (double)ri;
+            rz += (double)ri * (double)(ri * dv.v[t]);
+        }
+        reinterpret_cast<P*>(r)[c] = rv;
+    }
+    if (blockIdx.x == 0)
+        for (int64_t i = np * W + threadIdx.x; i < n; i += BT) {
+            const T ri = fma(-alpha, q[i], r[i]);
+            r[i] = ri;
+            rr += (double)ri * (double)ri;
+            rz += (double)ri * (double)(ri * invd[i]);
+        }
+    block_sum2<BT>(rr, rz);
+    write_partials(red, rr, rz);
 }
 
 template <typename T>
@@ -275,7 +359,6 @@ __global__ void __launch_bounds__(BT) cg_assemble_update_kernel(CgState* st, int
 // batch before it uses any of it, and the first batch before the reduction
 // that gives beta: each batch then costs one memory latency instead of one
 // per packet.
-constexpr int kBatch = 4;
 
 // Body of the search-direction update for workgroup bid of nblk (one system;
 // ng partials of the update to sum).
@@ -371,32 +454,23 @@ __global__ void __launch_bounds__(BT) cg_pupdate_kernel(CgState* st, int par, co
 // ---------------------------------------------------------------------------
 // Batched PCG: the update and the search-direction update of every system of a
 // batch in one launch each.  System i owns workgroups [blk_begin, blk_begin +
-// nblk) of the grid, nblk being what the single-system launch would use, so
-// each system's reductions are summed in the same order as in a single solve.
+// nblk) of the grid (cg_update_blocks); owner[] gives the system of each.
 
 template <typename T>
-__device__ __forceinline__ int system_of_block(const CgSystem<T>* sys, int nsys)
-{
-    int s = 0;
-    for (int i = 1; i < nsys; ++i)
-        if (sys[i].blk_begin <= (int)blockIdx.x) s = i;
-    return s;
-}
-
-template <typename T>
-__global__ void __launch_bounds__(BT) cg_batch_update_kernel(const CgSystem<T>* sys, int nsys, int par, int* queue)
+__global__ void __launch_bounds__(BT) cg_batch_update_kernel(const CgSystem<T>* sys, const int* owner, int par,
+                                                             int* queue)
 {
     // the batched apply that precedes this launch pulls work items from queue
     if (queue && blockIdx.x == 0 && threadIdx.x == 0) *queue = 0;
-    const CgSystem<T>& y = sys[system_of_block(sys, nsys)];
-    const SharedParts<T> sp{y.e, y.bcmask, y.part, y.stride, y.dot_part, y.ndot};
+    const CgSystem<T>& y = sys[owner[blockIdx.x]];
+    const SharedParts<T> sp{y.map, y.part, y.stride, y.dot_part, y.ndot};
     assemble_update_body<T>((int)blockIdx.x - y.blk_begin, y.nblk, y.st, par, y.red, sp, y.r, y.q, y.invd, y.n);
 }
 
 template <typename T>
-__global__ void __launch_bounds__(BT) cg_batch_pupdate_kernel(const CgSystem<T>* sys, int nsys, int par)
+__global__ void __launch_bounds__(BT) cg_batch_pupdate_kernel(const CgSystem<T>* sys, const int* owner, int par)
 {
-    const CgSystem<T>& y = sys[system_of_block(sys, nsys)];
+    const CgSystem<T>& y = sys[owner[blockIdx.x]];
     pupdate_body<T>((int)blockIdx.x - y.blk_begin, y.nblk, y.st, par, y.red, y.nblk, y.x, y.r, y.p, y.invd, y.n);
 }
 
@@ -479,35 +553,59 @@ hipError_t launch_cg_init(CgState* st, double* red, const T* b, const T* q, T* r
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_cg_assemble_update(CgState* st, int par, double* red, const double* dot_part, int ndot,
-                                     const MeshArgs& m, const SharedEnum& e, const T* part, int64_t stride, T* r,
-                                     const T* q, const T* invd, int64_t n, hipStream_t s)
+hipError_t launch_shared_map(const SharedEnum& e, int bcmask, unsigned* map, hipStream_t s)
 {
-    SharedParts<T> sp{e, m.bcmask, part, stride, dot_part, ndot};
-    hipLaunchKernelGGL(cg_assemble_update_kernel<T>, dim3(grid_update<T>(n)), dim3(BT), 0, s, st, par, red, sp, r,
-                       q, invd, n);
+    const int64_t n = (int64_t)e.nn[0] * e.nn[1] * e.nn[2];
+    const int g = (int)std::min<int64_t>(8192, (n + BT - 1) / BT);
+    hipLaunchKernelGGL(shared_map_kernel, dim3(g), dim3(BT), 0, s, e, bcmask, map, n);
     return hipGetLastError();
 }
+
+template <typename T>
+hipError_t launch_cg_assemble_update(CgState* st, int par, double* red, const double* dot_part, int ndot,
+                                     const unsigned* map, const T* part, int64_t stride, T* r, const T* q,
+                                     const T* invd, int64_t n, hipStream_t s)
+{
+    const SharedParts<T> sp{map, part, stride, dot_part, ndot};
+    hipLaunchKernelGGL(cg_assemble_update_kernel<T>, dim3(grid_update<T>(n)), dim3(BT), 0, s, st, par, red, sp, r, q,
+                       invd, n);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_cg_update(CgState* st, int par, double* red, const double* dot_part, int ndot, T* r, const T* q,
+                            const T* invd, int64_t n, hipStream_t s)
+{
+    hipLaunchKernelGGL(cg_update_kernel<T>, dim3(grid_update<T>(n)), dim3(BT), 0, s, st, par, red, dot_part, ndot, r, q,
+                       invd, n);
+    return hipGetLastError();
+}
+template hipError_t launch_cg_update<double>(CgState*, int, double*, const double*, int, double*, const double*,
+                                             const double*, int64_t, hipStream_t);
 
 template <typename T>
 hipError_t launch_cg_pupdate(CgState* st, int par, const double* red, T* x, const T* r, T* p, const T* invd,
                              int64_t n, hipStream_t s)
 {
-    const int g = grid_update<T>(n);   // also the number of partials the update wrote
-    hipLaunchKernelGGL(cg_pupdate_kernel<T>, dim3(g), dim3(BT), 0, s, st, par, red, g, x, r, p, invd, n);
+    const int ng = grid_update<T>(n);   // the partials the update wrote
+    hipLaunchKernelGGL(cg_pupdate_kernel<T>, dim3(grid_pupdate<T>(n)), dim3(BT), 0, s, st, par, red, ng, x, r, p, invd,
+                       n);
     return hipGetLastError();
 }
 
-int cg_update_blocks(int64_t n) { return grid_update<double>(n); }
+int cg_update_blocks(int64_t n, int packets)
+{
+    const int64_t per = (int64_t)packets * BT * Pack<double>::W;
+    return (int)std::min<int64_t>(kMaxRedBlocks, std::max<int64_t>(1, (n + per - 1) / per));
+}
 
-hipError_t launch_cg_batch_step(const CgSystem<double>* sys, int nsys, int total_blocks, int par, int* queue,
+hipError_t launch_cg_batch_step(const CgSystem<double>* sys, const int* owner, int total_blocks, int par, int* queue,
                                 hipStream_t s)
 {
-    hipLaunchKernelGGL(cg_batch_update_kernel<double>, dim3(total_blocks), dim3(BT), 0, s, sys, nsys, par, queue);
+    hipLaunchKernelGGL(cg_batch_update_kernel<double>, dim3(total_blocks), dim3(BT), 0, s, sys, owner, par, queue);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cg_batch_pupdate_kernel<double>, dim3(total_blocks), dim3(BT), 0, s, sys, nsys, par);
+    hipLaunchKernelGGL(cg_batch_pupdate_kernel<double>, dim3(total_blocks), dim3(BT), 0, s, sys, owner, par);
     return hipGetLastError();
 }
 
@@ -516,9 +614,8 @@ hipError_t launch_cg_batch_step(const CgSystem<double>* sys, int nsys, int total
                                           hipStream_t);                                                      \
     template hipError_t launch_cg_pupdate<T>(CgState*, int, const double*, T*, const T*, T*, const T*, int64_t, \
                                              hipStream_t);                                                       \
-    template hipError_t launch_cg_assemble_update<T>(CgState*, int, double*, const double*, int, const MeshArgs&, \
-                                                     const SharedEnum&, const T*, int64_t, T*, const T*,          \
-                                                     const T*, int64_t, hipStream_t);
+    template hipError_t launch_cg_assemble_update<T>(CgState*, int, double*, const double*, int, const unsigned*, \
+                                                     const T*, int64_t, T*, const T*, const T*, int64_t, hipStream_t);
 VPP_INST(double)
 VPP_INST(float)
 #undef VPP_INST
