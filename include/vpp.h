@@ -334,11 +334,12 @@ vpp_status vpp_extend(vpp_problem p, const double* y, const int32_t* info, const
  * matrices of the active cells with the coefficient of Eq. rhoEff from the
  * nodal phi of the cell's own lattice), with identity rows and columns on
  * every entry that is not a free unknown and on free unknowns of Dirichlet
- * faces (as A_D).  The apply and the diagonal run one cell per thread into a
- * cell-major scratch, then sum every entry over the cell results reaching it
- * (lists built on the host, constraint weights included) in a fixed order: no
- * atomics, repeated calls give the same bits; FP64 only.  Calls on one mesh
- * share that scratch and must not overlap.
+ * faces (as A_D).  The apply and the diagonal store every cell's results in a
+ * scratch, then sum every entry over the cell results reaching it (lists built
+ * on the host, constraint weights included) in a fixed order: no atomics,
+ * repeated calls give the same bits; FP64 only.  The solver iterates on the
+ * free unknowns and, for all identity rows together, one more.  Calls on one
+ * mesh share that scratch and must not overlap.
  *   vpp_amr_create:   host call; VPP_ERR_INVALID_ARG as vpp_create, or for a
  *                     NULL mask, more than 2^27 coarse cells or 2^31 entries.
  *   vpp_amr_set_phi:  nodal phi on both lattices (vpp_amr_num_dofs entries);

@@ -152,7 +152,7 @@ struct CgWork {
 // Workspace of the reinitialization step (allocated on first use).
 struct ReinitWork {
     double *b = nullptr, *r = nullptr, *p = nullptr, *q = nullptr, *x = nullptr;
-    double *diag = nullptr, *invd = nullptr, *red = nullptr, *dot = nullptr, *rr = nullptr, *hrr = nullptr;
+    double *diag = nullptr, *invd = nullptr, *red = nullptr, *rr = nullptr, *hrr = nullptr;
     float* inv32 = nullptr;
     unsigned* map = nullptr;       // shared-node map of the reinitialization operator's tiles
     CgState* st = nullptr;
@@ -191,7 +191,7 @@ static void free_reinit(ReinitWork* w)
 {
     if (!w) return;
     dev_free(w->b); dev_free(w->r); dev_free(w->p); dev_free(w->q); dev_free(w->x);
-    dev_free(w->diag); dev_free(w->invd); dev_free(w->red); dev_free(w->dot); dev_free(w->rr);
+    dev_free(w->diag); dev_free(w->invd); dev_free(w->red); dev_free(w->rr);
     dev_free(w->inv32); dev_free(w->map); dev_free(w->st);
     if (w->hst) (void)hipHostFree(w->hst);
     if (w->hrr) (void)hipHostFree(w->hrr);
@@ -1683,16 +1683,34 @@ struct vpp_amr_s {
     AmrArgs args{};
     int *d_cells = nullptr, *d_fkind = nullptr, *d_cptr = nullptr, *d_ccol = nullptr;
     double* d_cw = nullptr;
-    int *d_nptr = nullptr, *d_nidx = nullptr;   // per entry: the cell results that reach it
-    double *d_nw = nullptr, *d_scratch = nullptr;
+    // packed vector and the lists of the apply (AmrArgs)
+    int *d_fent = nullptr, *d_pidx = nullptr, *d_cpk = nullptr, *d_cidx = nullptr, *d_fptr = nullptr, *d_sptr = nullptr;
+    int *d_src = nullptr, *d_tptr = nullptr, *d_tcon = nullptr;
+    unsigned char* d_issrc = nullptr;
+    unsigned *d_fidx = nullptr, *d_sidx = nullptr;
+    double *d_tw = nullptr, *d_ext = nullptr, *d_invd = nullptr, *d_coef = nullptr, *d_csum = nullptr;
+    double* d_scratch = nullptr;
     int *d_soff = nullptr, *d_dptr = nullptr, *d_didx = nullptr;   // the same for the diagonal
     unsigned char* d_ident = nullptr;
     double *phi = nullptr, *diag = nullptr, *inv64 = nullptr;
     float* inv32 = nullptr;
     bool phi_set = false;
     hipStream_t stream = nullptr;
-    ReinitWork* w = nullptr;   // CG vectors (allocated by the first solve)
+    AmrCg cg{};                // CG workspace (allocated by the first solve)
+    CgState* hst = nullptr;    // pinned host mirrors
+    double* hrr = nullptr;
+    double *full = nullptr, *rr = nullptr;   // A x and its residual norm at the end of a solve
 };
+
+static void amr_free_cg(vpp_amr a)
+{
+    dev_free(a->cg.st); dev_free(a->cg.red); dev_free(a->cg.dot); dev_free(a->cg.idpart); dev_free(a->cg.rho);
+    dev_free(a->cg.x); dev_free(a->cg.r); dev_free(a->full); dev_free(a->rr);
+    if (a->hst) (void)hipHostFree(a->hst);
+    if (a->hrr) (void)hipHostFree(a->hrr);
+    a->hst = nullptr;
+    a->hrr = nullptr;
+}
 
 static double gll_point(int k, int i)
 {
@@ -1715,9 +1733,12 @@ static void amr_free(vpp_amr a)
     if (!a) return;
     dev_free(a->d_cells); dev_free(a->d_fkind); dev_free(a->d_cptr); dev_free(a->d_ccol); dev_free(a->d_cw);
     dev_free(a->d_ident); dev_free(a->phi); dev_free(a->diag); dev_free(a->inv64); dev_free(a->inv32);
-    dev_free(a->d_nptr); dev_free(a->d_nidx); dev_free(a->d_nw); dev_free(a->d_scratch);
+    dev_free(a->d_fent); dev_free(a->d_pidx); dev_free(a->d_cpk); dev_free(a->d_cidx); dev_free(a->d_fptr);
+    dev_free(a->d_src); dev_free(a->d_issrc); dev_free(a->d_sptr); dev_free(a->d_tptr); dev_free(a->d_tcon); dev_free(a->d_fidx); dev_free(a->d_sidx);
+    dev_free(a->d_tw); dev_free(a->d_ext); dev_free(a->d_invd); dev_free(a->d_coef); dev_free(a->d_csum);
+    dev_free(a->d_scratch);
     dev_free(a->d_soff); dev_free(a->d_dptr); dev_free(a->d_didx);
-    free_reinit(a->w);
+    amr_free_cg(a);
     if (a->stream) (void)hipStreamDestroy(a->stream);
     delete a;
 }
@@ -1836,54 +1857,95 @@ extern "C" vpp_status vpp_amr_create(const vpp_desc* d, const uint8_t* refined, 
             ident[Nc + gf] = 0;
             ++nfree;
         }
-    // the cell results reaching each entry (apply's second launch): cell e's
-    // local node q is scratch slot q * ncells + e; a free node takes it with
-    // weight 1, a constrained one passes it to its sources with their weights.
-    // Slots are visited in increasing order, so each entry's list is sorted.
+    // the packed vector: free unknowns in entry order, the identity unknown, the
+    // constrained nodes, a zero
+    std::vector<int> fent, pidx((size_t)(Nc + Nf), -1);
+    fent.reserve((size_t)nfree);
+    for (int64_t g = 0; g < Nc + Nf; ++g)
+        if (!ident[g]) {
+            pidx[g] = (int)fent.size();
+            fent.push_back((int)g);
+        }
+    const int ncon = (int)cptr.size() - 1;
+    if (nfree + ncon + 2 > (int64_t)INT32_MAX) return fail(VPP_ERR_INVALID_ARG, "mesh too large (at most 2^31-1 entries)");
+    const int zero = (int)nfree + 1 + ncon;
+    std::vector<int> cpk(ccol.size());
+    for (size_t i = 0; i < ccol.size(); ++i) cpk[i] = pidx[ccol[i]];
+    // cells kernel: packed index of every local node of every thread's x-plane,
+    // and per free unknown and constrained node the slots that hold its results
+    // (slot = that thread's position of the node, in increasing cell order)
     const int64_t ncell_act = (int64_t)cells.size();
     const int n3 = (k + 1) * (k + 1) * (k + 1);
     if (ncell_act * n3 > (int64_t)INT32_MAX) return fail(VPP_ERR_INVALID_ARG, "too many active cells");
-    std::vector<int> nptr((size_t)(Nc + Nf) + 1, 0), nidx;
-    std::vector<double> nwv;
-    {
-        // local node q of every cell, as (target entry, weight) terms
-        std::vector<int64_t> tgt;
-        std::vector<double> tw;
-        std::vector<int> tslot;
-        for (int q = 0; q < n3; ++q) {
-            const int a0 = q % (k + 1), a1 = (q / (k + 1)) % (k + 1), a2 = q / ((k + 1) * (k + 1));
-            for (int64_t e = 0; e < ncell_act; ++e) {
-                const int code = cells[e];
-                const bool fine = code < 0;
-                const int idx = fine ? -(code + 1) : code;
-                const int64_t* nn = fine ? fn : cn;
-                const int ncx = fine ? 2 * nc[0] : nc[0], ncy = fine ? 2 * nc[1] : nc[1];
-                const int64_t cx = idx % ncx, cy = (idx / ncx) % ncy, cz = idx / ((int64_t)ncx * ncy);
-                const int64_t gl = (k * cx + a0) + nn[0] * ((k * cy + a1) + nn[1] * (k * cz + a2));
-                const int slot = (int)(q * ncell_act + e);
-                if (!fine) {
-                    tgt.push_back(gl); tw.push_back(1.0); tslot.push_back(slot);
-                } else if (fkind[gl] < 0) {
-                    tgt.push_back(Nc + gl); tw.push_back(1.0); tslot.push_back(slot);
-                } else {
-                    for (int p = cptr[fkind[gl]]; p < cptr[fkind[gl] + 1]; ++p) {
-                        tgt.push_back(ccol[p]); tw.push_back(cwv[p]); tslot.push_back(slot);
+    const int N = k + 1, cb = amr_cells_per_block(k), cw_ = cb / 4;   // cells per workgroup and per wave
+    const int64_t nblk = (ncell_act + cb - 1) / cb, nslots = nblk * N * N * 256;
+    std::vector<int> cidx((size_t)nslots, zero), fptr((size_t)nfree + 1, 0), sptr((size_t)ncon + 1, 0);
+    std::vector<unsigned> fidx, sidx;
+    // visits (slot, packed index) of every local node, cell by cell
+    auto each_node = [&](auto&& f) {
+        for (int64_t e = 0; e < ncell_act; ++e) {
+            const bool fine = cells[e] < 0;
+            const int idx = fine ? -(cells[e] + 1) : cells[e];
+            const int64_t* nn = fine ? fn : cn;
+            const int ncx = fine ? 2 * nc[0] : nc[0], ncy = fine ? 2 * nc[1] : nc[1];
+            const int64_t cx = idx % ncx, cy = (idx / ncx) % ncy, cz = idx / ((int64_t)ncx * ncy);
+            const int64_t blk = e / cb, c = e % cb, tid0 = c / cw_ * 64 + c % cw_ * N;
+            for (int a2 = 0; a2 < N; ++a2)
+                for (int a1 = 0; a1 < N; ++a1)
+                    for (int a0 = 0; a0 < N; ++a0) {
+                        const int64_t gl = (k * cx + a0) + nn[0] * ((k * cy + a1) + nn[1] * (k * cz + a2));
+                        const int pk = !fine ? pidx[gl] : (fkind[gl] < 0 ? pidx[Nc + gl] : (int)nfree + 1 + fkind[gl]);
+                        f((blk * N * N + a1 + N * a2) * 256 + tid0 + a0, pk);
                     }
-                }
-            }
         }
-        if ((int64_t)tgt.size() > (int64_t)INT32_MAX) return fail(VPP_ERR_INVALID_ARG, "too many cell results");
-        for (int64_t g : tgt) ++nptr[g + 1];
-        for (size_t g = 0; g + 1 < nptr.size(); ++g) nptr[g + 1] += nptr[g];
-        nidx.resize(tgt.size());
-        nwv.resize(tgt.size());
-        std::vector<int> pos(nptr.begin(), nptr.end() - 1);
-        for (size_t t = 0; t < tgt.size(); ++t) {
-            const int j = pos[tgt[t]]++;
-            nidx[j] = tslot[t];
-            nwv[j] = tw[t];
-        }
+    };
+    each_node([&](int64_t slot, int pk) {
+        if (pk < 0) return;
+        cidx[slot] = pk;
+        if (pk < nfree) ++fptr[pk + 1];
+        else ++sptr[pk - nfree];
+    });
+    for (size_t i = 0; i + 1 < fptr.size(); ++i) fptr[i + 1] += fptr[i];
+    for (size_t i = 0; i + 1 < sptr.size(); ++i) sptr[i + 1] += sptr[i];
+    fidx.resize(fptr.back());
+    sidx.resize(sptr.back());
+    {
+        std::vector<int> fpos(fptr.begin(), fptr.end() - 1), spos(sptr.begin(), sptr.end() - 1);
+        each_node([&](int64_t slot, int pk) {
+            if (pk < 0) return;
+            if (pk < nfree) fidx[fpos[pk]++] = (unsigned)slot;
+            else sidx[spos[pk - (int)nfree - 1]++] = (unsigned)slot;
+        });
     }
+    // spare threads of a wave repeat its last thread
+    for (int64_t blk = 0; blk < nblk; ++blk)
+        for (int q = 0; q < N * N; ++q)
+            for (int w = 0; w < 4; ++w)
+                for (int t = cw_ * N; t < 64; ++t) {
+                    const size_t at = (size_t)((blk * N * N + q) * 256 + w * 64);
+                    cidx[at + t] = cidx[at + cw_ * N - 1];
+                }
+    // the free unknowns that constrained nodes draw on, and those nodes
+    std::vector<int> src, tptr(1, 0), tcon, order((size_t)nfree, 0);
+    std::vector<uint8_t> issrc((size_t)nfree, 0);
+    std::vector<double> tw;
+    for (int v : cpk)
+        if (v >= 0) ++order[v];
+    for (int i = 0; i < nfree; ++i)
+        if (order[i]) {
+            tptr.push_back(tptr.back() + order[i]);
+            order[i] = tptr[src.size()];   // next free place of its list
+            src.push_back(i);
+            issrc[i] = 1;
+        }
+    tcon.resize(tptr.back());
+    tw.resize(tptr.back());
+    for (int m = 0; m < ncon; ++m)
+        for (int i = cptr[m]; i < cptr[m + 1]; ++i)
+            if (cpk[i] >= 0) {
+                tcon[order[cpk[i]]] = m;
+                tw[order[cpk[i]]++] = cwv[i];
+            }
     // the diagonal's cell slots: free nodes as above (constrained ones have
     // none), then for every fine cell the coarse nodes its constrained nodes
     // reach, numbered in the order the diagonal kernel meets them (node q,
@@ -1956,15 +2018,27 @@ extern "C" vpp_status vpp_amr_create(const vpp_desc* d, const uint8_t* refined, 
         (st = upload(&a->d_cw, cwv, "amr weights")) || (st = upload(&a->d_ident, ident, "amr identity rows")) ||
         (st = dev_alloc(&a->phi, a->n, "amr phi")) || (st = dev_alloc(&a->diag, a->n, "amr diag")) ||
         (st = dev_alloc(&a->inv64, a->n, "amr inverse diag")) || (st = dev_alloc(&a->inv32, a->n, "amr inverse diag")) ||
-        (st = upload(&a->d_nptr, nptr, "amr entry lists")) || (st = upload(&a->d_nidx, nidx, "amr entry slots")) ||
-        (st = upload(&a->d_nw, nwv, "amr entry weights")) || (st = upload(&a->d_soff, soff, "amr source slots")) ||
-        (st = upload(&a->d_dptr, dptr, "amr diagonal lists")) || (st = upload(&a->d_didx, didx, "amr diagonal slots")) ||
-        (st = dev_alloc(&a->d_scratch, (size_t)std::max<int64_t>(ncell_act * n3 + soff[ncell_act], 1),
+        (st = upload(&a->d_fent, fent, "amr unknowns")) || (st = upload(&a->d_pidx, pidx, "amr packed indices")) ||
+        (st = upload(&a->d_cpk, cpk, "amr constraints")) || (st = upload(&a->d_cidx, cidx, "amr cell indices")) ||
+        (st = upload(&a->d_fptr, fptr, "amr unknown lists")) || (st = upload(&a->d_fidx, fidx, "amr unknown slots")) ||
+        (st = upload(&a->d_sptr, sptr, "amr constrained lists")) || (st = upload(&a->d_sidx, sidx, "amr constrained slots")) ||
+        (st = upload(&a->d_src, src, "amr sources")) || (st = upload(&a->d_issrc, issrc, "amr source flags")) ||
+        (st = upload(&a->d_tptr, tptr, "amr source lists")) || (st = upload(&a->d_tcon, tcon, "amr sources")) ||
+        (st = upload(&a->d_tw, tw, "amr source weights")) ||
+        (st = dev_alloc(&a->d_ext, (size_t)zero + 1, "amr packed vector")) ||
+        (st = dev_alloc(&a->d_invd, (size_t)nfree + 1, "amr packed inverse diag")) ||
+        (st = dev_alloc(&a->d_coef, (size_t)nslots, "amr coefficient")) ||
+        (st = dev_alloc(&a->d_csum, (size_t)ncon, "amr constrained sums")) ||
+        (st = upload(&a->d_soff, soff, "amr source slots")) || (st = upload(&a->d_dptr, dptr, "amr diagonal lists")) ||
+        (st = upload(&a->d_didx, didx, "amr diagonal slots")) ||
+        (st = dev_alloc(&a->d_scratch, (size_t)std::max<int64_t>(nslots, ncell_act * n3 + soff[ncell_act]),
                         "amr cell results"))) {
         amr_free(a);
         return st;
     }
-    if (hipStreamCreateWithFlags(&a->stream, hipStreamNonBlocking) != hipSuccess) {
+    if (hipStreamCreateWithFlags(&a->stream, hipStreamNonBlocking) != hipSuccess ||
+        hipMemset(a->d_ext, 0, ((size_t)zero + 1) * sizeof(double)) != hipSuccess ||   // the zero entry
+        hipDeviceSynchronize() != hipSuccess) {
         amr_free(a);
         return fail(VPP_ERR_HIP, "hipStreamCreate failed");
     }
@@ -1984,9 +2058,26 @@ extern "C" vpp_status vpp_amr_create(const vpp_desc* d, const uint8_t* refined, 
     g.cw = a->d_cw;
     g.ident = a->d_ident;
     g.scratch = a->d_scratch;
-    g.nptr = a->d_nptr;
-    g.nidx = a->d_nidx;
-    g.nw = a->d_nw;
+    g.nfree = (int)nfree;
+    g.ncon = ncon;
+    g.fent = a->d_fent;
+    g.pidx = a->d_pidx;
+    g.cpk = a->d_cpk;
+    g.ext = a->d_ext;
+    g.invd = a->d_invd;
+    g.cidx = a->d_cidx;
+    g.coef = a->d_coef;
+    g.fptr = a->d_fptr;
+    g.fidx = a->d_fidx;
+    g.sptr = a->d_sptr;
+    g.sidx = a->d_sidx;
+    g.nsrc = (int)src.size();
+    g.src = a->d_src;
+    g.issrc = a->d_issrc;
+    g.tptr = a->d_tptr;
+    g.tcon = a->d_tcon;
+    g.tw = a->d_tw;
+    g.csum = a->d_csum;
     g.soff = a->d_soff;
     g.dptr = a->d_dptr;
     g.didx = a->d_didx;
@@ -2014,6 +2105,7 @@ extern "C" vpp_status vpp_amr_set_phi(vpp_amr a, const double* phi, void* stream
     DeviceGuard dg(a->desc.device);
     hipStream_t s = (hipStream_t)stream;
     VPP_HIP(hipMemcpyAsync(a->phi, phi, a->n * sizeof(double), hipMemcpyDeviceToDevice, s));
+    VPP_HIP(launch_amr_coef(a->k, a->args, a->phi, s));
     VPP_HIP(launch_amr_diag(a->k, a->args, a->phi, a->diag, a->inv64, a->inv32, s));
     a->phi_set = true;
     return VPP_OK;
@@ -2026,7 +2118,7 @@ extern "C" vpp_status vpp_amr_apply(vpp_amr a, const double* x, double* y, void*
     if ((const void*)x == y) return fail(VPP_ERR_INVALID_ARG, "x and y must not alias");
     if (!a->phi_set) return fail(VPP_ERR_STATE, "vpp_amr_set_phi has not been called");
     DeviceGuard dg(a->desc.device);
-    VPP_HIP(launch_amr_apply(a->k, a->args, a->phi, x, y, (hipStream_t)stream));
+    VPP_HIP(launch_amr_apply(a->k, a->args, x, y, (hipStream_t)stream));
     return VPP_OK;
 }
 
@@ -2050,35 +2142,33 @@ extern "C" vpp_status vpp_amr_cg_solve(vpp_amr a, const double* b, double* x, co
     if (o->precision != VPP_FP64) return fail(VPP_ERR_UNSUPPORTED, "the refined-mesh solver runs in FP64");
     if (!a->phi_set) return fail(VPP_ERR_STATE, "vpp_amr_set_phi has not been called");
     DeviceGuard dg(a->desc.device);
-    if (!a->w) {
-        ReinitWork* w = new ReinitWork();
-        const size_t n = (size_t)a->n;
-        vpp_status st;
-        if ((st = dev_alloc(&w->b, n, "amr cg b")) || (st = dev_alloc(&w->r, n, "amr cg r")) ||
-            (st = dev_alloc(&w->p, n, "amr cg p")) || (st = dev_alloc(&w->q, n, "amr cg q")) ||
-            (st = dev_alloc(&w->red, kRedDoubles, "amr cg partials")) ||
-            (st = dev_alloc(&w->dot, kMaxRedBlocks, "amr cg dot partials")) || (st = dev_alloc(&w->rr, 1, "norm")) ||
-            (st = dev_alloc(&w->st, 1, "amr cg state"))) {
-            free_reinit(w);
+    vpp_status st;
+    AmrCg& w = a->cg;
+    if (!a->full) {
+        const size_t np = (size_t)a->nfree + 1;
+        w.nred = std::max(amr_red_blocks(a->args), kMaxRedBlocks);   // at least what launch_residual needs
+        if ((st = dev_alloc(&w.r, np, "amr cg r")) || (st = dev_alloc(&w.x, np, "amr cg x")) ||
+            (st = dev_alloc(&w.red, 2 * (size_t)w.nred, "amr cg partials")) ||
+            (st = dev_alloc(&w.dot, (size_t)amr_dot_partials(a->k, a->args), "amr cg dot partials")) ||
+            (st = dev_alloc(&w.idpart, (size_t)w.nred, "amr cg partials")) || (st = dev_alloc(&w.rho, 1, "norm")) ||
+            (st = dev_alloc(&a->rr, 1, "norm")) || (st = dev_alloc(&w.st, 1, "amr cg state")) ||
+            (st = dev_alloc(&a->full, (size_t)a->n, "amr cg product"))) {
+            amr_free_cg(a);
             return st;
         }
-        if (hipHostMalloc((void**)&w->hst, sizeof(CgState), hipHostMallocDefault) != hipSuccess ||
-            hipHostMalloc((void**)&w->hrr, sizeof(double), hipHostMallocDefault) != hipSuccess) {
-            free_reinit(w);
+        if (hipHostMalloc((void**)&a->hst, sizeof(CgState), hipHostMallocDefault) != hipSuccess ||
+            hipHostMalloc((void**)&a->hrr, sizeof(double), hipHostMallocDefault) != hipSuccess) {
+            amr_free_cg(a);
             return fail(VPP_ERR_OUT_OF_MEMORY, "amr cg host mirrors");
         }
-        a->w = w;
     }
     VPP_HIP(hipStreamSynchronize((hipStream_t)stream));
     hipStream_t s = a->stream;
-    ReinitWork& w = *a->w;
     const int64_t n = a->n;
-    const int gdot = (int)std::max<int64_t>(1, std::min<int64_t>(kMaxRedBlocks, (n + 1023) / 1024));
-    VPP_HIP(launch_amr_apply(a->k, a->args, a->phi, x, w.q, s));
-    CgState* hs = w.hst;
+    CgState* hs = a->hst;
     std::memset(hs, 0, sizeof(CgState));
     VPP_HIP(hipMemcpyAsync(w.st, hs, sizeof(CgState), hipMemcpyHostToDevice, s));
-    VPP_HIP(launch_cg_init<double>(w.st, w.red, b, w.q, w.r, w.p, a->inv64, n, s));
+    VPP_HIP(launch_amr_cg_init(a->k, a->args, w, b, x, s));
     VPP_HIP(hipMemcpyAsync(hs, w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
     VPP_HIP(hipStreamSynchronize(s));
     vpp_cg_info inf{};
@@ -2107,11 +2197,7 @@ extern "C" vpp_status vpp_amr_cg_solve(vpp_amr a, const double* b, double* x, co
         const int chunk = o->check_every > 0 ? o->check_every : 32;
         for (int done = 0; done < o->max_iter + chunk;) {
             for (int it = 0; it < chunk; ++it, ++done) {
-                const int par = done & 1;
-                VPP_HIP(launch_amr_apply(a->k, a->args, a->phi, w.p, w.q, s));
-                VPP_HIP(launch_dot_partials(w.p, w.q, n, w.dot, gdot, s));
-                VPP_HIP(launch_cg_update<double>(w.st, par, w.red, w.dot, gdot, w.r, w.q, a->inv64, n, s));
-                VPP_HIP(launch_cg_pupdate<double>(w.st, par, w.red, x, w.r, w.p, a->inv64, n, s));
+                VPP_HIP(launch_amr_cg_step(a->k, a->args, w, done & 1, s));
             }
             VPP_HIP(hipMemcpyAsync(hs, w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
             VPP_HIP(hipStreamSynchronize(s));
@@ -2123,11 +2209,12 @@ extern "C" vpp_status vpp_amr_cg_solve(vpp_amr a, const double* b, double* x, co
         else if (hs->rr_last < init.tol2) inf.status = VPP_OK;
         else inf.status = VPP_ERR_NOT_CONVERGED;
     }
-    VPP_HIP(launch_amr_apply(a->k, a->args, a->phi, x, w.q, s));
-    VPP_HIP(launch_residual(b, w.q, nullptr, n, w.red, w.rr, s));
-    VPP_HIP(hipMemcpyAsync(w.hrr, w.rr, sizeof(double), hipMemcpyDeviceToHost, s));
+    VPP_HIP(launch_amr_unpack(a->args, w, b, x, s));
+    VPP_HIP(launch_amr_apply(a->k, a->args, x, a->full, s));
+    VPP_HIP(launch_residual(b, a->full, nullptr, n, w.red, a->rr, s));
+    VPP_HIP(hipMemcpyAsync(a->hrr, a->rr, sizeof(double), hipMemcpyDeviceToHost, s));
     VPP_HIP(hipStreamSynchronize(s));
-    inf.true_rel_residual = r0 > 0 ? std::sqrt(*w.hrr) / r0 : 0.0;
+    inf.true_rel_residual = r0 > 0 ? std::sqrt(*a->hrr) / r0 : 0.0;
     if (info) *info = inf;
     if (inf.status == VPP_ERR_NOT_CONVERGED) return fail(VPP_ERR_NOT_CONVERGED, "CG did not converge");
     if (inf.status == VPP_ERR_BREAKDOWN) return fail(VPP_ERR_BREAKDOWN, "CG breakdown (p.Ap <= 0 or non-finite)");

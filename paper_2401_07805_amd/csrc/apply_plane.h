@@ -27,10 +27,10 @@ namespace vpp {
 // past the group's last cell are zeros (a neighbour below the tile), which
 // lets the write-out use the same buffer as its slot array.
 
-template <int K, int TX, int TY, int TZ>
+template <int K, int TX, int TY, int TZ, bool W = (K >= 3)>
 struct PlaneGeo {
     static constexpr int N = K + 1, NC = TX * TY * TZ;
-    static constexpr bool WAVE = K >= 3;                 // groups are waves
+    static constexpr bool WAVE = W;                      // groups are waves
     static constexpr int CG = WAVE ? 64 / N : NC;        // cells per group
     static constexpr int NG = (NC + CG - 1) / CG;
     static constexpr int NTH = WAVE ? 64 * NG : N * NC;  // threads per workgroup
@@ -298,10 +298,13 @@ __device__ __forceinline__ double flush_plane(const MeshArgs& m, const PlaneThre
     return dsum;
 }
 
-template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS = false>
-__global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) apply_plane_kernel(ApplyArgs<T> a)
+// The cell operator on a cell's planes: u (this thread's x-plane of nodal
+// values, Dirichlet entries zeroed) is replaced by its x-plane of A_e u; cw: the
+// coefficient factors on its z-plane, wz: its z Gauss weight (mass shift only).
+template <typename G, int K, typename T, bool MASS>
+__device__ __forceinline__ void plane_operator(const MeshArgs& m, T* px, T* pz, const T (&cw)[G::N * G::N], T wz,
+                                               T (&u)[G::N * G::N])
 {
-    using G = PlaneGeo<K, TX, TY, TZ>;
     constexpr int N = G::N, N2 = N * N;
     // The x and z derivatives either straight from the nodal values (D) or from
     // the interpolated ones (Dc), at as many operations.  D rounds once less,
@@ -310,52 +313,6 @@ __global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) apply_plane_ke
     // v_readlane per thread at k = 3), while FP32 takes them as literals.
     constexpr bool NODAL = sizeof(T) == 4;
     constexpr Mat DER = NODAL ? MD : MDC;
-    __shared__ T buf[G::NG * G::GB];
-    VPP_BC_BEGIN(a.x, a.y, a.phi, a.part, a.dot_part, buf, (int64_t)a.m.nn[0] * a.m.nn[1] * a.m.nn[2],
-                 8 * a.nshared, (int64_t)gridDim.x, G::NG * G::GB);
-    if (a.done && *a.done) return;
-    const MeshArgs& m = a.m;
-    const PlaneThread<K, TX, TY, TZ> th(m);
-    const int ip = th.ip;
-    const bool in = th.in;
-    T* const px = buf + th.offx;
-    T* const pz = buf + th.offz;
-    th.template clear_zero_columns<T>(buf);
-
-    // x-plane of phi and of the operand (zeros past the mesh; Dirichlet entries
-    // zeroed after every load has been issued)
-    T cw[N2], u[N2];
-    if (in) {
-        th.template load<BC_PHI>(m, a.phi, cw);
-        th.template load<BC_X>(m, a.x, u);
-        const int faces = cell_dirichlet_faces(m, th.cx, th.cy, th.cz);
-        if (faces) {
-#pragma unroll
-            for (int l = 0; l < N; ++l)
-#pragma unroll
-                for (int j = 0; j < N; ++j)
-                    if (local_dirichlet<K>(faces, ip, j, l)) u[j + N * l] = T(0);
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < N2; ++q) cw[q] = u[q] = T(0);
-    }
-
-    // coefficient at the Gauss points of this thread's z-plane
-    sweep2<K, MS, false, 0>(cw);
-    sweep2<K, MS, false, 1>(cw);
-    put_x<G>(px, cw);
-    plane_sync<G>();
-    get_z<G>(pz, cw);
-    sweep2<K, MS, false, 0>(cw);
-    T wz = T(0);
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-        if (ip == i) wz = T(Tab<K>::t.w[i]);
-#pragma unroll
-    for (int q = 0; q < N2; ++q)
-        cw[q] = coef_scaled<HV>(m, cw[q]) * (wz * T(Tab<K>::t.w[q % N] * Tab<K>::t.w[q / N]));
-
     // operand: y and z interpolation, z derivative; both turn to z-planes
     sweep2<K, MS, false, 0>(u);
     T v[N2];
@@ -444,10 +401,66 @@ __global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) apply_plane_ke
         sweep2<K, MS, true, 1>(v);
     }
     sweep2<K, MS, true, 0>(v);
+#pragma unroll
+    for (int q = 0; q < N2; ++q) u[q] = v[q];
+}
+
+template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS = false>
+__global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) apply_plane_kernel(ApplyArgs<T> a)
+{
+    using G = PlaneGeo<K, TX, TY, TZ>;
+    constexpr int N = G::N, N2 = N * N;
+    __shared__ T buf[G::NG * G::GB];
+    VPP_BC_BEGIN(a.x, a.y, a.phi, a.part, a.dot_part, buf, (int64_t)a.m.nn[0] * a.m.nn[1] * a.m.nn[2],
+                 8 * a.nshared, (int64_t)gridDim.x, G::NG * G::GB);
+    if (a.done && *a.done) return;
+    const MeshArgs& m = a.m;
+    const PlaneThread<K, TX, TY, TZ> th(m);
+    const int ip = th.ip;
+    const bool in = th.in;
+    T* const px = buf + th.offx;
+    T* const pz = buf + th.offz;
+    th.template clear_zero_columns<T>(buf);
+
+    // x-plane of phi and of the operand (zeros past the mesh; Dirichlet entries
+    // zeroed after every load has been issued)
+    T cw[N2], u[N2];
+    if (in) {
+        th.template load<BC_PHI>(m, a.phi, cw);
+        th.template load<BC_X>(m, a.x, u);
+        const int faces = cell_dirichlet_faces(m, th.cx, th.cy, th.cz);
+        if (faces) {
+#pragma unroll
+            for (int l = 0; l < N; ++l)
+#pragma unroll
+                for (int j = 0; j < N; ++j)
+                    if (local_dirichlet<K>(faces, ip, j, l)) u[j + N * l] = T(0);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < N2; ++q) cw[q] = u[q] = T(0);
+    }
+
+    // coefficient at the Gauss points of this thread's z-plane
+    sweep2<K, MS, false, 0>(cw);
+    sweep2<K, MS, false, 1>(cw);
+    put_x<G>(px, cw);
+    plane_sync<G>();
+    get_z<G>(pz, cw);
+    sweep2<K, MS, false, 0>(cw);
+    T wz = T(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (ip == i) wz = T(Tab<K>::t.w[i]);
+#pragma unroll
+    for (int q = 0; q < N2; ++q)
+        cw[q] = coef_scaled<HV>(m, cw[q]) * (wz * T(Tab<K>::t.w[q % N] * Tab<K>::t.w[q / N]));
+
+    plane_operator<G, K, T, MASS>(m, px, pz, cw, wz, u);
     // cell results to the slots: the positions this thread has just read
-    put_x<G>(px, v);
+    put_x<G>(px, u);
     __syncthreads();
-    const double d = flush_plane<K, T, TX, TY, TZ>(m, th, buf, v, a.x, a.y, a.part, a.nshared, DOT);
+    const double d = flush_plane<K, T, TX, TY, TZ>(m, th, buf, u, a.x, a.y, a.part, a.nshared, DOT);
     if constexpr (DOT) {
         const double s = block_sum<G::NTH>(d);
         if (threadIdx.x == 0) VPP_ST(&a.dot_part[blockIdx.x], BC_DOT, s);

@@ -51,10 +51,6 @@ template <typename T>
 hipError_t launch_cg_assemble_update(CgState* st, int par, double* red, const double* dot_part, int ndot,
                                      const unsigned* map, const T* part, int64_t stride, T* r, const T* q,
                                      const T* invd, int64_t n, hipStream_t s);
-// The same for a vector of length n without shared nodes (q = A p complete).
-template <typename T>
-hipError_t launch_cg_update(CgState* st, int par, double* red, const double* dot_part, int ndot, T* r, const T* q,
-                            const T* invd, int64_t n, hipStream_t s);
 // Stop decision, x += alpha p (alpha as in the update) and p = D^-1 r + beta p.
 template <typename T>
 hipError_t launch_cg_pupdate(CgState* st, int par, const double* red, T* x, const T* r, T* p, const T* invd,

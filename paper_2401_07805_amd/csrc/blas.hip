@@ -26,70 +26,10 @@
 
 #include <algorithm>
 
+#include "cg_device.h"
 #include "shared_nodes.h"
 
 namespace vpp {
-
-constexpr int BT = 256;
-
-// 16-byte packet of T (two doubles or four floats): one dwordx4 access.
-template <typename T>
-struct alignas(16) Pack {
-    static constexpr int W = 16 / (int)sizeof(T);
-    T v[W];
-};
-
-// Workgroup sums of two doubles in a fixed order (butterfly inside each wave,
-// then the waves in index order); every thread receives the totals.
-template <int NT>
-__device__ __forceinline__ void block_sum2(double& a, double& b)
-{
-    static_assert(NT % 64 == 0, "whole waves only");
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o);
-        b += __shfl_xor(b, o);
-    }
-    __shared__ double pa[NT / 64], pb[NT / 64];
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-        pa[threadIdx.x / 64] = a;
-        pb[threadIdx.x / 64] = b;
-    }
-    __syncthreads();
-    double sa = 0.0, sb = 0.0;
-#pragma unroll
-    for (int i = 0; i < NT / 64; ++i) {
-        sa += pa[i];
-        sb += pb[i];
-    }
-    a = sa;
-    b = sb;
-}
-
-// Totals of the ng partials of both quantities (every thread receives them).
-__device__ __forceinline__ void sum_partials(const double* red, int ng, double& a, double& b)
-{
-    a = 0.0;
-    b = 0.0;
-    for (int i = threadIdx.x; i < ng; i += BT) {
-        a += red[i];
-        b += red[kMaxRedBlocks + i];
-    }
-    block_sum2<BT>(a, b);
-}
-
-__device__ __forceinline__ void write_partials(double* red, double a, double b, int bid)
-{
-    if (threadIdx.x == 0) {
-        red[bid] = a;
-        red[kMaxRedBlocks + bid] = b;
-    }
-}
-__device__ __forceinline__ void write_partials(double* red, double a, double b)
-{
-    write_partials(red, a, b, blockIdx.x);
-}
 
 // Number of workgroups of the streaming kernels (about 4 packets per thread).
 template <typename T>
@@ -113,7 +53,6 @@ static int grid_update(int64_t n)
 // in batches of kBatch: two per CU while a batch covers the vector (48^3 Q2 8.3
 // us, with four 8.7), then four (64^3 15.9 us, with two 17.2), in whole batches
 // once there are two per thread (64^3 Q3 FP32 25.6 us against 27.3).
-constexpr int kBatch = 4;
 template <typename T>
 static int grid_pupdate(int64_t n)
 {
@@ -219,28 +158,6 @@ __device__ __forceinline__ void assemble_packet(const SharedParts<T>& sp, const 
         if (mp[t]) qv[t] = s[t];
 }
 
-// alpha = rz / p.Ap, with p.Ap summed from the ndot partials by every workgroup
-// in the same order; false when the system has stopped or breaks down here.
-template <typename T>
-__device__ __forceinline__ bool update_alpha(int bid, CgState* st, int par, const double* dot_part, int ndot, T& alpha)
-{
-    // the state read at once (before the barrier of the reduction, so the loads
-    // overlap it instead of following it)
-    const int halt = st->halt[par];
-    const double rz_par = st->rz[par];
-    if (halt) return false;
-    double pAp = 0.0, unused = 0.0;
-    for (int i = threadIdx.x; i < ndot; i += BT) pAp += dot_part[i];
-    block_sum2<BT>(pAp, unused);
-    if (bid == 0 && threadIdx.x == 0) st->pAp = pAp;
-    if (!(pAp > 0.0) || !isfinite(pAp)) {
-        if (bid == 0 && threadIdx.x == 0) st->breakdown = 1;
-        return false;
-    }
-    alpha = T(rz_par / pAp);
-    return true;
-}
-
 // Body of the update for workgroup bid of one system; the workgroup returns at
 // once when the system has stopped.
 template <typename T>
@@ -309,138 +226,12 @@ __device__ __forceinline__ void assemble_update_body(int bid, int nblk, CgState*
     write_partials(red, rr, rz, bid);
 }
 
-// The update for a vector without shared nodes (q complete): plain packets.
-template <typename T>
-__global__ void __launch_bounds__(BT) cg_update_kernel(CgState* st, int par, double* red, const double* dot_part, int ndot,
-                                                       T* __restrict__ r, const T* __restrict__ q,
-                                                       const T* __restrict__ invd, int64_t n)
-{
-    T alpha;
-    if (!update_alpha(blockIdx.x, st, par, dot_part, ndot, alpha)) return;
-    using P = Pack<T>;
-    constexpr int W = P::W;
-    double rr = 0.0, rz = 0.0;
-    const int64_t np = n / W;
-    for (int64_t c = (int64_t)blockIdx.x * BT + threadIdx.x; c < np; c += (int64_t)gridDim.x * BT) {
-        P rv = reinterpret_cast<const P*>(r)[c];
-        const P dv = reinterpret_cast<const P*>(invd)[c];
-        const P qv = reinterpret_cast<const P*>(q)[c];
-#pragma unroll
-        for (int t = 0; t < W; ++t) {
-            const T ri = fma(-alpha, qv.v[t], rv.v[t]);
-            rv.v[t] = ri;
-            rr += (double)ri * (double)ri;
-            rz += (double)ri * (double)(ri * dv.v[t]);
-        }
-        reinterpret_cast<P*>(r)[c] = rv;
-    }
-    if (blockIdx.x == 0)
-        for (int64_t i = np * W + threadIdx.x; i < n; i += BT) {
-            const T ri = fma(-alpha, q[i], r[i]);
-            r[i] = ri;
-            rr += (double)ri * (double)ri;
-            rz += (double)ri * (double)(ri * invd[i]);
-        }
-    block_sum2<BT>(rr, rz);
-    write_partials(red, rr, rz);
-}
-
 template <typename T>
 __global__ void __launch_bounds__(BT) cg_assemble_update_kernel(CgState* st, int par, double* red, SharedParts<T> sp,
                                                                 T* __restrict__ r, const T* __restrict__ q,
                                                                 const T* __restrict__ invd, int64_t n)
 {
     assemble_update_body<T>(blockIdx.x, gridDim.x, st, par, red, sp, r, q, invd, n);
-}
-
-// Packets a thread handles per batch in the search-direction update.  A
-// thread takes packets c, c + S, c + 2S, ... (S = threads of the system's
-// grid) in that order, as a plain grid-stride loop would, but loads a whole
-// batch before it uses any of it, and the first batch before the reduction
-// that gives beta: each batch then costs one memory latency instead of one
-// per packet.
-
-// Body of the search-direction update for workgroup bid of nblk (one system;
-// ng partials of the update to sum).
-template <typename T>
-__device__ __forceinline__ void pupdate_body(int bid, int nblk, CgState* st, int par, const double* red, int ng,
-                                             T* __restrict__ x, const T* __restrict__ r, T* __restrict__ p,
-                                             const T* __restrict__ invd, int64_t n)
-{
-    // every state field this kernel reads, at once (before the reduction's
-    // barrier); thread 0 of workgroup 0 is the only writer, of other fields
-    const int halt = st->halt[par], brk = st->breakdown;
-    const double rz_par = st->rz[par], pAp_par = st->pAp, tol2 = st->tol2;
-    const int iters0 = st->iters, max_iter = st->max_iter, hcap = st->hist_cap;
-    double* const coef = st->coef;
-    if (halt || brk) {
-        if (bid == 0 && threadIdx.x == 0) st->halt[1 - par] = 1;
-        return;
-    }
-    using P = Pack<T>;
-    constexpr int W = P::W, U = kBatch;
-    const int64_t np = n / W;
-    const int64_t S = (int64_t)nblk * BT;
-    const int64_t c0 = (int64_t)bid * BT + threadIdx.x;
-    P rv[U], dv[U], pv[U], xv[U];
-    auto load = [&](int64_t cb) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t c = cb + u * S;
-            if (c < np) {
-                rv[u] = reinterpret_cast<const P*>(r)[c];
-                dv[u] = reinterpret_cast<const P*>(invd)[c];
-                pv[u] = reinterpret_cast<const P*>(p)[c];
-                xv[u] = reinterpret_cast<const P*>(x)[c];
-            }
-        }
-    };
-    load(c0);
-    double rr, rzn;
-    sum_partials(red, ng, rr, rzn);
-    const double beta_d = rzn / rz_par;
-    if (bid == 0 && threadIdx.x == 0) {
-        const int it = iters0 + 1;
-        st->iters = it;
-        st->rr_last = rr;
-        st->rr[par] = rr;
-        st->rznew[par] = rzn;
-        st->rz[1 - par] = rzn;
-        if (!isfinite(rr) || !isfinite(rzn)) {
-            st->breakdown = 1;
-            st->halt[1 - par] = 1;
-        } else if (rr < tol2 || it >= max_iter) {
-            st->halt[1 - par] = 1;
-        }
-        if (coef && it < hcap) {
-            coef[3 * it] = rz_par / pAp_par;
-            coef[3 * it + 1] = beta_d;
-            coef[3 * it + 2] = rzn;
-        }
-    }
-    // the same alpha as the update's (same operands, same rounding)
-    const T alpha = T(rz_par / pAp_par);
-    const T beta = T(beta_d);
-    for (int64_t cb = c0; cb < np; cb += U * S) {
-        if (cb != c0) load(cb);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t c = cb + u * S;
-            if (c >= np) break;
-#pragma unroll
-            for (int j = 0; j < W; ++j) {
-                xv[u].v[j] = fma(alpha, pv[u].v[j], xv[u].v[j]);
-                pv[u].v[j] = fma(beta, pv[u].v[j], rv[u].v[j] * dv[u].v[j]);
-            }
-            reinterpret_cast<P*>(x)[c] = xv[u];
-            reinterpret_cast<P*>(p)[c] = pv[u];
-        }
-    }
-    if (bid == 0)
-        for (int64_t i = np * W + threadIdx.x; i < n; i += BT) {
-            x[i] = fma(alpha, p[i], x[i]);
-            p[i] = fma(beta, p[i], r[i] * invd[i]);
-        }
 }
 
 template <typename T>
@@ -571,17 +362,6 @@ hipError_t launch_cg_assemble_update(CgState* st, int par, double* red, const do
                        invd, n);
     return hipGetLastError();
 }
-
-template <typename T>
-hipError_t launch_cg_update(CgState* st, int par, double* red, const double* dot_part, int ndot, T* r, const T* q,
-                            const T* invd, int64_t n, hipStream_t s)
-{
-    hipLaunchKernelGGL(cg_update_kernel<T>, dim3(grid_update<T>(n)), dim3(BT), 0, s, st, par, red, dot_part, ndot, r, q,
-                       invd, n);
-    return hipGetLastError();
-}
-template hipError_t launch_cg_update<double>(CgState*, int, double*, const double*, int, double*, const double*,
-                                             const double*, int64_t, hipStream_t);
 
 template <typename T>
 hipError_t launch_cg_pupdate(CgState* st, int par, const double* red, T* x, const T* r, T* p, const T* invd,

@@ -182,10 +182,6 @@ hipError_t launch_reinit_apply(int k, const ReinitApplyArgs& a, hipStream_t s);
 // cv: cell_values(k, m) doubles of scratch each.
 hipError_t launch_reinit_diag(int k, const ReinitArgs& r, double* diag, double* cv, hipStream_t s);
 hipError_t launch_reinit_rhs(int k, const ReinitArgs& r, const double* psi, double* b, double* cv, hipStream_t s);
-// part[b] = partial of x . y over the elements workgroup b visits (nblocks <= 1024).
-hipError_t launch_dot_partials(const double* x, const double* y, int64_t n, double* part, int nblocks,
-                               hipStream_t s);
-
 // Batched persistent apply (FP64).
 // Work items of one problem of a batch: a (tile) at degree 2, whose
 // coefficient serves all right-hand sides, a (tile, rhs) at degree 3, the

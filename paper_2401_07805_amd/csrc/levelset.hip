@@ -343,23 +343,6 @@ __global__ void __launch_bounds__(64) reinit_rhs_kernel(ReinitArgs r, const doub
     store_cell<K>(m, cx, cy, cz, out, cv);
 }
 
-// Per-workgroup partials of x . y (fixed order inside the workgroup).
-__global__ void __launch_bounds__(256) dot_partials_kernel(const double* __restrict__ x, const double* __restrict__ y,
-                                                           int64_t n, double* __restrict__ part)
-{
-    __shared__ double red[256];
-    double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        s = fma(x[i], y[i], s);
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
 }  // namespace
 
 // The cell kernel KERNEL<k> over all cells (64-thread workgroups), writing the
@@ -431,11 +414,5 @@ hipError_t launch_reinit_rhs(int k, const ReinitArgs& r, const double* psi, doub
     return launch_node_sum(k, m, cv, b, s);
 }
 #undef VPP_CELLS
-
-hipError_t launch_dot_partials(const double* x, const double* y, int64_t n, double* part, int nblocks, hipStream_t s)
-{
-    hipLaunchKernelGGL(dot_partials_kernel, dim3(nblocks), dim3(256), 0, s, x, y, n, part);
-    return hipGetLastError();
-}
 
 }  // namespace vpp
