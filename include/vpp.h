@@ -379,13 +379,11 @@ vpp_status vpp_tune(vpp_problem p, const char* cache_path, void* stream);
 int32_t vpp_config_candidates(int32_t degree, vpp_kernel_config* out, int32_t cap);
 
 /* Batch of independent problems (same degree, k = 2 or 3; FP64) with nrhs[i]
- * right-hand sides each, applied by ONE persistent kernel that pulls work
- * items from a device queue, followed by one assembly launch for the
- * shared-face nodes of every (problem, rhs); both launches are recorded in one
- * hipGraph.  k = 2: an item is a (problem, tile), the coefficient of the tile
- * computed once for all right-hand sides of its problem; k = 3: an item is a
- * (problem, tile, rhs), the items of one tile consecutive, the coefficient
- * recomputed per item.  Degree 4 returns VPP_ERR_UNSUPPORTED.
+ * right-hand sides each, applied by ONE launch over all (problem, tile, rhs)
+ * items, the items of one tile consecutive, followed by one assembly launch for
+ * the shared-face nodes of every (problem, rhs); both launches are recorded in
+ * one hipGraph.  The tiles are reported as variant 4 (cell per thread); at
+ * degree 3 they run plane per thread.  Degree 4 returns VPP_ERR_UNSUPPORTED.
  * tune_cache: JSON cache path for the autotuner, or NULL to tune without a cache.
  * The problems must have phi set and outlive the batch. */
 vpp_status vpp_batch_create(const vpp_problem* probs, const int32_t* nrhs, int32_t nprob,
@@ -397,7 +395,7 @@ vpp_status vpp_batch_apply(vpp_batch b, const double* const* x, double* const* y
  * rhs, x: host arrays of sum(nrhs) device pointers, ordered problem-major; x
  * holds the initial guesses on entry and the solutions on return.
  * VPP_FP64: the systems of meshes below 2^20 unknowns iterate in lockstep,
- * one iteration being one persistent batched apply and two batched vector
+ * one iteration being one batched apply and two batched vector
  * launches over every such system that has not stopped (systems that have
  * stopped are skipped), recorded in a hipGraph of check_every iterations; each
  * system's reductions are summed in a fixed order.  Systems of larger meshes fill the GPU on their own and are solved

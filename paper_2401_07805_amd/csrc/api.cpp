@@ -206,13 +206,12 @@ struct vpp_batch_s {
     int nitems = 0;
     int64_t total_dofs = 0;
     LaunchCfg cfg{};
-    int nblocks = 0;
+    int* d_owner = nullptr;            // problem of each work item
     BatchProblem* d_probs = nullptr;
     double** d_x = nullptr;
     double** d_y = nullptr;
     double* d_part = nullptr;
     size_t part_n = 0;
-    int* d_queue = nullptr;
     std::vector<const double*> cur_x;
     std::vector<double*> cur_y;
     hipGraphExec_t graph = nullptr;
@@ -224,7 +223,8 @@ struct vpp_batch_s {
     std::vector<int> cg_prob;          // problems whose systems advance in lockstep
     std::vector<int> cg_index;         // system (problem-major) -> lockstep system, -1 if solved alone
     BatchProblem* cg_probs = nullptr;  // device table of the lockstep problems
-    int cg_nitems = 0, cg_nblocks = 0, cg_nsys = 0;
+    int* cg_item_owner = nullptr;      // lockstep problem of each of their work items
+    int cg_nitems = 0, cg_nsys = 0;
     std::vector<int64_t> cg_off;
     double *cg_x = nullptr, *cg_r = nullptr, *cg_p = nullptr, *cg_q = nullptr;
     double** cg_tx = nullptr;          // device pointer tables of x, p, q per system
@@ -2374,6 +2374,14 @@ vpp_status vpp_tune(vpp_problem p, const char* cache_path, void* stream)
 // ---------------------------------------------------------------------------
 // Batches
 
+// The problem of every work item of a table.
+static std::vector<int> batch_item_owner(const std::vector<BatchProblem>& tab)
+{
+    std::vector<int> owner;
+    for (size_t i = 0; i < tab.size(); ++i) owner.insert(owner.end(), batch_items(tab[i].ntiles, tab[i].nrhs), (int)i);
+    return owner;
+}
+
 static vpp_status batch_build_table(vpp_batch b)
 {
     std::vector<BatchProblem> tab(b->probs.size());
@@ -2393,7 +2401,7 @@ static vpp_status batch_build_table(vpp_batch b)
         tab[i].ntiles = tile_count(m);
         tab[i].dot_begin = dot;
         dot += tab[i].ntiles * b->nrhs[i];
-        item += batch_items(b->k, tab[i].ntiles, b->nrhs[i]);
+        item += batch_items(tab[i].ntiles, b->nrhs[i]);
         rhs += b->nrhs[i];
         part += 8 * std::max<int64_t>(1, tab[i].nshared) * b->nrhs[i];
     }
@@ -2407,12 +2415,17 @@ static vpp_status batch_build_table(vpp_batch b)
     }
     VPP_HIP(hipMemcpy(b->d_probs, tab.data(), tab.size() * sizeof(BatchProblem), hipMemcpyHostToDevice));
     b->tab = tab;
-    int per_cu = batch_blocks_per_cu(b->cfg, b->k);
-    if (per_cu < 1) per_cu = 1;
-    hipDeviceProp_t prop;
-    VPP_HIP(hipGetDeviceProperties(&prop, b->device));
-    b->nblocks = std::max(1, std::min(prop.multiProcessorCount * per_cu, b->nitems));
-    return VPP_OK;
+    VPP_HIP(hipStreamSynchronize(b->stream));   // a launch may still read the old table
+    dev_free(b->d_owner);
+    return upload(&b->d_owner, batch_item_owner(tab), "batch item table");
+}
+
+// Largest number of shared nodes of the problems in a table.
+static int64_t batch_max_shared(const std::vector<BatchProblem>& tab)
+{
+    int64_t n = 0;
+    for (const BatchProblem& P : tab) n = std::max(n, P.se.cz + P.se.cy + P.se.cx);
+    return n;
 }
 
 static int batch_any_mass(vpp_batch b)
@@ -2428,10 +2441,10 @@ static vpp_status batch_build_graph(vpp_batch b)
     b->graph = nullptr;
     hipGraph_t g = nullptr;
     VPP_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    BatchArgs ba{b->d_probs, (int)b->probs.size(), b->nitems, b->d_x, b->d_y, b->d_part, b->d_queue,
-                 b->probs[0]->desc.heaviside, nullptr, 0, nullptr};
+    BatchArgs ba{b->d_probs, (int)b->probs.size(), b->nitems, b->d_x, b->d_y, b->d_part, b->d_owner,
+                 batch_max_shared(b->tab), b->probs[0]->desc.heaviside, nullptr, 0, nullptr};
     ba.any_mass = batch_any_mass(b);
-    hipError_t err = launch_batch_apply(b->cfg, b->k, ba, b->nblocks, b->total_rhs, false, b->stream);
+    hipError_t err = launch_batch_apply(b->cfg, b->k, ba, b->total_rhs, false, b->stream);
     hipError_t e2 = hipStreamEndCapture(b->stream, &g);
     if (err != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -2460,7 +2473,7 @@ static vpp_status batch_tune(vpp_batch b, const char* cache_path)
 {
     const std::string key = size_bucket_key("batch", b->k, b->total_dofs);
     LaunchCfg c;
-    if (cache_lookup(cache_path, key, &c) && batch_blocks_per_cu(c, b->k) > 0) {
+    if (cache_lookup(cache_path, key, &c) && batch_config_supported(c, b->k)) {
         b->cfg = c;
         return batch_build_table(b);
     }
@@ -2479,8 +2492,7 @@ static vpp_status batch_tune(vpp_batch b, const char* cache_path)
     LaunchCfg all[16], cands[16];
     const int na = std::min(list_batch_configs(b->k, all, 16), 16);
     int nc = 0;
-    for (int i = 0; i < na; ++i)
-        if (batch_blocks_per_cu(all[i], b->k) > 0) cands[nc++] = all[i];
+    for (int i = 0; i < na; ++i) cands[nc++] = all[i];
     if (nc == 0) st = fail(VPP_ERR_UNSUPPORTED, "no batch kernel configuration for this degree");
     double best = 1e300;
     LaunchCfg best_cfg = nc ? cands[0] : LaunchCfg{4, {8, 8, 4}};
@@ -2545,7 +2557,7 @@ static void batch_cg_free(vpp_batch b)
     dev_free(b->cg_probs);
     dev_free(b->cg_x); dev_free(b->cg_r); dev_free(b->cg_p); dev_free(b->cg_q);
     dev_free(b->cg_tx); dev_free(b->cg_tp); dev_free(b->cg_tq);
-    dev_free(b->cg_st); dev_free(b->cg_red); dev_free(b->cg_dot); dev_free(b->cg_rr); dev_free(b->cg_sys); dev_free(b->cg_owner); dev_free(b->cg_map);
+    dev_free(b->cg_st); dev_free(b->cg_red); dev_free(b->cg_dot); dev_free(b->cg_rr); dev_free(b->cg_sys); dev_free(b->cg_owner); dev_free(b->cg_item_owner); dev_free(b->cg_map);
     if (b->cg_hst) (void)hipHostFree(b->cg_hst);
     if (b->cg_hrr) (void)hipHostFree(b->cg_hrr);
     b->cg_hst = nullptr;
@@ -2569,7 +2581,7 @@ static vpp_status batch_cg_setup(vpp_batch b)
         P.rhs_begin = rhs;
         P.dot_begin = ndot;
         for (int j = 0; j < b->nrhs[i]; ++j) b->cg_index[k + j] = rhs + j;
-        item += batch_items(b->k, P.ntiles, P.nrhs);
+        item += batch_items(P.ntiles, P.nrhs);
         rhs += P.nrhs;
         ndot += P.ntiles * P.nrhs;
         tab.push_back(P);
@@ -2579,8 +2591,6 @@ static vpp_status batch_cg_setup(vpp_batch b)
     b->cg_nsys = S;
     b->cg_nitems = item;
     if (S == 0) return VPP_OK;
-    int per_cu = batch_blocks_per_cu(b->cfg, b->k);
-    b->cg_nblocks = std::max(1, std::min(device_cu_count() * std::max(1, per_cu), item));
     b->cg_off.assign(S + 1, 0);
     for (size_t t = 0, sidx = 0; t < tab.size(); ++t)
         for (int j = 0; j < tab[t].nrhs; ++j, ++sidx)   // 512-byte aligned system vectors
@@ -2660,7 +2670,8 @@ static vpp_status batch_cg_setup(vpp_batch b)
     b->cg_blocks = blk;
     std::vector<int> owner;
     for (size_t i = 0; i < S; ++i) owner.insert(owner.end(), sys[i].nblk, (int)i);
-    if ((st = upload(&b->cg_owner, owner, "batch cg workgroup table"))) {
+    if ((st = upload(&b->cg_owner, owner, "batch cg workgroup table")) ||
+        (st = upload(&b->cg_item_owner, batch_item_owner(tab), "batch cg item table"))) {
         batch_cg_free(b);
         return st;
     }
@@ -2686,12 +2697,12 @@ static vpp_status batch_cg_graph(vpp_batch b, int iters)
     hipError_t err = hipSuccess;
     for (int it = 0; it < iters && err == hipSuccess; ++it) {
         const int par = it & 1;
-        BatchArgs ba{b->cg_probs, (int)b->cg_prob.size(), b->cg_nitems, b->cg_tp, b->cg_tq, b->d_part, b->d_queue,
-                     b->probs[0]->desc.heaviside, b->cg_st, par, b->cg_dot};
+        BatchArgs ba{b->cg_probs, (int)b->cg_prob.size(), b->cg_nitems, b->cg_tp, b->cg_tq, b->d_part,
+                     b->cg_item_owner, 0, b->probs[0]->desc.heaviside, b->cg_st, par, b->cg_dot};
         ba.any_mass = batch_any_mass(b);
-        err = launch_batch_apply(b->cfg, b->k, ba, b->cg_nblocks, b->cg_nsys, true, b->stream);
+        err = launch_batch_apply(b->cfg, b->k, ba, b->cg_nsys, true, b->stream);
         if (err == hipSuccess)
-            err = launch_cg_batch_step(b->cg_sys, b->cg_owner, b->cg_blocks, par, b->d_queue, b->stream);
+            err = launch_cg_batch_step(b->cg_sys, b->cg_owner, b->cg_blocks, par, b->stream);
     }
     hipError_t e2 = hipStreamEndCapture(b->stream, &g);
     if (err != hipSuccess) {
@@ -2709,10 +2720,10 @@ static vpp_status batch_cg_graph(vpp_batch b, int iters)
 // q = A x of every lockstep system (plain batched apply, assembly included).
 static vpp_status batch_cg_apply_x(vpp_batch b)
 {
-    BatchArgs ba{b->cg_probs, (int)b->cg_prob.size(), b->cg_nitems, b->cg_tx, b->cg_tq, b->d_part, b->d_queue,
-                 b->probs[0]->desc.heaviside, nullptr, 0, nullptr};
+    BatchArgs ba{b->cg_probs, (int)b->cg_prob.size(), b->cg_nitems, b->cg_tx, b->cg_tq, b->d_part, b->cg_item_owner,
+                 batch_max_shared(b->tab), b->probs[0]->desc.heaviside, nullptr, 0, nullptr};
     ba.any_mass = batch_any_mass(b);
-    VPP_HIP(launch_batch_apply(b->cfg, b->k, ba, b->cg_nblocks, b->cg_nsys, false, b->stream));
+    VPP_HIP(launch_batch_apply(b->cfg, b->k, ba, b->cg_nsys, false, b->stream));
     return VPP_OK;
 }
 
@@ -2847,13 +2858,11 @@ vpp_status vpp_batch_create(const vpp_problem* probs, const int32_t* nrhs, int32
     b->cfg = LaunchCfg{4, {8, 4, 4}};
     vpp_status st;
     if ((st = dev_alloc(&b->d_probs, nprob, "batch table")) || (st = dev_alloc(&b->d_x, b->total_rhs, "batch x")) ||
-        (st = dev_alloc(&b->d_y, b->total_rhs, "batch y")) || (st = dev_alloc(&b->d_queue, 1, "batch queue"))) {
+        (st = dev_alloc(&b->d_y, b->total_rhs, "batch y"))) {
         vpp_batch_destroy(b);
         return st;
     }
-    // the work counter starts at zero; the assembly launch resets it after every pass
-    if (hipMemset(b->d_queue, 0, sizeof(int)) != hipSuccess ||
-        hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) != hipSuccess) {
+    if (hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) != hipSuccess) {
         vpp_batch_destroy(b);
         return fail(VPP_ERR_HIP, "batch set-up failed");
     }
@@ -2946,7 +2955,7 @@ vpp_status vpp_batch_destroy(vpp_batch b)
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     if (b->graph) (void)hipGraphExecDestroy(b->graph);
     batch_cg_free(b);
-    dev_free(b->d_probs); dev_free(b->d_x); dev_free(b->d_y); dev_free(b->d_part); dev_free(b->d_queue);
+    dev_free(b->d_probs); dev_free(b->d_x); dev_free(b->d_y); dev_free(b->d_part); dev_free(b->d_owner);
     if (b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
     return VPP_OK;

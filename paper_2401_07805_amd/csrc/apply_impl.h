@@ -769,16 +769,12 @@ __device__ __forceinline__ double flush_two_pass(const MeshArgs& m, const TileCo
 // in for a neighbour cell below the tile.
 
 
-template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS = false>
-__global__ void __launch_bounds__(TX * TY * TZ) apply_slot_kernel(ApplyArgs<T> a)
+// Body of a workgroup on one tile; dot_out: its partial of x . (A x).
+template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS>
+__device__ __forceinline__ void slot_tile(const ApplyArgs<T>& a, int tile, T* slot, double* dot_out)
 {
     constexpr int N = K + 1, N3 = N * N * N, NT = TX * TY * TZ, CS = NT + 1;
-    __shared__ T slot[N3 * CS];
-    VPP_BC_BEGIN(a.x, a.y, a.phi, a.part, a.dot_part, slot, (int64_t)a.m.nn[0] * a.m.nn[1] * a.m.nn[2],
-                 8 * a.nshared, (int64_t)gridDim.x, N3 * CS);
-    if (a.done && *a.done) return;
     const MeshArgs& m = a.m;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const TileCoord tc = tile_coord<K, TX, TY, TZ>(m, tile);
     const int tid = threadIdx.x;
     const int lx = tid % TX, ly = (tid / TX) % TY, lz = tid / (TX * TY);
@@ -807,8 +803,19 @@ __global__ void __launch_bounds__(TX * TY * TZ) apply_slot_kernel(ApplyArgs<T> a
                                                       a.part, a.nshared, DOT);
     if constexpr (DOT) {
         const double s = block_sum<NT>(d);
-        if (threadIdx.x == 0) VPP_ST(&a.dot_part[blockIdx.x], BC_DOT, s);
+        if (threadIdx.x == 0) VPP_ST(dot_out, BC_DOT, s);
     }
+}
+
+template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS = false>
+__global__ void __launch_bounds__(TX * TY * TZ) apply_slot_kernel(ApplyArgs<T> a)
+{
+    constexpr int N3 = (K + 1) * (K + 1) * (K + 1), CS = TX * TY * TZ + 1;
+    __shared__ T slot[N3 * CS];
+    VPP_BC_BEGIN(a.x, a.y, a.phi, a.part, a.dot_part, slot, (int64_t)a.m.nn[0] * a.m.nn[1] * a.m.nn[2],
+                 8 * a.nshared, (int64_t)gridDim.x, N3 * CS);
+    if (a.done && *a.done) return;
+    slot_tile<K, T, TX, TY, TZ, HV, DOT, MASS>(a, xcd_tile(blockIdx.x, gridDim.x), slot, a.dot_part + blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,5 +1,5 @@
 // Diagonal, fill and batched kernels and their launchers.
-#include "apply_impl.h"
+#include "apply_plane.h"
 #include "shared_nodes.h"
 
 namespace vpp {
@@ -155,16 +155,35 @@ struct Pair<float> {
     using type = float2;
 };
 
+// Nodes f and f + 1 (f even) of the enumeration: their positions and sharer
+// counts first (no memory), then every partial of both loaded before any is used.
 template <typename T>
-__device__ __forceinline__ void assemble_one(const SharedEnum& e, const MeshArgs& m, const T* __restrict__ part,
-                                             int64_t stride, int64_t f, T v, T* __restrict__ y)
+__device__ __forceinline__ void assemble_pair(const SharedEnum& e, const MeshArgs& m, const T* __restrict__ part,
+                                              int64_t stride, int64_t f, int64_t count, T* __restrict__ y)
 {
-    int i, j, l;
-    shared_node(e, f, i, j, l);
-    if (is_dirichlet(m, i, j, l)) return;
-    const int n = sharer_count(e, i, j, l);
-    for (int c = 2; c < n; ++c) v += VPP_LD(&part[c * stride + f], BC_PART);
-    VPP_ST(&y[i + (int64_t)m.nn[0] * (j + (int64_t)m.nn[1] * l)], BC_Y, v);
+    using P = typename Pair<T>::type;
+    int i0, j0, l0, i1 = 0, j1 = 0, l1 = 0;
+    shared_node(e, f, i0, j0, l0);
+    const bool has1 = f + 1 < count;
+    if (has1) shared_node(e, f + 1, i1, j1, l1);
+    const int n0 = is_dirichlet(m, i0, j0, l0) ? 0 : sharer_count(e, i0, j0, l0);
+    const int n1 = !has1 || is_dirichlet(m, i1, j1, l1) ? 0 : sharer_count(e, i1, j1, l1);
+    const P r0 = VPP_LD(reinterpret_cast<const P*>(part + f), BC_PART);
+    const P r1 = VPP_LD(reinterpret_cast<const P*>(part + stride + f), BC_PART);
+    T x0[6], x1[6];
+#pragma unroll
+    for (int c = 2; c < 8; ++c) {
+        x0[c - 2] = c < n0 ? VPP_LD(&part[c * stride + f], BC_PART) : T(0);
+        x1[c - 2] = c < n1 ? VPP_LD(&part[c * stride + f + 1], BC_PART) : T(0);
+    }
+    T v0 = r0.x + r1.x, v1 = r0.y + r1.y;
+#pragma unroll
+    for (int c = 2; c < 8; ++c) {
+        if (c < n0) v0 += x0[c - 2];
+        if (c < n1) v1 += x1[c - 2];
+    }
+    if (n0 > 0) VPP_ST(&y[i0 + (int64_t)m.nn[0] * (j0 + (int64_t)m.nn[1] * l0)], BC_Y, v0);
+    if (n1 > 0) VPP_ST(&y[i1 + (int64_t)m.nn[0] * (j1 + (int64_t)m.nn[1] * l1)], BC_Y, v1);
 }
 
 template <typename T>
@@ -188,32 +207,8 @@ __global__ void __launch_bounds__(256) assemble_kernel(AssembleArgs<T> a)
     }
     const SharedEnum& e = a.e;
     const int64_t count = e.cz + e.cy + e.cx;
-    using P = typename Pair<T>::type;
     for (int64_t f = 2 * ((int64_t)blockIdx.x * 256 + threadIdx.x); f < count; f += 2 * (int64_t)gridDim.x * 256) {
-        // positions and sharer counts of nodes f and f + 1 first (no memory),
-        // then every partial of both nodes loaded before any is used
-        int i0, j0, l0, i1 = 0, j1 = 0, l1 = 0;
-        shared_node(e, f, i0, j0, l0);
-        const bool has1 = f + 1 < count;
-        if (has1) shared_node(e, f + 1, i1, j1, l1);
-        const int n0 = is_dirichlet(a.m, i0, j0, l0) ? 0 : sharer_count(e, i0, j0, l0);
-        const int n1 = !has1 || is_dirichlet(a.m, i1, j1, l1) ? 0 : sharer_count(e, i1, j1, l1);
-        const P r0 = VPP_LD(reinterpret_cast<const P*>(a.part + f), BC_PART);
-        const P r1 = VPP_LD(reinterpret_cast<const P*>(a.part + a.nshared + f), BC_PART);
-        T x0[6], x1[6];
-#pragma unroll
-        for (int c = 2; c < 8; ++c) {
-            x0[c - 2] = c < n0 ? VPP_LD(&a.part[c * a.nshared + f], BC_PART) : T(0);
-            x1[c - 2] = c < n1 ? VPP_LD(&a.part[c * a.nshared + f + 1], BC_PART) : T(0);
-        }
-        T v0 = r0.x + r1.x, v1 = r0.y + r1.y;
-#pragma unroll
-        for (int c = 2; c < 8; ++c) {
-            if (c < n0) v0 += x0[c - 2];
-            if (c < n1) v1 += x1[c - 2];
-        }
-        if (n0 > 0) VPP_ST(&a.y[i0 + (int64_t)a.m.nn[0] * (j0 + (int64_t)a.m.nn[1] * l0)], BC_Y, v0);
-        if (n1 > 0) VPP_ST(&a.y[i1 + (int64_t)a.m.nn[0] * (j1 + (int64_t)a.m.nn[1] * l1)], BC_Y, v1);
+        assemble_pair(e, a.m, a.part, a.nshared, f, count, a.y);
     }
 }
 
@@ -242,119 +237,52 @@ int device_cu_count()
 }
 
 // ---------------------------------------------------------------------------
-// Batched persistent apply: one launch over the (problem, tile) work items of
-// several independent meshes.  Workgroups pull items from a device counter
-// until the list is exhausted (every workgroup leaves the loop once the
-// counter passes the item count).  The coefficient of a tile is computed once
-// and reused for all right-hand sides of its problem.  A second launch
-// assembles the shared-face nodes of every (problem, rhs) and resets the counter.
+// Batched apply: one launch over the (problem, tile, rhs) items of several
+// independent meshes, a workgroup each, the items of one tile consecutive (on one
+// XCD, so the tile's phi stays in its L2 for the next right-hand side); a second
+// launch assembles the shared nodes of every (problem, rhs).
+//
+// An item runs the single apply's body: cell per thread at k = 2, plane per
+// thread at k = 3, with its registers (two waves per SIMD at k = 2).  A
+// persistent kernel that pulled tiles from a queue and kept a tile's coefficient
+// over its right-hand sides held 421-512 registers, one wave per SIMD: 8 meshes of
+// 16^3-64^3 Q2 x 4 right-hand sides 607 us against 430, the apply of a PCG over
+// 16 systems of 16^3-40^3 60 against 43; 8 Q3 meshes of 8^3-32^3 x 4 228 against
+// 103 (there cell per thread, spilled).
 
-template <int K, int TX, int TY, int TZ, int HV, int DM>
-__global__ void __launch_bounds__(TX * TY * TZ) batch_apply_kernel(BatchArgs a)
+template <int K, int TX, int TY, int TZ>
+constexpr int batch_threads()
 {
-    constexpr int N = K + 1, N3 = N * N * N, NT = TX * TY * TZ, CS = NT + 1;
-    // Q2: a work item is a (problem, tile) whose coefficient is computed once
-    // for all right-hand sides of the problem.  Q3: a work item is a (problem,
-    // tile, rhs), the items of one tile consecutive, and the coefficient is
-    // recomputed per item (its 64 values held across a loop over right-hand
-    // sides, beside the cell's 64, would not fit in the registers; the tile's
-    // phi is still in the caches for the next item).  The x . Ax partials of
-    // the batched PCG (DM & 1) and the mass shift (DM & 2) are template
-    // choices, as in the single-problem kernel, which keeps the branches they
-    // would add out of the register allocation.
-    constexpr bool per_tile = K == 2;
-    __shared__ double slot[N3 * CS];
-    __shared__ int item_s;
-    const int tid = threadIdx.x;
-    for (int q = tid; q < N3; q += NT) slot[q * CS + NT] = 0.0;
-    const int lx = tid % TX, ly = (tid / TX) % TY, lz = tid / (TX * TY);
-    for (;;) {
-        if (tid == 0) item_s = atomicAdd(a.queue, 1);
-        __syncthreads();
-        const int item = item_s;
-        __syncthreads();
-        if (item >= a.nitems) break;
-        int pi = 0;
-        for (int i = 1; i < a.nprob; ++i)
-            if (a.probs[i].tile_begin <= item) pi = i;
-        const MeshArgs m = a.probs[pi].m;
-        const double* phi = a.probs[pi].phi;
-        const int nrhs = a.probs[pi].nrhs, rhs0 = a.probs[pi].rhs_begin;
-        const int local = item - a.probs[pi].tile_begin;
-        const int tile = per_tile ? local : local / nrhs;   // the inverse of batch_items
-        const TileCoord tc = tile_coord<K, TX, TY, TZ>(m, tile);
-        const int cx = tc.t[0] * TX + lx, cy = tc.t[1] * TY + ly, cz = tc.t[2] * TZ + lz;
-        const bool active = cx < m.nc[0] && cy < m.nc[1] && cz < m.nc[2];
-        // gathers from a wave-uniform tile base plus the lane's cell offset
-        const int nx = m.nn[0], nxy = m.nn[0] * m.nn[1];
-        const int64_t tile0 = uniform_i64(node_index(m, tc.n0[0], tc.n0[1], tc.n0[2]));
-        const unsigned lane_b = (unsigned)(K * lx + nx * K * ly + nxy * K * lz) * (unsigned)sizeof(double);
-        const int faces = active ? cell_dirichlet_faces(m, cx, cy, cz) : 0;
-        auto coefficient = [&](double (&w)[N3]) {
-            gather_cell_t<K>(phi + tile0, lane_b, nx, nxy, 0, w);
-            sweep3<K, MS, false, 0>(w);
-            sweep3<K, MS, false, 1>(w);
-            sweep3<K, MS, false, 2>(w);
-            coef_weights3<K, HV>(m, w);
-        };
-        // one right-hand side r of this tile with the coefficient cw
-        auto one_rhs = [&](int r, const double (&cw)[N3]) {
-            const double* x = a.x[rhs0 + r];
-            double* y = a.y[rhs0 + r];
-            double* part = a.part + a.probs[pi].part_begin + (int64_t)r * 8 * a.probs[pi].nshared;
-            VPP_BC_SYNC();
-            VPP_BC_BEGIN(x, y, phi, part, a.dot_part ? a.dot_part + a.probs[pi].dot_begin : nullptr, slot,
-                         (int64_t)m.nn[0] * m.nn[1] * m.nn[2], 8 * a.probs[pi].nshared,
-                         (int64_t)nrhs * a.probs[pi].ntiles, N3 * CS);
-            double u[N3];
-            if (active) {
-                gather_cell_t<K>(x + tile0, lane_b, nx, nxy, faces, u);
-                cell_operator<K, double, (DM & 2) != 0>(m, cw, u);   // a zero shift adds exact zeros
-            }
-            __syncthreads();   // the previous write-out has finished reading the slots
-            if (active) {
-#pragma unroll
-                for (int q = 0; q < N3; ++q)
-                    if (!owned_pos<K>(q % N, (q / N) % N, q / (N * N))) VPP_ST(&slot[q * CS + tid], BC_SLOT, u[q]);
-            }
-            __syncthreads();
-            constexpr bool dot = (DM & 1) != 0;
-            const double d = flush_two_pass<K, double, TX, TY, TZ>(m, tc, slot, CS, u, active, lx, ly, lz, cx, cy,
-                                                                   cz, x, y, part, a.probs[pi].nshared, dot);
-            if (dot) {
-                const double sum = block_sum<NT>(d);
-                if (tid == 0) VPP_ST(&a.dot_part[a.probs[pi].dot_begin + r * a.probs[pi].ntiles + tile], BC_DOT, sum);
-            }
-        };
-        if constexpr (per_tile) {
-            // systems of a batched PCG that have stopped are skipped
-            bool any = true;
-            if (a.st) {
-                any = false;
-                for (int r = 0; r < nrhs; ++r) any = any || !a.st[rhs0 + r].halt[a.par];
-            }
-            // the bounds table of the debug build: this problem's phi (the
-            // barrier first: the previous item's write-out may still read it)
-            VPP_BC_SYNC();
-            VPP_BC_BEGIN((const double*)nullptr, (const double*)nullptr, phi, (const double*)nullptr,
-                         (const double*)nullptr, slot, (int64_t)m.nn[0] * m.nn[1] * m.nn[2], 0, 0, N3 * CS);
-            double cw[N3];
-            if (active && any) coefficient(cw);
-            for (int r = 0; r < nrhs; ++r) {
-                if (a.st && a.st[rhs0 + r].halt[a.par]) continue;   // uniform over the workgroup
-                one_rhs(r, cw);
-            }
-        } else {
-            const int r = local - tile * nrhs;
-            if (a.st && a.st[rhs0 + r].halt[a.par]) continue;   // uniform over the workgroup
-            VPP_BC_SYNC();
-            VPP_BC_BEGIN((const double*)nullptr, (const double*)nullptr, phi, (const double*)nullptr,
-                         (const double*)nullptr, slot, (int64_t)m.nn[0] * m.nn[1] * m.nn[2], 0, 0, N3 * CS);
-            double cw[N3];
-            if (active) coefficient(cw);
-            one_rhs(r, cw);
-        }
-    }
+    if constexpr (K == 2) return TX * TY * TZ;
+    else return PlaneGeo<K, TX, TY, TZ>::NTH;
+}
+
+template <int K, int TX, int TY, int TZ>
+constexpr int batch_lds()
+{
+    if constexpr (K == 2) return (K + 1) * (K + 1) * (K + 1) * (TX * TY * TZ + 1);
+    else return PlaneGeo<K, TX, TY, TZ>::NG * PlaneGeo<K, TX, TY, TZ>::GB;
+}
+
+// DM & 1: x . Ax partials (batched PCG), DM & 2: mass shift (zero adds exact zeros).
+template <int K, int TX, int TY, int TZ, int HV, int DM>
+__global__ void __launch_bounds__((batch_threads<K, TX, TY, TZ>())) batch_apply_kernel(BatchArgs a)
+{
+    constexpr int LDS = batch_lds<K, TX, TY, TZ>();
+    constexpr bool dot = (DM & 1) != 0, mass = (DM & 2) != 0;
+    __shared__ double slot[LDS];
+    const int item = xcd_tile(blockIdx.x, gridDim.x);
+    const BatchProblem& P = a.probs[__builtin_amdgcn_readfirstlane(a.owner[item])];
+    const int local = item - P.tile_begin, tile = local / P.nrhs, r = local - tile * P.nrhs;   // batch_items' order
+    const int rhs = P.rhs_begin + r;
+    if (a.st && a.st[rhs].halt[a.par]) return;   // a system that has stopped
+    const ApplyArgs<double> t{P.m, a.x[rhs], a.y[rhs], P.phi, a.part + P.part_begin + (int64_t)r * 8 * P.nshared,
+                              P.nshared, dot ? a.dot_part + P.dot_begin : nullptr, nullptr, nullptr, true};
+    double* const dot_out = t.dot_part + r * P.ntiles + tile;
+    VPP_BC_BEGIN(t.x, t.y, t.phi, t.part, t.dot_part, slot, (int64_t)t.m.nn[0] * t.m.nn[1] * t.m.nn[2],
+                 8 * t.nshared, (int64_t)P.nrhs * P.ntiles, LDS);
+    if constexpr (K == 2) slot_tile<K, double, TX, TY, TZ, HV, dot, mass>(t, tile, slot, dot_out);
+    else plane_tile<K, double, TX, TY, TZ, HV, dot, mass>(t, tile, slot, dot_out);
 }
 
 struct BatchAssembleArgs {
@@ -362,13 +290,11 @@ struct BatchAssembleArgs {
     int nprob;
     double* const* y;
     double* part;
-    int* queue;
 };
 
 // grid.y = (problem, rhs) pair; grid.x strides over that pair's shared nodes.
 __global__ void __launch_bounds__(256) batch_assemble_kernel(BatchAssembleArgs a)
 {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *a.queue = 0;
     int pr = blockIdx.y, pi = 0;
     for (; pi < a.nprob; ++pi) {
         if (pr < a.probs[pi].nrhs) break;
@@ -383,12 +309,8 @@ __global__ void __launch_bounds__(256) batch_assemble_kernel(BatchAssembleArgs a
                  (const double*)nullptr, (int64_t)P.m.nn[0] * P.m.nn[1] * P.m.nn[2], 8 * ns, 0, 0);
     const SharedEnum& e = P.se;
     const int64_t count = e.cz + e.cy + e.cx;
-    for (int64_t f = 2 * ((int64_t)blockIdx.x * 256 + threadIdx.x); f < count; f += 2 * (int64_t)gridDim.x * 256) {
-        const double2 r0 = VPP_LD(reinterpret_cast<const double2*>(part + f), BC_PART);
-        const double2 r1 = VPP_LD(reinterpret_cast<const double2*>(part + ns + f), BC_PART);
-        assemble_one(e, P.m, part, ns, f, r0.x + r1.x, y);
-        if (f + 1 < count) assemble_one(e, P.m, part, ns, f + 1, r0.y + r1.y, y);
-    }
+    for (int64_t f = 2 * ((int64_t)blockIdx.x * 256 + threadIdx.x); f < count; f += 2 * (int64_t)gridDim.x * 256)
+        assemble_pair(e, P.m, part, ns, f, count, y);
 }
 
 #define VPP_BATCH_CONFIGS(X) \
@@ -401,9 +323,9 @@ __global__ void __launch_bounds__(256) batch_assemble_kernel(BatchAssembleArgs a
     X(3, 4, 4, 4)
 
 template <int K, int TX, int TY, int TZ, int HV>
-static void launch_batch_tiles(const BatchArgs& a, int nblocks, hipStream_t s)
+static void launch_batch_tiles(const BatchArgs& a, hipStream_t s)
 {
-    const dim3 g(nblocks), blk(TX * TY * TZ);
+    const dim3 g(a.nitems), blk(batch_threads<K, TX, TY, TZ>());
     switch ((a.st ? 1 : 0) | (a.any_mass ? 2 : 0)) {
     case 0: hipLaunchKernelGGL((batch_apply_kernel<K, TX, TY, TZ, HV, 0>), g, blk, 0, s, a); break;
     case 1: hipLaunchKernelGGL((batch_apply_kernel<K, TX, TY, TZ, HV, 1>), g, blk, 0, s, a); break;
@@ -412,22 +334,34 @@ static void launch_batch_tiles(const BatchArgs& a, int nblocks, hipStream_t s)
     }
 }
 
-hipError_t launch_batch_apply(const LaunchCfg& c, int k, const BatchArgs& a, int nblocks, int total_rhs,
-                              bool tiles_only, hipStream_t s)
+hipError_t launch_batch_apply(const LaunchCfg& c, int k, const BatchArgs& a, int total_rhs, bool tiles_only,
+                              hipStream_t s)
 {
+    if (a.nitems < 1) return hipErrorInvalidValue;
 #define VPP_BL(K, TX, TY, TZ)                                                                       \
     if (k == K && c.variant == 4 && c.tile[0] == TX && c.tile[1] == TY && c.tile[2] == TZ) {       \
-        if (a.heaviside == 0) launch_batch_tiles<K, TX, TY, TZ, 0>(a, nblocks, s);                  \
-        else launch_batch_tiles<K, TX, TY, TZ, 1>(a, nblocks, s);                                   \
+        if (a.heaviside == 0) launch_batch_tiles<K, TX, TY, TZ, 0>(a, s);                           \
+        else launch_batch_tiles<K, TX, TY, TZ, 1>(a, s);                                            \
         hipError_t e = hipGetLastError();                                                           \
         if (e != hipSuccess || tiles_only) return e;                                                \
-        BatchAssembleArgs b{a.probs, a.nprob, a.y, a.part, a.queue};                                \
-        hipLaunchKernelGGL(batch_assemble_kernel, dim3(512, (unsigned)total_rhs), dim3(256), 0, s, b);  \
+        BatchAssembleArgs b{a.probs, a.nprob, a.y, a.part};                                         \
+        const int64_t want = (a.max_shared + 511) / 512;                                            \
+        const unsigned gx = (unsigned)(want < 1 ? 1 : (want < 512 ? want : 512));                   \
+        hipLaunchKernelGGL(batch_assemble_kernel, dim3(gx, (unsigned)total_rhs), dim3(256), 0, s, b);  \
         return hipGetLastError();                                                                   \
     }
     VPP_BATCH_CONFIGS(VPP_BL)
 #undef VPP_BL
     return hipErrorInvalidValue;
+}
+
+bool batch_config_supported(const LaunchCfg& c, int k)
+{
+#define VPP_BS(K, TX, TY, TZ) \
+    if (k == K && c.variant == 4 && c.tile[0] == TX && c.tile[1] == TY && c.tile[2] == TZ) return true;
+    VPP_BATCH_CONFIGS(VPP_BS)
+#undef VPP_BS
+    return false;
 }
 
 int list_batch_configs(int k, LaunchCfg* out, int cap)
@@ -441,21 +375,6 @@ int list_batch_configs(int k, LaunchCfg* out, int cap)
     VPP_BATCH_CONFIGS(VPP_BLIST)
 #undef VPP_BLIST
     return n;
-}
-
-int batch_blocks_per_cu(const LaunchCfg& c, int k)
-{
-    int nb = 0;
-#define VPP_BO(K, TX, TY, TZ)                                                                      \
-    if (k == K && c.variant == 4 && c.tile[0] == TX && c.tile[1] == TY && c.tile[2] == TZ) {      \
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch_apply_kernel<K, TX, TY, TZ, 0, 0>,\
-                                                         TX * TY * TZ, 0) != hipSuccess)          \
-            return 0;                                                                              \
-        return nb;                                                                                 \
-    }
-    VPP_BATCH_CONFIGS(VPP_BO)
-#undef VPP_BO
-    return 0;
 }
 
 unsigned long long bounds_count_misc() { return bc_count_here(); }

@@ -131,8 +131,7 @@ struct PlaneThread {
     bool spare;          // repeats the group's last thread: writes nothing out
     int offx, offz;      // its planes in the workgroup's buffer
 
-    __device__ __forceinline__ explicit PlaneThread(const MeshArgs& m)
-        : tc(tile_coord<K, TX, TY, TZ>(m, xcd_tile(blockIdx.x, gridDim.x)))
+    __device__ __forceinline__ PlaneThread(const MeshArgs& m, int tile) : tc(tile_coord<K, TX, TY, TZ>(m, tile))
     {
         const int tid = threadIdx.x;
         const int group = G::WAVE ? tid / 64 : 0;
@@ -405,17 +404,14 @@ __device__ __forceinline__ void plane_operator(const MeshArgs& m, T* px, T* pz, 
     for (int q = 0; q < N2; ++q) u[q] = v[q];
 }
 
-template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS = false>
-__global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) apply_plane_kernel(ApplyArgs<T> a)
+// Body of a workgroup on one tile; dot_out: its partial of x . (A x).
+template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS>
+__device__ __forceinline__ void plane_tile(const ApplyArgs<T>& a, int tile, T* buf, double* dot_out)
 {
     using G = PlaneGeo<K, TX, TY, TZ>;
     constexpr int N = G::N, N2 = N * N;
-    __shared__ T buf[G::NG * G::GB];
-    VPP_BC_BEGIN(a.x, a.y, a.phi, a.part, a.dot_part, buf, (int64_t)a.m.nn[0] * a.m.nn[1] * a.m.nn[2],
-                 8 * a.nshared, (int64_t)gridDim.x, G::NG * G::GB);
-    if (a.done && *a.done) return;
     const MeshArgs& m = a.m;
-    const PlaneThread<K, TX, TY, TZ> th(m);
+    const PlaneThread<K, TX, TY, TZ> th(m, tile);
     const int ip = th.ip;
     const bool in = th.in;
     T* const px = buf + th.offx;
@@ -463,8 +459,19 @@ __global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) apply_plane_ke
     const double d = flush_plane<K, T, TX, TY, TZ>(m, th, buf, u, a.x, a.y, a.part, a.nshared, DOT);
     if constexpr (DOT) {
         const double s = block_sum<G::NTH>(d);
-        if (threadIdx.x == 0) VPP_ST(&a.dot_part[blockIdx.x], BC_DOT, s);
+        if (threadIdx.x == 0) VPP_ST(dot_out, BC_DOT, s);
     }
+}
+
+template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS = false>
+__global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) apply_plane_kernel(ApplyArgs<T> a)
+{
+    using G = PlaneGeo<K, TX, TY, TZ>;
+    __shared__ T buf[G::NG * G::GB];
+    VPP_BC_BEGIN(a.x, a.y, a.phi, a.part, a.dot_part, buf, (int64_t)a.m.nn[0] * a.m.nn[1] * a.m.nn[2],
+                 8 * a.nshared, (int64_t)gridDim.x, G::NG * G::GB);
+    if (a.done && *a.done) return;
+    plane_tile<K, T, TX, TY, TZ, HV, DOT, MASS>(a, xcd_tile(blockIdx.x, gridDim.x), buf, a.dot_part + blockIdx.x);
 }
 
 }  // namespace vpp

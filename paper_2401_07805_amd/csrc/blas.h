@@ -81,10 +81,8 @@ struct CgSystem {
 int cg_update_blocks(int64_t n, int packets);
 // The update and the search-direction update of every system of the device
 // table sys as two launches of total_blocks workgroups (owner[b]: system of
-// workgroup b); the first also resets the batched apply's work counter *queue
-// (if not null).
-hipError_t launch_cg_batch_step(const CgSystem<double>* sys, const int* owner, int total_blocks, int par, int* queue,
-                                hipStream_t s);
+// workgroup b).
+hipError_t launch_cg_batch_step(const CgSystem<double>* sys, const int* owner, int total_blocks, int par, hipStream_t s);
 
 // r = b - q in FP64 (r may be null) and *rr = r.r.
 // Deflation space of the mixed-precision solver: W[t] = D^-1 sum_j C[j k + t]

@@ -248,11 +248,8 @@ __global__ void __launch_bounds__(BT) cg_pupdate_kernel(CgState* st, int par, co
 // nblk) of the grid (cg_update_blocks); owner[] gives the system of each.
 
 template <typename T>
-__global__ void __launch_bounds__(BT) cg_batch_update_kernel(const CgSystem<T>* sys, const int* owner, int par,
-                                                             int* queue)
+__global__ void __launch_bounds__(BT) cg_batch_update_kernel(const CgSystem<T>* sys, const int* owner, int par)
 {
-    // the batched apply that precedes this launch pulls work items from queue
-    if (queue && blockIdx.x == 0 && threadIdx.x == 0) *queue = 0;
     const CgSystem<T>& y = sys[owner[blockIdx.x]];
     const SharedParts<T> sp{y.map, y.part, y.stride, y.dot_part, y.ndot};
     assemble_update_body<T>((int)blockIdx.x - y.blk_begin, y.nblk, y.st, par, y.red, sp, y.r, y.q, y.invd, y.n);
@@ -379,10 +376,9 @@ int cg_update_blocks(int64_t n, int packets)
     return (int)std::min<int64_t>(kMaxRedBlocks, std::max<int64_t>(1, (n + per - 1) / per));
 }
 
-hipError_t launch_cg_batch_step(const CgSystem<double>* sys, const int* owner, int total_blocks, int par, int* queue,
-                                hipStream_t s)
+hipError_t launch_cg_batch_step(const CgSystem<double>* sys, const int* owner, int total_blocks, int par, hipStream_t s)
 {
-    hipLaunchKernelGGL(cg_batch_update_kernel<double>, dim3(total_blocks), dim3(BT), 0, s, sys, owner, par, queue);
+    hipLaunchKernelGGL(cg_batch_update_kernel<double>, dim3(total_blocks), dim3(BT), 0, s, sys, owner, par);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(cg_batch_pupdate_kernel<double>, dim3(total_blocks), dim3(BT), 0, s, sys, owner, par);

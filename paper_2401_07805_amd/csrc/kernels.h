@@ -182,11 +182,10 @@ hipError_t launch_reinit_apply(int k, const ReinitApplyArgs& a, hipStream_t s);
 // cv: cell_values(k, m) doubles of scratch each.
 hipError_t launch_reinit_diag(int k, const ReinitArgs& r, double* diag, double* cv, hipStream_t s);
 hipError_t launch_reinit_rhs(int k, const ReinitArgs& r, const double* psi, double* b, double* cv, hipStream_t s);
-// Batched persistent apply (FP64).
-// Work items of one problem of a batch: a (tile) at degree 2, whose
-// coefficient serves all right-hand sides, a (tile, rhs) at degree 3, the
-// items of one tile consecutive (batch_apply_kernel).
-__host__ __device__ inline int batch_items(int k, int ntiles, int nrhs) { return k == 2 ? ntiles : ntiles * nrhs; }
+// Batched apply (FP64).
+// Work items of one problem of a batch: (tile, rhs) pairs, the items of one tile
+// consecutive (batch_apply_kernel).
+__host__ __device__ inline int batch_items(int ntiles, int nrhs) { return ntiles * nrhs; }
 
 struct BatchProblem {
     MeshArgs m;
@@ -208,7 +207,8 @@ struct BatchArgs {
     const double* const* x;
     double* const* y;
     double* part;        // partial slots of every (problem, rhs)
-    int* queue;          // work counter, zero at launch (reset by the assembly kernel)
+    const int* owner;    // problem of each item
+    int64_t max_shared;  // largest shared-node count of the problems
     int heaviside;       // shared by every problem of the batch
     // batched PCG (st null: plain apply): the (problem, rhs) vectors whose state
     // st[rhs].halt[par] is set are skipped, and every tile writes its partial of
@@ -216,15 +216,14 @@ struct BatchArgs {
     const CgState* st;
     int par;
     double* dot_part;
-    int any_mass = 0;    // some problem has a mass shift (at degree 3 it selects the kernel instantiation)
+    int any_mass = 0;    // some problem has a mass shift (selects the kernel instantiation)
 };
 
-// Persistent tile kernel over all work items, then (unless tiles_only) one
-// assembly launch over all (problem, rhs) vectors, which also resets the work
-// counter; with tiles_only the caller assembles and resets it.
-hipError_t launch_batch_apply(const LaunchCfg& c, int k, const BatchArgs& a, int nblocks, int total_rhs,
-                              bool tiles_only, hipStream_t s);
-int batch_blocks_per_cu(const LaunchCfg& c, int k);
+// Tile kernel over all work items, then (unless tiles_only) one assembly launch
+// over all (problem, rhs) vectors; with tiles_only the caller assembles.
+hipError_t launch_batch_apply(const LaunchCfg& c, int k, const BatchArgs& a, int total_rhs, bool tiles_only,
+                              hipStream_t s);
+bool batch_config_supported(const LaunchCfg& c, int k);
 // Instantiated batch configurations of degree k (writes up to cap, returns the count).
 int list_batch_configs(int k, LaunchCfg* out, int cap);
 

@@ -51,7 +51,7 @@ __global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) reinit_plane_k
     __shared__ double buf[G::NG * G::GB];
     if (a.done && *a.done) return;
     const MeshArgs& m = a.r.g.m;
-    const PlaneThread<K, TX, TY, TZ> th(m);
+    const PlaneThread<K, TX, TY, TZ> th(m, xcd_tile(blockIdx.x, gridDim.x));
     double* const px = buf + th.offx;
     double* const pz = buf + th.offz;
     th.template clear_zero_columns<double>(buf);
