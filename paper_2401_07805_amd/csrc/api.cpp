@@ -1365,7 +1365,7 @@ static vpp_status closest_points(vpp_problem p, const double* pts, int64_t n, co
     vpp_status st;
     if (!p->cp_ctr && (st = dev_alloc(&p->cp_ctr, 2, "closest-point counters"))) return st;
     if (!pts && !p->cp_list && (st = dev_alloc(&p->cp_list, (size_t)p->N, "closest-point band list"))) return st;
-    VPP_HIP(launch_closest_points(p->k, a, p->cp_list, p->cp_ctr, closest_point_blocks(p->k), (hipStream_t)stream));
+    VPP_HIP(launch_closest_points(p->k, a, p->cp_list, p->cp_ctr, (hipStream_t)stream));
     return VPP_OK;
 }
 

@@ -77,65 +77,132 @@ __device__ __forceinline__ int64_t locate(const CpArgs& a, const double (&y)[3],
     return node_index(a.m, (int64_t)K * c[0], (int64_t)K * c[1], (int64_t)K * c[2]);
 }
 
-// Value and gradient at y of the nodal field f (phi or any Q_k field of the mesh).
-template <int K>
-__device__ __forceinline__ void eval_field(const CpArgs& a, const double* __restrict__ f, const double (&y)[3],
-                                           double& val, double (&g)[3])
-{
-    constexpr int N = K + 1;
-    double V[3][N], D[3][N];
-    const int64_t nx = a.m.nn[0], nxy = (int64_t)a.m.nn[0] * a.m.nn[1];
-    const double* p = f + locate<K>(a, y, V, D);
-    // (loads left where they are used: this evaluation's time is its
-    // dependent arithmetic, and gathering first only raised its registers)
-    val = 0.0;
-    g[0] = g[1] = g[2] = 0.0;
-#pragma unroll
-    for (int a2 = 0; a2 < N; ++a2)
-#pragma unroll
-        for (int a1 = 0; a1 < N; ++a1)
-#pragma unroll
-            for (int a0 = 0; a0 < N; ++a0) {
-                const double fv = p[a0 + nx * a1 + nxy * a2];
-                val += V[0][a0] * V[1][a1] * V[2][a2] * fv;
-                g[0] += D[0][a0] * V[1][a1] * V[2][a2] * fv;
-                g[1] += V[0][a0] * D[1][a1] * V[2][a2] * fv;
-                g[2] += V[0][a0] * V[1][a1] * D[2][a2] * fv;
-            }
-}
+// The nodal values of the cell a lane evaluates in: of phi, or of phi and the
+// three components of the nodal normal (NF fields).  Each lane asks for cache
+// lines of its own, and with every evaluation gathering its cell the load path
+// was the bound (TA busy 85%, TD 90% of the kernel, about 26 cycles per load;
+// records of the four fields per node, a third of the lines, gained nothing:
+// it is the 64 returned values per instruction that count).  So the values
+// stay in registers while the lane's y stays in the cell (KEEP), across
+// corrections, outer steps and points.  The line lies where they still fit
+// beside the evaluation: 27, 64 (gradient) and 4 x 27 (k = 2 with a normal,
+// 348 registers and one wave per SIMD), not 125 or 4 x 64.  64^3 Q2, 310,000
+// points: 698 -> 303 us with a normal, 1240 -> 740 with the gradient; 32^3 Q3
+// gradient 1960 -> 1300 us (with kRefill below, which alone gave 610, 811 and
+// 1520).
+template <int K, int NF>
+struct CellValues {
+    static constexpr int N = K + 1, N3 = N * N * N;
+    static constexpr bool KEEP = NF * N3 <= 108;   // 216 registers
+    int64_t base = -1;
+    double f[NF][KEEP ? N3 : 1];
 
-// Values at y of phi_h and of the nodal normal field's three components.
+    __device__ __forceinline__ void fetch(const CpArgs& a, int64_t b)
+    {
+        if (!KEEP || b == base) return;
+        base = b;
+        const int64_t nx = a.m.nn[0], nxy = (int64_t)a.m.nn[0] * a.m.nn[1];
+#pragma unroll
+        for (int fi = 0; fi < NF; ++fi) {
+            const double* __restrict__ p = (fi == 0 ? a.phi : a.nrm[fi - 1]) + b;
+#pragma unroll
+            for (int a2 = 0; a2 < N; ++a2)
+#pragma unroll
+                for (int a1 = 0; a1 < N; ++a1)
+#pragma unroll
+                    for (int a0 = 0; a0 < N; ++a0) f[fi][a0 + N * (a1 + N * a2)] = p[a0 + nx * a1 + nxy * a2];
+        }
+    }
+};
+
+// Value and gradient at y of phi_h.
 template <int K>
-__device__ __forceinline__ void eval_phi_normal(const CpArgs& a, const double (&y)[3], double& val,
-                                                double (&nv)[3])
+__device__ __forceinline__ void eval_phi(const CpArgs& a, CellValues<K, 1>& c, const double (&y)[3], double& val,
+                                         double (&g)[3])
 {
     constexpr int N = K + 1;
     double V[3][N], D[3][N];
     const int64_t nx = a.m.nn[0], nxy = (int64_t)a.m.nn[0] * a.m.nn[1];
     const int64_t base = locate<K>(a, y, V, D);
-    // one field at a time, its nodal values loaded before any is used (four
-    // memory latencies per evaluation instead of one per few loads: 950 -> 805
-    // us for the 64^3 band)
-    const double* fields[4] = {a.phi, a.nrm[0], a.nrm[1], a.nrm[2]};
-    double out[4];
+    c.fetch(a, base);
+    const double* p = a.phi + base;
+    val = 0.0;
+    g[0] = g[1] = g[2] = 0.0;
 #pragma unroll
-    for (int fi = 0; fi < 4; ++fi) {
-        const double* __restrict__ f = fields[fi];
-        double fc[N * N * N];
+    for (int a2 = 0; a2 < N; ++a2) {
 #pragma unroll
-        for (int a2 = 0; a2 < N; ++a2)
+        for (int a1 = 0; a1 < N; ++a1)
+#pragma unroll
+            for (int a0 = 0; a0 < N; ++a0) {
+                double fv;
+                if constexpr (CellValues<K, 1>::KEEP) fv = c.f[0][a0 + N * (a1 + N * a2)];
+                else fv = p[a0 + nx * a1 + nxy * a2];
+                val += V[0][a0] * V[1][a1] * V[2][a2] * fv;
+                g[0] += D[0][a0] * V[1][a1] * V[2][a2] * fv;
+                g[1] += V[0][a0] * D[1][a1] * V[2][a2] * fv;
+                g[2] += V[0][a0] * V[1][a1] * D[2][a2] * fv;
+            }
+        // a plane at a time (125 values at once leave no registers: 20^3 Q4 5.6 ms against 4.7)
+        if constexpr (!CellValues<K, 1>::KEEP) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Values at y of phi_h and of the nodal normal field's three components.
+template <int K>
+__device__ __forceinline__ void eval_phi_normal(const CpArgs& a, CellValues<K, 4>& c, const double (&y)[3],
+                                                double& val, double (&nv)[3])
+{
+    constexpr int N = K + 1;
+    double V[3][N], D[3][N];
+    const int64_t nx = a.m.nn[0], nxy = (int64_t)a.m.nn[0] * a.m.nn[1];
+    const int64_t base = locate<K>(a, y, V, D);
+    c.fetch(a, base);
+    double out[4] = {0.0, 0.0, 0.0, 0.0};
+    if constexpr (K < 4) {
+#pragma unroll
+        for (int fi = 0; fi < 4; ++fi) {
+            // not kept: one field at a time, its nodal values loaded before any is
+            // used (four memory latencies per evaluation instead of one per few loads)
+            const double* __restrict__ f = (fi == 0 ? a.phi : a.nrm[fi - 1]) + base;
+            double fc[N * N * N];
+#pragma unroll
+            for (int a2 = 0; a2 < N; ++a2)
+#pragma unroll
+                for (int a1 = 0; a1 < N; ++a1)
+#pragma unroll
+                    for (int a0 = 0; a0 < N; ++a0) {
+                        const int q = a0 + N * (a1 + N * a2);
+                        if constexpr (CellValues<K, 4>::KEEP) fc[q] = c.f[fi][q];
+                        else fc[q] = f[a0 + nx * a1 + nxy * a2];
+                    }
+#pragma unroll
+            for (int a2 = 0; a2 < N; ++a2)
+#pragma unroll
+                for (int a1 = 0; a1 < N; ++a1)
+#pragma unroll
+                    for (int a0 = 0; a0 < N; ++a0)
+                        out[fi] += V[0][a0] * V[1][a1] * V[2][a2] * fc[a0 + N * (a1 + N * a2)];
+        }
+    } else {
+        // planes in a loop, all fields of a node at once: unrolled, 500 values and
+        // their addresses spilled (20^3 Q4: 18.5 ms against 9.3)
+        const double* p[4] = {a.phi + base, a.nrm[0] + base, a.nrm[1] + base, a.nrm[2] + base};
+#pragma unroll 1
+        for (int a2 = 0; a2 < N; ++a2) {
+            double v2 = V[2][0];
+#pragma unroll
+            for (int q = 1; q < N; ++q) v2 = a2 == q ? V[2][q] : v2;
 #pragma unroll
             for (int a1 = 0; a1 < N; ++a1)
 #pragma unroll
-                for (int a0 = 0; a0 < N; ++a0) fc[a0 + N * (a1 + N * a2)] = f[base + a0 + nx * a1 + nxy * a2];
-        double s = 0.0;
+                for (int a0 = 0; a0 < N; ++a0) {
+                    const double w = V[0][a0] * V[1][a1] * v2;
 #pragma unroll
-        for (int a2 = 0; a2 < N; ++a2)
+                    for (int fi = 0; fi < 4; ++fi) out[fi] += w * p[fi][a0 + nx * a1];
+                }
 #pragma unroll
-            for (int a1 = 0; a1 < N; ++a1)
-#pragma unroll
-                for (int a0 = 0; a0 < N; ++a0) s += V[0][a0] * V[1][a1] * V[2][a2] * fc[a0 + N * (a1 + N * a2)];
-        out[fi] = s;
+            for (int fi = 0; fi < 4; ++fi) p[fi] += nxy;
+        }
     }
     val = out[0];
     nv[0] = out[1];
@@ -145,13 +212,15 @@ __device__ __forceinline__ void eval_phi_normal(const CpArgs& a, const double (&
 
 // phi_h(y) and the unit normal at y (the normalised gradient of phi_h, or of
 // the nodal normal field when one is given); false where that vector vanishes.
-template <int K>
-__device__ __forceinline__ bool normal_at(const CpArgs& a, const double (&y)[3], double& val, double (&n)[3])
+template <int K, int NF>
+__device__ __forceinline__ bool normal_at(const CpArgs& a, CellValues<K, NF>& c, const double (&y)[3], double& val,
+                                          double (&n)[3])
 {
     double g[3];
-    if (a.nrm[0]) eval_phi_normal<K>(a, y, val, g);
-    else eval_field<K>(a, a.phi, y, val, g);
-    const double gn = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
+    if constexpr (NF == 4) eval_phi_normal<K>(a, c, y, val, g);
+    else eval_phi<K>(a, c, y, val, g);
+    // (the order spelled out, so that the kernel variants round alike)
+    const double gn = sqrt(fma(g[2], g[2], fma(g[0], g[0], g[1] * g[1])));
     if (!(gn > 0.0)) return false;
 #pragma unroll
     for (int d = 0; d < 3; ++d) n[d] = g[d] / gn;
@@ -184,13 +253,13 @@ __device__ __forceinline__ void node_coords(const CpArgs& a, int64_t i, double (
 
 // One outer step from y towards the closest point of x; true once the step
 // moved y by less than tol.
-template <int K>
-__device__ __forceinline__ bool outer_step(const CpArgs& a, const double (&x)[3], double (&y)[3])
+template <int K, int NF>
+__device__ __forceinline__ bool outer_step(const CpArgs& a, CellValues<K, NF>& c, const double (&x)[3], double (&y)[3])
 {
     const double prev[3] = {y[0], y[1], y[2]};
     double val, n[3];
     for (int s = 0; s < a.normal_steps; ++s) {
-        if (normal_at<K>(a, y, val, n)) {
+        if (normal_at<K>(a, c, y, val, n)) {
             const double pc = fmin(fmax(val, -kPhiClip), kPhiClip);
             const double dist = a.eps * log((1.0 + pc) / (1.0 - pc));
 #pragma unroll
@@ -198,7 +267,7 @@ __device__ __forceinline__ bool outer_step(const CpArgs& a, const double (&x)[3]
             clip_box(a, y);
         }
     }
-    if (normal_at<K>(a, y, val, n)) {
+    if (normal_at<K>(a, c, y, val, n)) {
         const bool use_y = fabs(n[0]) > 0.9;
         const double v[3] = {use_y ? 0.0 : 1.0, use_y ? 1.0 : 0.0, 0.0};
         const double vn = v[0] * n[0] + v[1] * n[1] + v[2] * n[2];
@@ -265,12 +334,17 @@ __global__ void __launch_bounds__(kListThreads) band_list_kernel(CpArgs a, int* 
 }
 
 // Persistent projection over a queue of points (the band list, or the caller's
-// points 0..n-1): a lane whose point has converged or used max_iter outer steps
-// writes it and takes the next one (one atomic per wave and refill), so a
-// point that needs many steps does not hold its wave's other lanes idle.
+// points 0..n-1): lanes whose points have converged or used max_iter outer steps
+// take the next ones, so a point that needs many steps does not hold its wave's
+// other lanes idle.  A wave fetches (one atomic) once kRefill of its lanes are
+// idle: neighbours in the queue are neighbours in space, and lanes refilled
+// singly drift apart until no two share a cell or a cache line (64^3 Q2 with a
+// normal 513 us at 1, 304 at 16, 316 at 32; 32^3 Q3 2050, 1650, 1615).
 // Every lane leaves once the queue is empty and its point is done; each point
 // takes at most max_iter steps, so every wave finishes.
-template <int K>
+constexpr int kRefill = 16;
+
+template <int K, int NF>
 __global__ void __launch_bounds__(256) closest_point_queue_kernel(CpArgs a, const int* __restrict__ list,
                                                                   const int* __restrict__ count,
                                                                   int* __restrict__ next)
@@ -280,9 +354,10 @@ __global__ void __launch_bounds__(256) closest_point_queue_kernel(CpArgs a, cons
     int64_t g = 0;
     int it = 0;
     double x[3] = {0.0, 0.0, 0.0}, y[3] = {0.0, 0.0, 0.0};
+    CellValues<K, NF> c;
     for (;;) {
         const unsigned long long need = __ballot(live && !have);
-        if (need) {
+        if (need && (__popcll(need) >= kRefill || !__ballot(have))) {
             const int leader = __ffsll((long long)need) - 1;
             int base = 0;
             if (__lane_id() == leader) base = atomicAdd(next, __popcll(need));
@@ -310,7 +385,7 @@ __global__ void __launch_bounds__(256) closest_point_queue_kernel(CpArgs a, cons
         if (!__ballot(have)) break;   // queue empty and every point written
         if (have) {
             ++it;
-            const bool conv = outer_step<K>(a, x, y);
+            const bool conv = outer_step<K>(a, c, x, y);
             if (conv || it >= a.max_iter) {
 #pragma unroll
                 for (int d = 0; d < 3; ++d) a.y[3 * g + d] = y[d];
@@ -334,8 +409,17 @@ __global__ void __launch_bounds__(256) extend_kernel(CpArgs a, const double* __r
         return;
     }
     const double y[3] = {a.y[3 * i], a.y[3 * i + 1], a.y[3 * i + 2]};
-    double val, g[3];
-    eval_field<K>(a, f, y, val, g);
+    constexpr int N = K + 1;
+    double V[3][N], D[3][N];
+    const int64_t nx = a.m.nn[0], nxy = (int64_t)a.m.nn[0] * a.m.nn[1];
+    const double* p = f + locate<K>(a, y, V, D);
+    double val = 0.0;
+#pragma unroll
+    for (int a2 = 0; a2 < N; ++a2)
+#pragma unroll
+        for (int a1 = 0; a1 < N; ++a1)
+#pragma unroll
+            for (int a0 = 0; a0 < N; ++a0) val += V[0][a0] * V[1][a1] * V[2][a2] * p[a0 + nx * a1 + nxy * a2];
     out[i] = val;
 }
 
@@ -355,45 +439,35 @@ hipError_t launch_extend(int k, const CpArgs& a, const double* f, double* out, h
     return hipGetLastError();
 }
 
-hipError_t launch_closest_points(int k, const CpArgs& a, int* list, int* ctr, int nblocks, hipStream_t s)
+// One persistent workgroup per CU, a wave per SIMD: what the registers allow at
+// k = 2 with a normal, and no worse elsewhere (64^3 Q2 gradient 748 us against
+// 790 with two, 32^3 Q3 1303 and 1664 against 1289 and 1650).
+template <int K>
+static hipError_t launch_k(const CpArgs& a, int* list, int* ctr, hipStream_t s)
+{
+    if (!a.pts) {
+        const unsigned blocks = (unsigned)((a.n + kListThreads - 1) / kListThreads);
+        hipLaunchKernelGGL(band_list_kernel<K>, dim3(blocks), dim3(kListThreads), 0, s, a, list, ctr);
+    }
+    const dim3 grid(device_cu_count()), nt(256);
+    if (a.nrm[0])
+        hipLaunchKernelGGL((closest_point_queue_kernel<K, 4>), grid, nt, 0, s, a, list, ctr, ctr + 1);
+    else
+        hipLaunchKernelGGL((closest_point_queue_kernel<K, 1>), grid, nt, 0, s, a, list, ctr, ctr + 1);
+    return hipGetLastError();
+}
+
+hipError_t launch_closest_points(int k, const CpArgs& a, int* list, int* ctr, hipStream_t s)
 {
     if (a.n <= 0) return hipSuccess;
     hipError_t e = launch_fill<int>(ctr, 2, 0, s);   // ctr[0]: band count, ctr[1]: queue head
     if (e != hipSuccess) return e;
-    const int64_t blocks = (a.n + kListThreads - 1) / kListThreads;
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
-#define VPP_CP(K)                                                                                          \
-    if (!a.pts)                                                                                             \
-        hipLaunchKernelGGL(band_list_kernel<K>, dim3((unsigned)blocks), dim3(kListThreads), 0, s, a, list, ctr); \
-    hipLaunchKernelGGL(closest_point_queue_kernel<K>, dim3(nblocks), dim3(256), 0, s, a, list, ctr, ctr + 1);
     switch (k) {
-    case 2: VPP_CP(2) break;
-    case 3: VPP_CP(3) break;
-    case 4: VPP_CP(4) break;
+    case 2: return launch_k<2>(a, list, ctr, s);
+    case 3: return launch_k<3>(a, list, ctr, s);
+    case 4: return launch_k<4>(a, list, ctr, s);
     default: return hipErrorInvalidValue;
     }
-#undef VPP_CP
-    return hipGetLastError();
-}
-
-// Persistent workgroups of the projection: two per CU (two waves per SIMD), so
-// that the lanes are fewer than the points of a typical band and refill from
-// the queue, while the loads of one wave still overlap the other's arithmetic.
-constexpr int kCpBlocksPerCu = 2;
-
-int closest_point_blocks(int k)
-{
-    int per_cu = 0;
-    hipError_t e = hipErrorInvalidValue;
-    switch (k) {
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, closest_point_queue_kernel<2>, 256, 0); break;
-    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, closest_point_queue_kernel<3>, 256, 0); break;
-    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, closest_point_queue_kernel<4>, 256, 0); break;
-    default: break;
-    }
-    if (e != hipSuccess || per_cu < 1) per_cu = 1;
-    if (per_cu > kCpBlocksPerCu) per_cu = kCpBlocksPerCu;
-    return per_cu * device_cu_count();
 }
 
 }  // namespace vpp
