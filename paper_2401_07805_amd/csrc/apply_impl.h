@@ -105,10 +105,14 @@ __device__ __forceinline__ void gather_cell_t(const S* __restrict__ tb, unsigned
 #pragma unroll
     for (int a2 = 0; a2 < N; ++a2)
 #pragma unroll
-        for (int a1 = 0; a1 < N; ++a1)
+        for (int a1 = 0; a1 < N; ++a1) {
+            // one address per row: its values are adjacent in memory to the compiler
+            // too and come as 16-byte loads (k = 2: 36 loads instead of 54 for x and
+            // phi; 64^3 Q2 apply 29.4 -> 28.7 us, FP32 29.7 -> 27.7 with cold caches)
+            const S* row = at_byte(tb + (nx * a1 + nxy * a2), lane_b);
 #pragma unroll
-            for (int a0 = 0; a0 < N; ++a0)
-                u[a0 + N * (a1 + N * a2)] = T(VPP_LD(at_byte(tb + (a0 + nx * a1 + nxy * a2), lane_b), BC_IN));
+            for (int a0 = 0; a0 < N; ++a0) u[a0 + N * (a1 + N * a2)] = T(VPP_LD(&row[a0], BC_IN));
+        }
     if (faces) {
 #pragma unroll
         for (int a2 = 0; a2 < N; ++a2)
@@ -715,10 +719,11 @@ __device__ __forceinline__ double flush_two_pass(const MeshArgs& m, const TileCo
 #pragma unroll
             for (int a2 = 0; a2 < K; ++a2)
 #pragma unroll
-                for (int a1 = 0; a1 < K; ++a1)
+                for (int a1 = 0; a1 < K; ++a1) {
+                    const T* row = at_byte(xt + (nx * a1 + nxy * a2), lane_b);
 #pragma unroll
-                    for (int a0 = 0; a0 < K; ++a0)
-                        xd[a0 + K * (a1 + K * a2)] = VPP_LD(at_byte(xt + (a0 + nx * a1 + nxy * a2), lane_b), BC_X);
+                    for (int a0 = 0; a0 < K; ++a0) xd[a0 + K * (a1 + K * a2)] = VPP_LD(&row[a0], BC_X);
+                }
         }
 #pragma unroll
         for (int a2 = 0; a2 < K; ++a2)
@@ -927,10 +932,11 @@ __device__ __forceinline__ double flush_half_owned(const MeshArgs& m, const Tile
         for (int j = 0; j < 2; ++j) {
             if (pl[j] >= K) continue;
 #pragma unroll
-            for (int a1 = 0; a1 < K; ++a1)
+            for (int a1 = 0; a1 < K; ++a1) {
+                const T* row = at_byte(xt + (nx * a1 + nxy * pl[j]), lane_b);
 #pragma unroll
-                for (int a0 = 0; a0 < K; ++a0)
-                    xd[j][a0 + K * a1] = VPP_LD(at_byte(xt + (a0 + nx * a1 + nxy * pl[j]), lane_b), BC_X);
+                for (int a0 = 0; a0 < K; ++a0) xd[j][a0 + K * a1] = VPP_LD(&row[a0], BC_X);
+            }
         }
     }
 #pragma unroll
@@ -1003,12 +1009,15 @@ __global__ void __launch_bounds__(2 * TX * TY * TZ) apply_half_kernel(ApplyArgs<
             const unsigned lane_b =
                 (unsigned)(K * lx + nx * K * ly + nxy * (K * lz + pl[j])) * (unsigned)sizeof(T);
 #pragma unroll
-            for (int a1 = 0; a1 < N; ++a1)
+            for (int a1 = 0; a1 < N; ++a1) {
+                const T* prow = at_byte(a.phi + tile0 + nx * a1, lane_b);
+                const T* xrow = at_byte(a.x + tile0 + nx * a1, lane_b);
 #pragma unroll
                 for (int a0 = 0; a0 < N; ++a0) {
-                    cw[j][a0 + N * a1] = VPP_LD(at_byte(a.phi + tile0 + (a0 + nx * a1), lane_b), BC_PHI);
-                    u[j][a0 + N * a1] = VPP_LD(at_byte(a.x + tile0 + (a0 + nx * a1), lane_b), BC_X);
+                    cw[j][a0 + N * a1] = VPP_LD(&prow[a0], BC_PHI);
+                    u[j][a0 + N * a1] = VPP_LD(&xrow[a0], BC_X);
                 }
+            }
         }
         // Dirichlet entries zeroed after every load has been issued (zeroing
         // inside the load loop made each group of loads wait for the last)
