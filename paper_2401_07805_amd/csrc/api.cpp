@@ -94,6 +94,19 @@ LaunchCfg default_config(int k, int prec, int64_t ncell)
     return f32 ? LaunchCfg{1, {6, 4, 2}} : LaunchCfg{1, {4, 4, 3}};
 }
 
+// The same with the mass shift, where the configuration in use has no kernel with
+// it.  PCG iteration, us: k = 2, 16^3 cells 16.9 with 8x4x4 against 18.9 with
+// 16x8x4, 32^3 20.7 against 23.1, 40^3 27.5 against 27.1, 48^3 33.6 against 31.5;
+// k = 3, 4x4x4 at every size (8^3 19.2 against 21.8 with 8x4x4, 24^3 25.0 against
+// 27.8, 48^3 83.4 against 86.5, 64^3 202 against 200).  k = 4 as without: its tiles
+// have both kernels (32^3: 4x4x3 65.6 against 71.8 with 4x3x2).
+LaunchCfg mass_default_config(int k, int prec, int64_t ncell)
+{
+    if (k == 2) return ncell <= 40000 ? LaunchCfg{4, {8, 4, 4}} : LaunchCfg{4, {16, 8, 4}};
+    if (k == 3) return LaunchCfg{4, {4, 4, 4}};
+    return default_config(k, prec, ncell);
+}
+
 template <typename T>
 vpp_status dev_alloc(T** p, size_t n, const char* what)
 {
@@ -1183,9 +1196,6 @@ vpp_status vpp_set_mass(vpp_problem p, double mu, void* stream)
     if (!(mu >= 0.0) || !std::isfinite(mu)) return fail(VPP_ERR_INVALID_ARG, "the mass shift must be finite and >= 0");
     if (mu != 0.0 && arith_law(p->desc))
         return fail(VPP_ERR_UNSUPPORTED, "the mass shift is not available with the arithmetic density mean");
-    LaunchCfg mc[16];
-    if (mu != 0.0 && list_mass_configs(p->k, mc, 16) < 1)
-        return fail(VPP_ERR_UNSUPPORTED, "no kernel configuration with the mass shift for this degree");
     DeviceGuard dg(p->desc.device);
     VPP_HIP(hipStreamSynchronize((hipStream_t)stream));
     if (p->stream) VPP_HIP(hipStreamSynchronize(p->stream));
@@ -1193,8 +1203,10 @@ vpp_status vpp_set_mass(vpp_problem p, double mu, void* stream)
     for (int d = 0; d < 3; ++d) vol *= p->desc.extent[d] / p->desc.ncells[d];
     p->m.mass = p->m32.mass = mu * vol;
     if (mu != 0.0) {
-        if (!mass_config_supported(p->cfg, p->k)) put_config(p, VPP_FP64, mc[0]);
-        if (!mass_config_supported(p->cfg32, p->k)) put_config(p, VPP_FP32, mc[0]);
+        if (!mass_config_supported(p->cfg, p->k))
+            put_config(p, VPP_FP64, mass_default_config(p->k, VPP_FP64, p->ncell));
+        if (!mass_config_supported(p->cfg32, p->k))
+            put_config(p, VPP_FP32, mass_default_config(p->k, VPP_FP32, p->ncell));
     }
     free_graphs(p->w);   // they hold the operator's arguments by value
     vpp_status st = ensure_apply_scratch(p);

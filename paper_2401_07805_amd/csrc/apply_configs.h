@@ -4,7 +4,10 @@
 
 namespace vpp {
 
-// Instantiated configurations: (k, variant, tile).
+// Instantiated configurations: (k, variant, tile).  At k = 3 variant 4 runs the
+// plane-per-thread kernel on its tiles: one cell per thread is 64 values of
+// operand, coefficient and result each, which spilled (mass-shifted PCG
+// iteration, 8x4x4: 24^3 32.6 us against 27.8, 43^3 82.3 against 68.3).
 #define VPP_APPLY_CONFIGS(X)  \
     X(2, 4, 8, 8, 8)          \
     X(2, 4, 32, 4, 4)         \
@@ -33,15 +36,19 @@ namespace vpp {
     X(4, 1, 6, 4, 2)
 
 // Configurations also instantiated with the mass shift mu M of the level-set
-// filter operators (variant 4: the mass term sits in cell_operator; variant 1:
-// in the plane kernel's Gauss-point step).
+// filter operators (the mass term sits in cell_operator at k = 2, in the plane
+// kernel's Gauss-point step at k = 3 and 4); mass_default_config picks one.
 #define VPP_MASS_CONFIGS(X) \
     X(2, 4, 16, 8, 4)       \
     X(2, 4, 32, 4, 4)       \
     X(2, 4, 8, 4, 4)        \
     X(3, 4, 8, 4, 4)        \
+    X(3, 4, 4, 4, 4)        \
     X(4, 1, 4, 2, 2)        \
-    X(4, 1, 2, 2, 2)
+    X(4, 1, 2, 2, 2)        \
+    X(4, 1, 4, 3, 2)        \
+    X(4, 1, 4, 4, 3)        \
+    X(4, 1, 6, 4, 2)
 
 // Configurations also instantiated with the arithmetic density mean (laws 2
 // and 3 of coef_scaled; the contrast of App. D): one per degree, the default
@@ -51,12 +58,18 @@ namespace vpp {
     X(3, 1, 4, 4, 2)         \
     X(4, 1, 4, 2, 2)
 
+template <int K, int V>
+constexpr bool plane_per_thread()
+{
+    return V == 1 || (V == 4 && K == 3);
+}
+
 template <int K, typename T, int V, int TX, int TY, int TZ, int HV, bool DOT, bool MASS>
 inline auto kernel_ptr()
 {
     static_assert(!MASS || V == 4 || V == 1, "the mass shift is instantiated for variants 1 and 4");
-    if constexpr (V == 0) return &apply_cell_kernel<K, T, TX, TY, TZ, HV, DOT>;
-    else if constexpr (V == 1) return &apply_plane_kernel<K, T, TX, TY, TZ, HV, DOT, MASS>;
+    if constexpr (plane_per_thread<K, V>()) return &apply_plane_kernel<K, T, TX, TY, TZ, HV, DOT, MASS>;
+    else if constexpr (V == 0) return &apply_cell_kernel<K, T, TX, TY, TZ, HV, DOT>;
     else if constexpr (V == 2) return &apply_half_kernel<K, T, TX, TY, TZ, HV, DOT>;
     else return &apply_slot_kernel<K, T, TX, TY, TZ, HV, DOT, MASS>;
 }
@@ -65,7 +78,7 @@ template <int K, typename T, int V, int TX, int TY, int TZ, int HV, bool DOT, bo
 inline hipError_t launch_hv(const ApplyArgs<T>& a, hipStream_t s)
 {
     const int nblocks = a.m.ntile[0] * a.m.ntile[1] * a.m.ntile[2];
-    constexpr int threads = V == 1 ? PlaneGeo<K, TX, TY, TZ>::NTH : (V == 2 ? 2 : 1) * TX * TY * TZ;
+    constexpr int threads = plane_per_thread<K, V>() ? PlaneGeo<K, TX, TY, TZ>::NTH : (V == 2 ? 2 : 1) * TX * TY * TZ;
     hipLaunchKernelGGL((kernel_ptr<K, T, V, TX, TY, TZ, HV, DOT, MASS>()), dim3(nblocks), dim3(threads), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.tiles_only) return e;

@@ -463,8 +463,11 @@ __device__ __forceinline__ void plane_tile(const ApplyArgs<T>& a, int tile, T* b
     }
 }
 
+// The bound of 128 registers: with the mass term the FP64 kernel took 130 at k = 3
+// and lost its fourth wave per SIMD (PCG iteration at 48^3 87.9 -> 83.4 us).
 template <int K, typename T, int TX, int TY, int TZ, int HV, bool DOT, bool MASS = false>
-__global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) apply_plane_kernel(ApplyArgs<T> a)
+__global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH), (K == 3 && MASS && sizeof(T) == 8 ? 4 : 1))
+    apply_plane_kernel(ApplyArgs<T> a)
 {
     using G = PlaneGeo<K, TX, TY, TZ>;
     __shared__ T buf[G::NG * G::GB];

@@ -82,3 +82,29 @@ def test_default_configuration_rule(k, ncells):
     p.set_config(other[0]["variant"], other[0]["tile"])
     ref = host(p.apply(x))
     assert rel(y, ref) < 1e-12 and rel(y32, ref) < 2e-6
+
+
+@pytest.mark.parametrize("k,ncells", [(2, (34, 34, 34)), (2, (35, 35, 33)), (3, (21, 14, 9)),
+                                      (4, (20, 20, 20)), (4, (21, 20, 20))])
+def test_default_configuration_with_the_mass_shift(k, ncells):
+    """The configuration chosen by mesh size once the mass shift is set, on both
+    sides of the line, against every other one with the shift (1e-12: FP64
+    rounding of sums of at most 8 (k+1)^3 terms, with room)."""
+    m = W.Mesh(ncells=ncells, degree=k, bc=(1,) * 6, rho_l=1000.0, rho_g=1.0, mass=1.5)
+    m.eps = 0.1
+    prob = vpp.Problem.from_mesh(m)
+    prob.set_phi(dev(W.droplet_phi(m, 0.3, m.eps, centre=(0.45, 0.5, 0.55))))
+    prob.set_mass(1.5)
+    x = dev(W.uniform_vectors(5, 1, m.ndofs)[0])
+    y, y32 = prob.apply(x), prob.apply(x.float())
+    count = 0
+    for cfg in vpp.config_candidates(k):
+        try:
+            prob.set_config(cfg["variant"], cfg["tile"])
+        except vpp.VppError:
+            continue
+        count += 1
+        z, z32 = prob.apply(x), prob.apply(x.float())
+        assert float((z - y).norm() / y.norm()) < 1e-12, cfg
+        assert float((z32 - y32).norm() / y32.norm()) < 2e-6, cfg
+    assert count >= 2
