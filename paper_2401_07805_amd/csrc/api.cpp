@@ -97,13 +97,13 @@ LaunchCfg default_config(int k, int prec, int64_t ncell)
 // The same with the mass shift, where the configuration in use has no kernel with
 // it.  PCG iteration, us: k = 2, 16^3 cells 16.9 with 8x4x4 against 18.9 with
 // 16x8x4, 32^3 20.7 against 23.1, 40^3 27.5 against 27.1, 48^3 33.6 against 31.5;
-// k = 3, 4x4x4 at every size (8^3 19.2 against 21.8 with 8x4x4, 24^3 25.0 against
+// k = 3, 4x4x4 until 64^3 cells (8^3 19.2 against 21.8 with 8x4x4, 24^3 25.0 against
 // 27.8, 48^3 83.4 against 86.5, 64^3 202 against 200).  k = 4 as without: its tiles
 // have both kernels (32^3: 4x4x3 65.6 against 71.8 with 4x3x2).
 LaunchCfg mass_default_config(int k, int prec, int64_t ncell)
 {
     if (k == 2) return ncell <= 40000 ? LaunchCfg{4, {8, 4, 4}} : LaunchCfg{4, {16, 8, 4}};
-    if (k == 3) return LaunchCfg{4, {4, 4, 4}};
+    if (k == 3) return ncell <= 200000 ? LaunchCfg{4, {4, 4, 4}} : LaunchCfg{4, {8, 4, 4}};
     return default_config(k, prec, ncell);
 }
 
@@ -1515,7 +1515,8 @@ static ReinitArgs reinit_geometry(vpp_problem p, const double* n0, const double*
 static size_t reinit_scratch(const MeshArgs& m) { return 8 * (size_t)shared_stride(m) + (size_t)tile_count(m); }
 
 // The kernels index the partials with 32 bits (as ensure_apply_scratch checks
-// for the apply); a mesh past that has outgrown the memory for the step's vectors.
+// for the apply); reinit_config's tiles keep every mesh below it that vpp_create takes
+// with its default configuration.
 static vpp_status reinit_tiles_ok(const MeshArgs& m)
 {
     if (8 * shared_stride(m) < (int64_t(1) << 32)) return VPP_OK;
@@ -2554,7 +2555,7 @@ static vpp_status batch_tune(vpp_batch b, const char* cache_path)
 // Batched FP64 PCG.  A system (one (problem, rhs) pair) whose mesh has at
 // least kLockstepMaxDofs unknowns fills the GPU on its own and is solved with
 // the single-problem solver and its tuned kernels.  All other systems advance
-// in lockstep, one iteration being the persistent batched apply (tile kernel
+// in lockstep, one iteration being the batched apply (tile kernel
 // with per-tile p.Ap partials) and the batched update and search-direction
 // update; a system that has stopped is skipped by all three.  Each lockstep
 // system's reductions have the workgroup count and summation order of a single

@@ -192,10 +192,16 @@ hipError_t launch_reinit_tiles(const ReinitApplyArgs& a, hipStream_t s)
 // another often and other workgroups fill in (64^3 Q2, whole step: 8x4x2 14.0
 // ms, 8x4x4 16.3, 8x8x4 16.0; 20x17x15 Q3: 4x4x2 5.4, 4x4x4 5.8, 8x4x4 6.5;
 // 24x25x23 Q4: 4x3x2 19.2, 4x4x3 19.6).  At k = 3 a large mesh takes 4x4x4 for
-// its fewer shared nodes.
+// its fewer shared nodes.  At k = 2 a mesh whose partials' indices would pass 32
+// bits with 8x4x2 (above 10^9 nodes) takes 8x8x4, the pressure operator's tile.
 LaunchCfg reinit_config(int k, const MeshArgs& m)
 {
-    if (k == 2) return LaunchCfg{1, {8, 4, 2}};
+    if (k == 2) {
+        MeshArgs t = m;
+        const LaunchCfg c{1, {8, 4, 2}};
+        for (int d = 0; d < 3; ++d) t.ntile[d] = (m.nc[d] + c.tile[d] - 1) / c.tile[d];
+        return 8 * shared_stride(t) < (int64_t(1) << 32) ? c : LaunchCfg{1, {8, 8, 4}};
+    }
     if (k == 4) return LaunchCfg{1, {4, 3, 2}};
     return (int64_t)m.nc[0] * m.nc[1] * m.nc[2] <= 50000 ? LaunchCfg{1, {4, 4, 2}} : LaunchCfg{1, {4, 4, 4}};
 }
@@ -207,7 +213,7 @@ hipError_t launch_reinit_apply(int k, const ReinitApplyArgs& a, hipStream_t s)
     for (int d = 0; d < 3; ++d)
         if (m.ntile[d] != (m.nc[d] + c.tile[d] - 1) / c.tile[d]) return hipErrorInvalidValue;
     hipError_t e;
-    if (k == 2) e = launch_reinit_tiles<2, 8, 4, 2>(a, s);
+    if (k == 2) e = c.tile[2] == 2 ? launch_reinit_tiles<2, 8, 4, 2>(a, s) : launch_reinit_tiles<2, 8, 8, 4>(a, s);
     else if (k == 4) e = launch_reinit_tiles<4, 4, 3, 2>(a, s);
     else if (k != 3) return hipErrorInvalidValue;
     else if (c.tile[2] == 2) e = launch_reinit_tiles<3, 4, 4, 2>(a, s);
