@@ -16,7 +16,7 @@ also carries the rest of the metric: the cold FP32 Q2 apply, the Q3 (43^3)
 FP64 and FP32 applies under the same protocol and its FP64-vs-mixed PCG to
 rtol 1e-8, the same solves on the 64^3 Q2 bubble, the adjoint kernels
 against their algorithmic bytes, the once-refined mesh, the batched workload
-(8 meshes of 16^3..64^3 Q2 with 4 right-hand sides each: one persistent graph
+(8 meshes of 16^3..64^3 Q2 with 4 right-hand sides each: one graph
 launch, and the batched FP64 PCG of its 32 systems) and FP64 vs mixed PCG on
 96^3 Q3 (24.1M DoFs, 20 spheres, ratio 1e4).  After the timed steps the same
 applies are also captured in one HIP graph and replayed (`apply_us_graph`,
@@ -628,7 +628,7 @@ def c2_figures(torch, vpp, W, dev, cache):
 
 def batch_figures(torch, vpp, W, dev, cache, per_mesh=True):
     """The batched workload: 8 independent single-sphere meshes of 16..64 cells per
-    side (Q2, 7.6M DoFs) with 4 right-hand sides each, applied by one persistent
+    side (Q2, 7.6M DoFs) with 4 right-hand sides each, applied by one
     graph launch; aggregate (and with per_mesh, per-mesh) DoF-rhs rates, the
     batched FP64 PCG of its 32 systems, and a Q3 batch (8 meshes of 8..32 cells
     per side, 4 right-hand sides each) against its 32 single applies."""

@@ -305,7 +305,7 @@ def config_candidates(degree: int) -> list:
 
 
 class Batch:
-    """Independent problems applied together by one persistent graph launch."""
+    """Independent problems applied together by one graph launch."""
 
     def __init__(self, problems: Sequence[Problem], nrhs: Sequence[int], tune_cache: Optional[str] = None):
         lib = L.load()
