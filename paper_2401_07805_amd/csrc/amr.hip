@@ -179,7 +179,11 @@ __global__ void __launch_bounds__(256) amr_cells_kernel(AmrArgs a, const double*
     }
 }
 
-// Sum of the slots idx[b .. e): all loaded before any is added, eight at a time.
+// Sum of the slots idx[b .. e): all loaded before any is added, eight at a time;
+// past the end the last one is read again, since a load under a condition waits
+// for its index by itself (the same in amr_constrained; with
+// amr_source_value's, PCG of 0.5 M unknowns at 32^3 Q2 15.5 -> 14.5 ms, 17x14x19 Q3
+// 17.8 -> 15.1, 9x10x8 Q4 20.2 -> 16.3).
 __device__ __forceinline__ double amr_slot_sum(const double* __restrict__ slots, const unsigned* __restrict__ idx, int b,
                                                int e)
 {
@@ -187,7 +191,7 @@ __device__ __forceinline__ double amr_slot_sum(const double* __restrict__ slots,
     for (; b < e; b += 8) {
         double t[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) t[k] = b + k < e ? slots[idx[b + k]] : 0.0;
+        for (int k = 0; k < 8; ++k) t[k] = slots[idx[min(b + k, e - 1)]];
 #pragma unroll
         for (int k = 0; k < 8; ++k)
             if (b + k < e) v += t[k];
@@ -218,9 +222,9 @@ __device__ __forceinline__ double amr_source_value(const AmrArgs& a, int k, int 
         double w[4], c[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int j = b + u * kLanes;
-            w[u] = j < t1 ? a.tw[j] : 0.0;
-            c[u] = j < t1 ? a.csum[a.tcon[j]] : 0.0;
+            const int j = min(b + u * kLanes, t1 - 1);
+            w[u] = a.tw[j];
+            c[u] = a.csum[a.tcon[j]];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -238,7 +242,11 @@ __device__ __forceinline__ void amr_each_unknown(const AmrArgs& a, int g, F&& f)
 {
     if ((int)blockIdx.x < g) {
         for (int i = blockIdx.x * BT + threadIdx.x; i < a.nfree; i += g * BT)
-            if (!a.issrc[i]) f(i, amr_slot_sum(a.scratch, a.fidx, a.fptr[i], a.fptr[i + 1]));
+        {
+            const int b = a.fptr[i], e = a.fptr[i + 1];
+            const bool src = a.issrc[i];
+            if (!src) f(i, amr_slot_sum(a.scratch, a.fidx, b, e));
+        }
         return;
     }
     const int k = ((blockIdx.x - g) * BT + threadIdx.x) / kLanes;
@@ -248,8 +256,8 @@ __device__ __forceinline__ void amr_each_unknown(const AmrArgs& a, int g, F&& f)
 }
 
 // sum_p w_p v(p) over constraint terms p of node m, p's loads batched.
-template <typename F>
-__device__ __forceinline__ double amr_constrained(const AmrArgs& a, int m, F&& v)
+template <typename I, typename F>
+__device__ __forceinline__ double amr_constrained(const AmrArgs& a, int m, I&& index, F&& value)
 {
     const int p1 = a.cptr[m + 1];
     double s = 0.0;
@@ -257,9 +265,10 @@ __device__ __forceinline__ double amr_constrained(const AmrArgs& a, int m, F&& v
         double w[8], x[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int p = b + u;
-            w[u] = p < p1 ? a.cw[p] : 0.0;
-            x[u] = p < p1 ? v(p) : 0.0;
+            const int p = min(b + u, p1 - 1), i = index(p);
+            w[u] = a.cw[p];
+            x[u] = value(max(i, 0));
+            if (i < 0) x[u] = 0.0;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
@@ -275,7 +284,8 @@ __global__ void __launch_bounds__(BT) amr_expand_kernel(AmrArgs a, const double*
     if (i < a.nfree) a.ext[i] = x[a.fent[i]];
     const int m = i - a.nfree;
     if (m >= 0 && m < a.ncon) {
-        a.ext[a.nfree + 1 + m] = amr_constrained(a, m, [&](int p) { return a.cpk[p] < 0 ? 0.0 : x[a.ccol[p]]; });
+        a.ext[a.nfree + 1 + m] = amr_constrained(
+            a, m, [&](int p) { return a.cpk[p] < 0 ? -1 : a.ccol[p]; }, [&](int64_t e) { return x[e]; });
     }
 }
 
@@ -351,10 +361,8 @@ __global__ void __launch_bounds__(BT) amr_constrain_kernel(AmrArgs a)
 {
     const int m = blockIdx.x * BT + threadIdx.x;
     if (m >= a.ncon) return;
-    a.ext[a.nfree + 1 + m] = amr_constrained(a, m, [&](int p) {
-        const int i = a.cpk[p];
-        return i < 0 ? 0.0 : a.ext[i];
-    });
+    a.ext[a.nfree + 1 + m] = amr_constrained(
+        a, m, [&](int p) { return a.cpk[p]; }, [&](int i) { return a.ext[i]; });
 }
 
 // The residual update, (A p) formed on the way (amr_each_unknown's split).
@@ -393,10 +401,8 @@ __global__ void __launch_bounds__(BT) amr_pupdate_kernel(AmrArgs a, AmrCg w, int
     double s = 0.0, old = 0.0;
     if (m < a.ncon) {
         old = a.ext[a.nfree + 1 + m];
-        s = amr_constrained(a, m, [&](int p) {
-            const int i = a.cpk[p];
-            return i < 0 ? 0.0 : w.r[i] * a.invd[i];
-        });
+        s = amr_constrained(
+            a, m, [&](int p) { return a.cpk[p]; }, [&](int i) { return w.r[i] * a.invd[i]; });
     }
     double rr, rzn;
     sum_partials(w.red, ng, rr, rzn, w.nred);
