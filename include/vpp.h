@@ -362,7 +362,10 @@ vpp_status vpp_amr_cg_solve(vpp_amr a, const double* b, double* x, const vpp_cg_
 
 /* Kernel configuration of a problem (what the autotuner chooses), held per
  * precision: the FP64 and the FP32 apply may use different kernels and tiles.
- * Setting an unsupported one returns VPP_ERR_UNSUPPORTED.  vpp_get_config /
+ * Setting an unsupported one returns VPP_ERR_UNSUPPORTED, as does one whose
+ * 32-bit lane offsets do not span the mesh (boxes wider than about 10^8 nodes a
+ * plane: shallower tiles do); new problems never get such a one while their
+ * degree has another.  vpp_get_config /
  * vpp_set_config read the FP64 choice / set both.  vpp_tune times the
  * candidates of both precisions on this problem (synchronises) and keeps the
  * fastest of each; every timed apply follows a write of a 512 MiB scratch

@@ -21,6 +21,7 @@
 #include "amr.h"
 #include "kernels.h"
 #include "noalloc.h"
+#include "tile_rules.h"
 
 using namespace vpp;
 
@@ -68,44 +69,6 @@ struct DeviceGuard {
         if (prev >= 0) (void)hipSetDevice(prev);
     }
 };
-
-// Kernel configuration of a new problem, by degree, precision and number of
-// cells (vpp_tune measures instead).  Measured hot, one apply, us, FP64 / FP32:
-//  k = 2: the plane kernel gives a small mesh three times the waves of the
-//    cell-per-thread one, each with a third of the serial work (24^3 cells: 11.1
-//    against 12.7 / 10.8 against 12.9); a mesh that fills the GPU prefers the
-//    latter's fewer LDS accesses (32^3: 12.9 against 13.1 in FP64 but still 11.1
-//    against 13.0 in FP32; 48^3: 17.9 against 22.5 / 14.9 against 16.6).
-//  k = 3: small tiles until there are enough of them for every CU (20^3: 4x4x2
-//    13.6 against 17.3 with 8x4x4), then the fewer shared nodes of 8x4x4 (32^3:
-//    19.7 against 20.5, 64^3: 80 against 88 / 52 against 56).
-//  k = 4: the same, in multiples of the 12 cells of a wave (16^3: 4x3x2 16.1
-//    against 17.6 with 4x4x3; 32^3: 35.4 against 38.9; in FP32 6x4x2 23.1
-//    against 24.1 with 4x4x3).
-LaunchCfg default_config(int k, int prec, int64_t ncell)
-{
-    const bool f32 = prec == VPP_FP32;
-    if (k == 2) {
-        if (ncell <= (f32 ? 50000 : 20000)) return LaunchCfg{1, {8, 4, 2}};
-        return f32 ? LaunchCfg{4, {16, 8, 4}} : LaunchCfg{4, {8, 8, 4}};
-    }
-    if (k == 3) return ncell <= 16000 ? LaunchCfg{1, {4, 4, 2}} : LaunchCfg{1, {8, 4, 4}};
-    if (ncell <= 8000) return LaunchCfg{1, {4, 3, 2}};
-    return f32 ? LaunchCfg{1, {6, 4, 2}} : LaunchCfg{1, {4, 4, 3}};
-}
-
-// The same with the mass shift, where the configuration in use has no kernel with
-// it.  PCG iteration, us: k = 2, 16^3 cells 16.9 with 8x4x4 against 18.9 with
-// 16x8x4, 32^3 20.7 against 23.1, 40^3 27.5 against 27.1, 48^3 33.6 against 31.5;
-// k = 3, 4x4x4 until 64^3 cells (8^3 19.2 against 21.8 with 8x4x4, 24^3 25.0 against
-// 27.8, 48^3 83.4 against 86.5, 64^3 202 against 200).  k = 4 as without: its tiles
-// have both kernels (32^3: 4x4x3 65.6 against 71.8 with 4x3x2).
-LaunchCfg mass_default_config(int k, int prec, int64_t ncell)
-{
-    if (k == 2) return ncell <= 40000 ? LaunchCfg{4, {8, 4, 4}} : LaunchCfg{4, {16, 8, 4}};
-    if (k == 3) return ncell <= 200000 ? LaunchCfg{4, {4, 4, 4}} : LaunchCfg{4, {8, 4, 4}};
-    return default_config(k, prec, ncell);
-}
 
 template <typename T>
 vpp_status dev_alloc(T** p, size_t n, const char* what)
@@ -180,6 +143,7 @@ struct vpp_problem_s {
     LaunchCfg cfg{};
     MeshArgs m32{};                 // FP32 apply (tile counts of cfg32)
     LaunchCfg cfg32{};
+    bool fits = true, fits32 = true;   // whether those tiles address the whole mesh (tiles_fit)
     double* phi64 = nullptr;
     float* phi32 = nullptr;
     double* diag = nullptr;
@@ -257,12 +221,7 @@ struct vpp_batch_s {
     int cg_graph_iters = 0;
 };
 
-static void set_tiles(MeshArgs& m, const LaunchCfg& c)
-{
-    for (int d = 0; d < 3; ++d) m.ntile[d] = (m.nc[d] + c.tile[d] - 1) / c.tile[d];
-}
-
-static int tile_count(const MeshArgs& m) { return m.ntile[0] * m.ntile[1] * m.ntile[2]; }
+static int tile_count(const MeshArgs& m) { return (int)tile_count64(m); }
 
 static MeshArgs make_mesh_args(const vpp_desc& d)
 {
@@ -388,14 +347,28 @@ static bool config_ok(vpp_problem p, const LaunchCfg& c)
     return p->m.mass != 0.0 ? mass_config_supported(c, p->k) : apply_config_supported(c, p->k);
 }
 
+static bool config_fits(vpp_problem p, int prec, const LaunchCfg& c)
+{
+    return tiles_fit(p->k, p->m, c, prec == VPP_FP32 ? sizeof(float) : sizeof(double));
+}
+
 static int config_list(vpp_problem p, LaunchCfg* out, int cap)
 {
     if (arith_law(p->desc)) return list_arith_configs(p->k, out, cap);
     return p->m.mass != 0.0 ? list_mass_configs(p->k, out, cap) : list_apply_configs(p->k, out, cap);
 }
 
+// A wide, shallow mesh can be out of reach of a tile's 32-bit lane offsets: such
+// a configuration is neither taken by vpp_set_config_for nor tried by vpp_tune,
+// and where a problem has no other, its applies and solves return this.
+static vpp_status tiles_out_of_reach()
+{
+    return fail(VPP_ERR_UNSUPPORTED, "mesh too wide for the 32-bit offsets of this tile configuration");
+}
+
 static vpp_status do_apply64(vpp_problem p, const double* x, double* y, double* dot, const int* done, hipStream_t s)
 {
+    if (!p->fits) return tiles_out_of_reach();
     ApplyArgs<double> a{p->m, x, y, p->phi64, p->part, shared_stride(p->m), dot ? p->dot_part : nullptr, dot,
                         done};
     VPP_HIP(launch_apply_f64(p->cfg, p->k, a, s));
@@ -404,6 +377,7 @@ static vpp_status do_apply64(vpp_problem p, const double* x, double* y, double* 
 
 static vpp_status do_apply32(vpp_problem p, const float* x, float* y, double* dot, const int* done, hipStream_t s)
 {
+    if (!p->fits32) return tiles_out_of_reach();
     ApplyArgs<float> a{p->m32, x, y, p->phi32, reinterpret_cast<float*>(p->part), shared_stride(p->m32),
                        dot ? p->dot_part : nullptr, dot, done};
     VPP_HIP(launch_apply_f32(p->cfg32, p->k, a, s));
@@ -466,6 +440,7 @@ static vpp_status build_cg_graph(vpp_problem p, int iters, hipGraphExec_t* out)
     CgWork& w = p->w;
     hipStream_t s = p->stream;
     hipGraph_t g = nullptr;
+    if (!(sizeof(T) == 8 ? p->fits : p->fits32)) return tiles_out_of_reach();
     VPP_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     hipError_t err = hipSuccess;
     for (int it = 0; it < iters && err == hipSuccess; ++it) {
@@ -1125,8 +1100,8 @@ vpp_status vpp_create(const vpp_desc* d, vpp_problem* out)
     p->ncell = ncell;
     p->NQ = ncell * (k + 1) * (k + 1) * (k + 1);
     p->m = make_mesh_args(*d);
-    p->cfg = default_config(p->k, VPP_FP64, ncell);
-    p->cfg32 = default_config(p->k, VPP_FP32, ncell);
+    p->cfg = default_config(p->k, false, p->m);
+    p->cfg32 = default_config(p->k, true, p->m);
     if (arith_law(*d)) {
         LaunchCfg ac[4];
         if (list_arith_configs(p->k, ac, 4) < 1) {
@@ -1135,9 +1110,9 @@ vpp_status vpp_create(const vpp_desc* d, vpp_problem* out)
         }
         p->cfg = p->cfg32 = ac[0];
     }
-    set_tiles(p->m, p->cfg);
     p->m32 = p->m;
-    set_tiles(p->m32, p->cfg32);
+    put_config(p, VPP_FP64, p->cfg);
+    put_config(p, VPP_FP32, p->cfg32);
     vpp_status s;
     if ((s = dev_alloc(&p->phi64, N, "phi")) || (s = dev_alloc(&p->phi32, N, "phi32")) ||
         (s = dev_alloc(&p->diag, N, "diag")) || (s = dev_alloc(&p->inv64, N, "invdiag")) ||
@@ -1204,9 +1179,9 @@ vpp_status vpp_set_mass(vpp_problem p, double mu, void* stream)
     p->m.mass = p->m32.mass = mu * vol;
     if (mu != 0.0) {
         if (!mass_config_supported(p->cfg, p->k))
-            put_config(p, VPP_FP64, mass_default_config(p->k, VPP_FP64, p->ncell));
+            put_config(p, VPP_FP64, mass_default_config(p->k, false, p->m));
         if (!mass_config_supported(p->cfg32, p->k))
-            put_config(p, VPP_FP32, mass_default_config(p->k, VPP_FP32, p->ncell));
+            put_config(p, VPP_FP32, mass_default_config(p->k, true, p->m));
     }
     free_graphs(p->w);   // they hold the operator's arguments by value
     vpp_status st = ensure_apply_scratch(p);
@@ -1510,18 +1485,10 @@ static ReinitArgs reinit_geometry(vpp_problem p, const double* n0, const double*
     return ra;
 }
 
-// Doubles of scratch of the operator: partials of the shared nodes, then one
-// partial of x . y per tile.
-static size_t reinit_scratch(const MeshArgs& m) { return 8 * (size_t)shared_stride(m) + (size_t)tile_count(m); }
-
-// The kernels index the partials with 32 bits (as ensure_apply_scratch checks
-// for the apply); reinit_config's tiles keep every mesh below it that vpp_create takes
-// with its default configuration.
-static vpp_status reinit_tiles_ok(const MeshArgs& m)
-{
-    if (8 * shared_stride(m) < (int64_t(1) << 32)) return VPP_OK;
-    return fail(VPP_ERR_UNSUPPORTED, "mesh too large for 32-bit partial indices of the reinitialization operator");
-}
+// Doubles of scratch of the operator: partials of the shared nodes, or the cells'
+// results where it runs one cell per thread; then the partials of x . y.
+static int64_t reinit_parts(int k, const MeshArgs& m) { return reinit_config(k, m).variant == 1 ? 8 * shared_stride(m) : cell_values(k, m); }
+static size_t reinit_scratch(int k, const MeshArgs& m) { return (size_t)(reinit_parts(k, m) + reinit_dot_partials(k, m)); }
 
 vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, const double* n1, const double* n2,
                            const vpp_reinit_opts* o, double* psi_out, vpp_cg_info* info, void* stream)
@@ -1540,11 +1507,11 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
     const int64_t n = p->N;
     const ReinitArgs ra = reinit_geometry(p, n0, n1, n2, o);
     const int64_t stride = shared_stride(ra.g.m);
-    const int ntiles = tile_count(ra.g.m);
+    const int ndot = reinit_dot_partials(p->k, ra.g.m);
     double* cv;
-    if ((st = reinit_tiles_ok(ra.g.m))) return st;
-    if ((st = scratch_begin(p, std::max((size_t)cell_values(p->k, p->m), reinit_scratch(ra.g.m)), s, &cv))) return st;
-    double* const dot_part = cv + 8 * stride;
+    if ((st = scratch_begin(p, std::max((size_t)cell_values(p->k, p->m), reinit_scratch(p->k, ra.g.m)), s, &cv)))
+        return st;
+    double* const dot_part = cv + reinit_parts(p->k, ra.g.m);
     const ReinitApplyArgs plain{ra, w.x, w.q, cv, stride, nullptr, nullptr, false};
     VPP_HIP(launch_reinit_rhs(p->k, ra, psi, w.b, cv, s));
     VPP_HIP(launch_reinit_diag(p->k, ra, w.diag, cv, s));
@@ -1587,7 +1554,7 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
                 // tile kernel (with p.q partials); the update assembles the shared nodes
                 const ReinitApplyArgs a{ra, w.p, w.q, cv, stride, dot_part, &w.st->halt[par], true};
                 VPP_HIP(launch_reinit_apply(p->k, a, s));
-                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, dot_part, ntiles, w.map, cv, stride, w.r,
+                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, dot_part, ndot, w.map, cv, stride, w.r,
                                                           w.q, w.invd, n, s));
                 VPP_HIP(launch_cg_pupdate<double>(w.st, par, w.red, w.x, w.r, w.p, w.invd, n, s));
             }
@@ -1641,8 +1608,7 @@ vpp_status vpp_reinit_apply(vpp_problem p, const double* n0, const double* n1, c
     DeviceGuard dg(p->desc.device);
     hipStream_t s = (hipStream_t)stream;
     double* cv;
-    if ((st = reinit_tiles_ok(ra.g.m))) return st;
-    if ((st = scratch_begin(p, reinit_scratch(ra.g.m), s, &cv))) return st;
+    if ((st = scratch_begin(p, reinit_scratch(p->k, ra.g.m), s, &cv))) return st;
     const ReinitApplyArgs a{ra, x, y, cv, shared_stride(ra.g.m), nullptr, nullptr, false};
     VPP_HIP(launch_reinit_apply(p->k, a, s));
     return cell_scratch_end(p, s);
@@ -2241,9 +2207,11 @@ static void put_config(vpp_problem p, int prec, const LaunchCfg& c)
     if (prec == VPP_FP32) {
         p->cfg32 = c;
         set_tiles(p->m32, c);
+        p->fits32 = tiles_fit(p->k, p->m32, c, sizeof(float));
     } else {
         p->cfg = c;
         set_tiles(p->m, c);
+        p->fits = tiles_fit(p->k, p->m, c, sizeof(double));
     }
 }
 
@@ -2267,6 +2235,7 @@ vpp_status vpp_set_config_for(vpp_problem p, int32_t precision, const vpp_kernel
     if (!config_ok(p, c))
         return fail(VPP_ERR_UNSUPPORTED, p->m.mass != 0.0 ? "kernel configuration not available with the mass shift"
                                                           : "kernel configuration not available");
+    if (!config_fits(p, precision, c)) return tiles_out_of_reach();
     DeviceGuard dg(p->desc.device);
     if (p->stream) VPP_HIP(hipStreamSynchronize(p->stream));
     put_config(p, precision, c);
@@ -2305,7 +2274,7 @@ static vpp_status tune_precision(vpp_problem p, int prec, const char* cache_path
                                                              : (mass ? "applym/hbm" : "apply/hbm"),
                                             p->k, p->N);
     LaunchCfg c;
-    if (cache_lookup(cache_path, key, &c) && config_ok(p, c)) {
+    if (cache_lookup(cache_path, key, &c) && config_ok(p, c) && config_fits(p, prec, c)) {
         put_config(p, prec, c);
         return ensure_apply_scratch(p);
     }
@@ -2332,6 +2301,7 @@ static vpp_status tune_precision(vpp_problem p, int prec, const char* cache_path
         return st == VPP_OK;
     };
     for (int i = 0; i < n && !st; ++i) {
+        if (!config_fits(p, prec, cands[i])) continue;
         put_config(p, prec, cands[i]);
         if ((st = ensure_apply_scratch(p))) break;
         if ((st = one())) break;
@@ -2482,11 +2452,19 @@ static vpp_status batch_set_pointers(vpp_batch b, const double* const* x, double
     return batch_build_graph(b);
 }
 
+// Whether the tiles of configuration c address every mesh of the batch.
+static bool batch_fits(vpp_batch b, const LaunchCfg& c)
+{
+    for (vpp_problem p : b->probs)
+        if (!tiles_fit(b->k, p->m, c, sizeof(double))) return false;
+    return true;
+}
+
 static vpp_status batch_tune(vpp_batch b, const char* cache_path)
 {
     const std::string key = size_bucket_key("batch", b->k, b->total_dofs);
     LaunchCfg c;
-    if (cache_lookup(cache_path, key, &c) && batch_config_supported(c, b->k)) {
+    if (cache_lookup(cache_path, key, &c) && batch_config_supported(c, b->k) && batch_fits(b, c)) {
         b->cfg = c;
         return batch_build_table(b);
     }
@@ -2505,8 +2483,9 @@ static vpp_status batch_tune(vpp_batch b, const char* cache_path)
     LaunchCfg all[16], cands[16];
     const int na = std::min(list_batch_configs(b->k, all, 16), 16);
     int nc = 0;
-    for (int i = 0; i < na; ++i) cands[nc++] = all[i];
-    if (nc == 0) st = fail(VPP_ERR_UNSUPPORTED, "no batch kernel configuration for this degree");
+    for (int i = 0; i < na; ++i)
+        if (batch_fits(b, all[i])) cands[nc++] = all[i];
+    if (nc == 0) st = na == 0 ? fail(VPP_ERR_UNSUPPORTED, "no batch kernel configuration for this degree") : tiles_out_of_reach();
     double best = 1e300;
     LaunchCfg best_cfg = nc ? cands[0] : LaunchCfg{4, {8, 8, 4}};
     hipEvent_t e0 = nullptr, e1 = nullptr;

@@ -165,18 +165,20 @@ struct ReinitArgs {
 };
 // y = A x on tiles (reinit_config's; r.g.m holds their counts): the tile kernel
 // (interior nodes of y, partials of the shared nodes, per-tile partials of x . y
-// if dot_part), then, unless tiles_only, the assembly of the shared nodes.
+// if dot_part), then, unless tiles_only, the assembly of the shared nodes.  Where
+// reinit_config takes no tiles, launch_reinit_cells writes all of y.
 struct ReinitApplyArgs {
     ReinitArgs r;
     const double* x;
     double* y;
-    double* part;       // 8 nshared doubles
+    double* part;       // 8 nshared doubles (without tiles: cell_values)
     int64_t nshared;    // shared_stride
-    double* dot_part;   // optional: one partial of x . y per tile
+    double* dot_part;   // optional: reinit_dot_partials partials of x . y
     const int* done;    // optional: return at once when *done != 0
     bool tiles_only;
 };
-LaunchCfg reinit_config(int k, const MeshArgs& m);
+int reinit_dot_partials(int k, const MeshArgs& m);
+hipError_t launch_reinit_cells(int k, const ReinitApplyArgs& a, int ndot, hipStream_t s);
 hipError_t launch_reinit_apply(int k, const ReinitApplyArgs& a, hipStream_t s);
 // cv: cell_values(k, m) doubles of scratch each.
 hipError_t launch_reinit_diag(int k, const ReinitArgs& r, double* diag, double* cv, hipStream_t s);

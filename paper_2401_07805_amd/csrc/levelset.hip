@@ -1,7 +1,7 @@
 // Right-hand sides of the level-set filter systems (Eqs. normal_vector and
 // normal_vector_regularized, curvature and curvature_regularized), and the
 // diagonal and right-hand side of one semi-implicit step of
-// Eq. reinitialization (further below; its operator is in reinit.hip):
+// Eq. reinitialization (further below; its operator on tiles is in reinit.hip):
 //   normal:    b_d = (n_bar_d, v) with n_bar = grad phi_h / |grad phi_h| at every
 //              Gauss point (zero where the gradient vanishes), d = x, y, z;
 //   curvature: b = (kappa_bar, v) with kappa_bar = -div n_h at every Gauss point,
@@ -212,6 +212,31 @@ __device__ __forceinline__ void normal_at_gauss(const ReinitArgs& r, int cx, int
     }
 }
 
+// One nodal normal component at the Gauss points of a cell.
+template <int K, int D>
+__device__ __forceinline__ void normal_comp_at_gauss(const ReinitArgs& r, int cx, int cy, int cz,
+                                                     double (&nd)[(K + 1) * (K + 1) * (K + 1)])
+{
+    load_nodes<K>(r.g.m, D == 0 ? r.n0 : (D == 1 ? r.n1 : r.n2), cx, cy, cz, nd);
+    sweep3<K, MS, false, 0>(nd);
+    sweep3<K, MS, false, 1>(nd);
+    sweep3<K, MS, false, 2>(nd);
+}
+
+template <int K, int D>
+__device__ __forceinline__ void add_directional(const double (&u)[(K + 1) * (K + 1) * (K + 1)],
+                                                const double (&n)[(K + 1) * (K + 1) * (K + 1)], double ih,
+                                                double (&s)[(K + 1) * (K + 1) * (K + 1)])
+{
+    constexpr int N3 = (K + 1) * (K + 1) * (K + 1);
+    double g[N3];
+#pragma unroll
+    for (int q = 0; q < N3; ++q) g[q] = u[q];
+    sweep3<K, MDC, false, D>(g);
+#pragma unroll
+    for (int q = 0; q < N3; ++q) s[q] = fma(n[q] * ih, g[q], s[q]);
+}
+
 // out += Dc_D^T (w n ih) at the Gauss points.
 template <int K, int D>
 __device__ __forceinline__ void add_flux(const double (&w)[(K + 1) * (K + 1) * (K + 1)],
@@ -225,6 +250,48 @@ __device__ __forceinline__ void add_flux(const double (&w)[(K + 1) * (K + 1) * (
     sweep3<K, MDC, true, D>(g);
 #pragma unroll
     for (int q = 0; q < N3; ++q) out[q] += g[q];
+}
+
+// The operator one cell per thread, for meshes that the tiles of reinit.hip do
+// not address (reinit_config): 64-bit indices throughout, no shared nodes.
+template <int K>
+__global__ void __launch_bounds__(64) reinit_cells_kernel(ReinitArgs r, const double* __restrict__ x,
+                                                          double* __restrict__ cv, const int* done)
+{
+    constexpr int N = K + 1, N3 = N * N * N;
+    const MeshArgs& m = r.g.m;
+    if (done && *done) return;
+    int cx, cy, cz;
+    if (!cell_of(m, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, cx, cy, cz)) return;
+    // One normal component is live at a time (interpolated again for the
+    // flux pass): holding all three at the Gauss points left one wave per SIMD.
+    double u[N3], s[N3], out[N3], nd[N3];
+    load_nodes<K>(m, x, cx, cy, cz, u);
+    sweep3<K, MS, false, 0>(u);
+    sweep3<K, MS, false, 1>(u);
+    sweep3<K, MS, false, 2>(u);
+#pragma unroll
+    for (int q = 0; q < N3; ++q) s[q] = 0.0;
+    normal_comp_at_gauss<K, 0>(r, cx, cy, cz, nd);
+    add_directional<K, 0>(u, nd, r.g.ih[0], s);
+    normal_comp_at_gauss<K, 1>(r, cx, cy, cz, nd);
+    add_directional<K, 1>(u, nd, r.g.ih[1], s);
+    normal_comp_at_gauss<K, 2>(r, cx, cy, cz, nd);
+    add_directional<K, 2>(u, nd, r.g.ih[2], s);
+#pragma unroll
+    for (int q = 0; q < N3; ++q) {
+        const double w = r.g.vol * wref<K>(q % N, (q / N) % N, q / (N * N));
+        out[q] = r.idtau * w * u[q];
+        s[q] *= r.eps * w;
+    }
+    normal_comp_at_gauss<K, 0>(r, cx, cy, cz, nd);
+    add_flux<K, 0>(s, nd, r.g.ih[0], out);
+    normal_comp_at_gauss<K, 1>(r, cx, cy, cz, nd);
+    add_flux<K, 1>(s, nd, r.g.ih[1], out);
+    normal_comp_at_gauss<K, 2>(r, cx, cy, cz, nd);
+    add_flux<K, 2>(s, nd, r.g.ih[2], out);
+    transpose_interp<K>(out);
+    store_cell<K>(m, cx, cy, cz, out, cv);
 }
 
 // Transposed sweep along DIR with the product table T0(q,a) T1(q,a) of the
@@ -343,6 +410,23 @@ __global__ void __launch_bounds__(64) reinit_rhs_kernel(ReinitArgs r, const doub
     store_cell<K>(m, cx, cy, cz, out, cv);
 }
 
+// Per-workgroup partials of x . y (fixed order inside the workgroup).
+__global__ void __launch_bounds__(256) dot_partials_kernel(const double* __restrict__ x, const double* __restrict__ y,
+                                                           int64_t n, double* __restrict__ part)
+{
+    __shared__ double red[256];
+    double s = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        s = fma(x[i], y[i], s);
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+}
+
 }  // namespace
 
 // The cell kernel KERNEL<k> over all cells (64-thread workgroups), writing the
@@ -398,6 +482,18 @@ hipError_t launch_curvature_rhs(int k, const RhsGeo& g, const double* n0, const 
     const MeshArgs& m = g.m;
     VPP_CELLS(curvature_rhs_kernel, g, n0, n1, n2, cv)
     return launch_node_sum(k, m, cv, b, s);
+}
+
+hipError_t launch_reinit_cells(int k, const ReinitApplyArgs& a, int ndot, hipStream_t s)
+{
+    const MeshArgs& m = a.r.g.m;
+    double* const cv = a.part;
+    VPP_CELLS(reinit_cells_kernel, a.r, a.x, cv, a.done)
+    hipError_t e = launch_node_sum(k, m, cv, a.y, s);
+    if (e != hipSuccess || !a.dot_part) return e;
+    const int64_t n = (int64_t)m.nn[0] * m.nn[1] * m.nn[2];
+    hipLaunchKernelGGL(dot_partials_kernel, dim3(ndot), dim3(256), 0, s, a.x, a.y, n, a.dot_part);
+    return hipGetLastError();
 }
 
 hipError_t launch_reinit_diag(int k, const ReinitArgs& r, double* diag, double* cv, hipStream_t s)

@@ -15,6 +15,7 @@
 // the step, both launches before, us: 40x36x27 Q3 133 -> 28, 64^3 Q2 75 -> 45;
 // whole step: 39.8 -> 12.3 ms, 18.6 -> 14.0 ms, 24x25x23 Q4 149.5 -> 19.2 ms.
 #include "apply_plane.h"
+#include "tile_rules.h"
 
 namespace vpp {
 
@@ -188,22 +189,11 @@ hipError_t launch_reinit_tiles(const ReinitApplyArgs& a, hipStream_t s)
 
 }  // namespace
 
-// Small workgroups: seven turns per apply, so a workgroup's waves wait for one
-// another often and other workgroups fill in (64^3 Q2, whole step: 8x4x2 14.0
-// ms, 8x4x4 16.3, 8x8x4 16.0; 20x17x15 Q3: 4x4x2 5.4, 4x4x4 5.8, 8x4x4 6.5;
-// 24x25x23 Q4: 4x3x2 19.2, 4x4x3 19.6).  At k = 3 a large mesh takes 4x4x4 for
-// its fewer shared nodes.  At k = 2 a mesh whose partials' indices would pass 32
-// bits with 8x4x2 (above 10^9 nodes) takes 8x8x4, the pressure operator's tile.
-LaunchCfg reinit_config(int k, const MeshArgs& m)
+int reinit_dot_partials(int k, const MeshArgs& m)
 {
-    if (k == 2) {
-        MeshArgs t = m;
-        const LaunchCfg c{1, {8, 4, 2}};
-        for (int d = 0; d < 3; ++d) t.ntile[d] = (m.nc[d] + c.tile[d] - 1) / c.tile[d];
-        return 8 * shared_stride(t) < (int64_t(1) << 32) ? c : LaunchCfg{1, {8, 8, 4}};
-    }
-    if (k == 4) return LaunchCfg{1, {4, 3, 2}};
-    return (int64_t)m.nc[0] * m.nc[1] * m.nc[2] <= 50000 ? LaunchCfg{1, {4, 4, 2}} : LaunchCfg{1, {4, 4, 4}};
+    if (reinit_config(k, m).variant == 1) return (int)tile_count64(m);
+    const int64_t n = (int64_t)m.nn[0] * m.nn[1] * m.nn[2];
+    return (int)std::max<int64_t>(1, std::min<int64_t>(kMaxRedBlocks, (n + 1023) / 1024));
 }
 
 hipError_t launch_reinit_apply(int k, const ReinitApplyArgs& a, hipStream_t s)
@@ -212,8 +202,9 @@ hipError_t launch_reinit_apply(int k, const ReinitApplyArgs& a, hipStream_t s)
     const LaunchCfg c = reinit_config(k, m);
     for (int d = 0; d < 3; ++d)
         if (m.ntile[d] != (m.nc[d] + c.tile[d] - 1) / c.tile[d]) return hipErrorInvalidValue;
+    if (c.variant != 1) return launch_reinit_cells(k, a, reinit_dot_partials(k, m), s);
     hipError_t e;
-    if (k == 2) e = c.tile[2] == 2 ? launch_reinit_tiles<2, 8, 4, 2>(a, s) : launch_reinit_tiles<2, 8, 8, 4>(a, s);
+    if (k == 2) e = launch_reinit_tiles<2, 8, 4, 2>(a, s);
     else if (k == 4) e = launch_reinit_tiles<4, 4, 3, 2>(a, s);
     else if (k != 3) return hipErrorInvalidValue;
     else if (c.tile[2] == 2) e = launch_reinit_tiles<3, 4, 4, 2>(a, s);
