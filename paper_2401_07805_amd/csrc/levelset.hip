@@ -253,7 +253,8 @@ __device__ __forceinline__ void add_flux(const double (&w)[(K + 1) * (K + 1) * (
 }
 
 // The operator one cell per thread, for meshes that the tiles of reinit.hip do
-// not address (reinit_config): 64-bit indices throughout, no shared nodes.
+// not address or would mostly pad (reinit_config): 64-bit indices throughout, no
+// shared nodes.
 template <int K>
 __global__ void __launch_bounds__(64) reinit_cells_kernel(ReinitArgs r, const double* __restrict__ x,
                                                           double* __restrict__ cv, const int* done)

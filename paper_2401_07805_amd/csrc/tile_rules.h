@@ -49,15 +49,49 @@ inline bool tiles_fit(int k, MeshArgs m, const LaunchCfg& c, size_t value_bytes)
            tile_count64(m) * tile_threads(k, c) < lim;
 }
 
-// The first of the n configurations that fits the mesh, else the first.
-inline LaunchCfg first_fit(int k, const MeshArgs& m, const LaunchCfg* c, int n, size_t value_bytes)
+inline int64_t cell_count(const MeshArgs& m) { return (int64_t)m.nc[0] * m.nc[1] * m.nc[2]; }
+
+// Cells of the mesh's tiles, those past its upper faces included: a thread there
+// runs the whole kernel on zeros.
+inline int64_t padded_cells(MeshArgs m, const LaunchCfg& c)
 {
-    for (int i = 0; i < n; ++i)
-        if (tiles_fit(k, m, c[i], value_bytes)) return c[i];
-    return c[0];
+    set_tiles(m, c);
+    return tile_count64(m) * c.tile[0] * c.tile[1] * c.tile[2];
 }
 
-inline int64_t cell_count(const MeshArgs& m) { return (int64_t)m.nc[0] * m.nc[1] * m.nc[2]; }
+// Relative time of a slot of the padded mesh: at k = 4 the tiles that are not made
+// of full waves cost more (2x150x150, 2x2x2 at half the slots of 4x4x3 56.1 us
+// against 63.6; 90x90x4, 4x4x1 at 1.02 times the slots of 4x3x2 44.1 against 38.3).
+inline int slot_cost(int k, const LaunchCfg& c)
+{
+    if (k != 4) return 100;
+    return c.tile[0] == 2 ? 160 : (c.tile[2] == 1 ? 130 : 100);
+}
+
+// One of n configurations, preferred ones first: the first that fits the mesh,
+// unless it fills the GPU (a tile per CU) and its slots cost a quarter more than a
+// later one's.  Below a quarter the larger tile's fewer shared nodes win
+// (43x37x29 Q3, FP64 / FP32 us: 8x4x4 26.2 / 19.5 at 1.17 times the slots of 4x4x2,
+// 26.8 / 21.0; 26^3 at 1.23 times 18.8 / 14.4 and 18.5 / 14.6), above it they do
+// not (150x150x5 at 1.33 times 55.7 / 38.0 against 48.7 / 33.7, 400x400x1 at 2 times
+// 116.5 / 76.1 against 72.8 / 47.6; Q4 200x200x2, 4x4x3 at 1.5 times 73.7 against
+// 65.3 with 4x3x2).
+inline LaunchCfg pick_config(int k, const MeshArgs& m, const LaunchCfg* c, int n, size_t value_bytes)
+{
+    auto cost = [&](int i) { return padded_cells(m, c[i]) * slot_cost(k, c[i]); };
+    int best = -1;
+    for (int i = 0; i < n; ++i) {
+        if (!tiles_fit(k, m, c[i], value_bytes)) continue;
+        if (best < 0) {
+            best = i;
+            continue;
+        }
+        MeshArgs t = m;
+        set_tiles(t, c[best]);
+        if (tile_count64(t) > 256 && 4 * cost(best) > 5 * cost(i)) best = i;
+    }
+    return c[best < 0 ? 0 : best];
+}
 
 // Kernel configuration of a new problem, by degree, precision and number of
 // cells (vpp_tune measures instead).  Measured hot, one apply, us, FP64 / FP32:
@@ -72,26 +106,38 @@ inline int64_t cell_count(const MeshArgs& m) { return (int64_t)m.nc[0] * m.nc[1]
 //  k = 4: the same, in multiples of the 12 cells of a wave (16^3: 4x3x2 16.1
 //    against 17.6 with 4x4x3; 32^3: 35.4 against 38.9; in FP32 6x4x2 23.1
 //    against 24.1 with 4x4x3).
-// A wide and shallow box whose lane offsets would pass 32 bits with that tile
-// (2576 x 2576 x 4 cells at k = 3, 2048 x 2048 x 3 at k = 4) takes a shallower one.
+// A thin box takes a tile that its extent fills better (pick_config); at k = 2 the
+// plane kernel's per-slot cost, 1.25 times the other's, decides once both pad
+// beyond twice the size (1x300x300 in FP64 / FP32: 70.6 / 42.1 against 57.0 / 32.0
+// with 8x8x4; 1x1x2000, half the slots: 13.7 against 17.5), and FP32 takes 16x8x4
+// up to 1.1 times the slots of 8x8x4 (64^3 18.2 against 20.1; 88^3 at 1.09 times 39.3
+// against 39.8, 72^3 at 1.11 28.1 against 26.2, 40x80x80 at 1.2 23.3 against 19.7).  A wide and shallow box
+// whose lane offsets would pass 32 bits (2576 x 2576 x 4 cells at k = 3, 2048 x
+// 2048 x 3 at k = 4) takes a shallower tile.
 inline LaunchCfg default_config(int k, bool f32, const MeshArgs& m)
 {
     const size_t vb = f32 ? 4 : 8;
     const int64_t ncell = cell_count(m);
     if (k == 2) {
-        if (ncell <= (f32 ? 50000 : 20000)) return LaunchCfg{1, {8, 4, 2}};
-        const LaunchCfg c[3] = {f32 ? LaunchCfg{4, {16, 8, 4}} : LaunchCfg{4, {8, 8, 4}}, {4, {8, 8, 4}}, {1, {8, 4, 2}}};
-        return first_fit(k, m, c, 3, vb);
+        const LaunchCfg plane{1, {8, 4, 2}}, slot{4, {8, 8, 4}};
+        const int64_t size = f32 ? 50000 : 20000, pad = padded_cells(m, plane);
+        if (ncell <= size && (pad <= 2 * size || 4 * padded_cells(m, slot) > 5 * pad)) return plane;
+        const LaunchCfg wide{4, {16, 8, 4}};
+        if (f32 && 10 * padded_cells(m, wide) <= 11 * padded_cells(m, slot) && tiles_fit(k, m, wide, vb)) return wide;
+        return tiles_fit(k, m, slot, vb) ? slot : plane;
     }
     if (k == 3) {
         if (ncell <= 16000) return LaunchCfg{1, {4, 4, 2}};
-        const LaunchCfg c[2] = {{1, {8, 4, 4}}, {1, {4, 4, 2}}};
-        return first_fit(k, m, c, 2, vb);
+        const LaunchCfg c[3] = {{1, {8, 4, 4}}, {1, {4, 4, 2}}, {1, {4, 2, 2}}};
+        return pick_config(k, m, c, 3, vb);
     }
-    if (ncell <= 8000) return LaunchCfg{1, {4, 3, 2}};
-    const LaunchCfg c[4] = {f32 ? LaunchCfg{1, {6, 4, 2}} : LaunchCfg{1, {4, 4, 3}}, {1, {4, 3, 2}}, {1, {4, 2, 2}},
+    if (ncell <= 8000) {
+        const LaunchCfg c[2] = {{1, {4, 3, 2}}, {1, {2, 2, 2}}};
+        return pick_config(k, m, c, 2, vb);
+    }
+    const LaunchCfg c[4] = {f32 ? LaunchCfg{1, {6, 4, 2}} : LaunchCfg{1, {4, 4, 3}}, {1, {4, 3, 2}}, {1, {2, 2, 2}},
                             {1, {4, 4, 1}}};
-    return first_fit(k, m, c, 4, vb);
+    return pick_config(k, m, c, 4, vb);
 }
 
 // The same with the mass shift, where the configuration in use has no kernel with
@@ -107,23 +153,33 @@ inline LaunchCfg mass_default_config(int k, bool f32, const MeshArgs& m)
     if (k == 3) return ncell <= 200000 ? LaunchCfg{4, {4, 4, 4}} : LaunchCfg{4, {8, 4, 4}};
     const LaunchCfg c[3] = {default_config(k, f32, m), {1, {4, 3, 2}}, {1, {4, 2, 2}}};
     const int first = c[0].tile[2] == 1 ? 1 : 0;   // 4x4x1 has no kernel with the mass shift
-    return first_fit(k, m, c + first, 3 - first, f32 ? 4 : 8);
+    return pick_config(k, m, c + first, 3 - first, f32 ? 4 : 8);
 }
 
-// Configuration of the reinitialization operator: tiles (variant 1), or, where
-// they do not address the mesh, one cell per thread into the cell-major scratch
-// (variant 0, the whole mesh being one tile: no shared nodes).  Small tiles:
-// seven turns per apply, so a workgroup's waves wait for one another often and
-// other workgroups fill in (64^3 Q2, whole step: 8x4x2 14.0 ms, 8x4x4 16.3, 8x8x4
-// 16.0; 20x17x15 Q3: 4x4x2 5.4, 4x4x4 5.8, 8x4x4 6.5; 24x25x23 Q4: 4x3x2 19.2,
-// 4x4x3 19.6).  At k = 3 a large mesh takes 4x4x4 for its fewer shared nodes.
+// Configuration of the reinitialization operator: tiles (variant 1), or one cell
+// per thread into the cell-major scratch (variant 0, the whole mesh being one
+// tile: no shared nodes) where they do not address the mesh or would mostly be
+// padding.  Small tiles: seven turns per apply, so a workgroup's waves wait for
+// one another often and other workgroups fill in (64^3 Q2, whole step: 8x4x2 14.0
+// ms, 8x4x4 16.3, 8x8x4 16.0; 20x17x15 Q3: 4x4x2 5.4, 4x4x4 5.8, 8x4x4 6.5;
+// 24x25x23 Q4: 4x3x2 19.2, 4x4x3 19.6).  At k = 3 a large mesh takes 4x4x4 for its
+// fewer shared nodes (200x200x3 126 us an iteration against 142) unless it pads a
+// quarter more (150x150x5 137 against 128, 400x400x1 332 against 232).
+// Tiles or cells, us an iteration: k = 2, 300x300x1 52 against 64, 300x1x300 78
+// against 63, 1x300x300 130 against 64, 300x2x300 89 against 90, 1x100x100 25
+// against 38: a slot costs 3/4 of a cell, and the cell kernel some 15 us more to
+// start with.  k = 3, 1x1x20000 155 against 142, 1x200x200 99 against 162; at k = 4
+// the tiles are ahead everywhere (1x1x20000, 12 slots a cell: 329 against 415).
 inline LaunchCfg reinit_config(int k, const MeshArgs& m)
 {
-    const LaunchCfg big{1, {4, 4, 4}};
-    const LaunchCfg small = k == 2 ? LaunchCfg{1, {8, 4, 2}} : (k == 3 ? LaunchCfg{1, {4, 4, 2}} : LaunchCfg{1, {4, 3, 2}});
-    if (k == 3 && cell_count(m) > 50000 && tiles_fit(k, m, big, 8)) return big;
-    if (tiles_fit(k, m, small, 8)) return small;
-    return LaunchCfg{0, {m.nc[0], m.nc[1], m.nc[2]}};
+    const LaunchCfg cells{0, {m.nc[0], m.nc[1], m.nc[2]}};
+    const LaunchCfg c[2] = {{1, {4, 4, 4}}, k == 2 ? LaunchCfg{1, {8, 4, 2}} : (k == 3 ? LaunchCfg{1, {4, 4, 2}} : LaunchCfg{1, {4, 3, 2}})};
+    const int first = k == 3 && cell_count(m) > 50000 ? 0 : 1;
+    const LaunchCfg t = pick_config(k, m, c + first, 2 - first, 8);
+    if (!tiles_fit(k, m, t, 8)) return cells;
+    const int64_t n = cell_count(m), pad = padded_cells(m, t);
+    if ((k == 2 && 3 * (pad - 120000) > 4 * n) || (k == 3 && pad - 150000 > 5 * n)) return cells;
+    return t;
 }
 
 }  // namespace vpp

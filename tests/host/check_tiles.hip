@@ -53,8 +53,28 @@ static bool reaches(int k, const MeshArgs& m, const LaunchCfg& c, int bytes)
     return largest_offset(k, m, c, bytes) < (1ull << 32);
 }
 
+// Thin boxes: a default's padded cells stay near those of the shallow tile a
+// new problem of its degree could take (8x8x4, 4x4x2, 4x2x2) once the tiles fill
+// the GPU; the reinitialization operator's cells stay near the mesh's.
+static void check_padding(int k, const MeshArgs& m)
+{
+    const LaunchCfg ref = k == 2 ? LaunchCfg{4, {8, 8, 4}} : (k == 3 ? LaunchCfg{1, {4, 4, 2}} : LaunchCfg{1, {4, 2, 2}});
+    for (int f32 = 0; f32 < 2; ++f32) {
+        const LaunchCfg c = default_config(k, f32, m);
+        MeshArgs t = m;
+        set_tiles(t, c);
+        if (!tiles_fit(k, m, ref, f32 ? 4 : 8) || tile_count64(t) <= 256) continue;
+        // k = 4: 4x2x2 itself is not offered; 4x3x2 has up to 1.5 times its slots
+        expect(padded_cells(m, c) <= (k == 4 ? 2.0 : 1.25) * padded_cells(m, ref), "padding", k, m, c);
+    }
+    const LaunchCfg r = reinit_config(k, m);
+    if (r.variant == 1 && k < 4)
+        expect(padded_cells(m, r) <= (k == 2 ? 4.0 / 3 : 5.0) * cell_count(m) + (k == 2 ? 120000 : 150000), "reinitialization padding", k, m, r);
+}
+
 static void check(int k, const MeshArgs& m)
 {
+    check_padding(k, m);
     for (int f32 = 0; f32 < 2; ++f32) {
         const int vb = f32 ? 4 : 8;
         const LaunchCfg c = default_config(k, f32, m), ms = mass_default_config(k, f32, m);
@@ -96,6 +116,11 @@ int main()
            default_config(3, true, mesh(3, 2576, 2576, 4)));
     expect(!tiles_fit(3, mesh(3, 2576, 2576, 4), {1, {8, 4, 4}}, 8), "8x4x4 refused", 3, mesh(3, 2576, 2576, 4), {1, {8, 4, 4}});
     expect(!tiles_fit(4, mesh(4, 2048, 2048, 3), {1, {4, 4, 3}}, 8), "4x4x3 refused", 4, mesh(4, 2048, 2048, 3), {1, {4, 4, 3}});
+    // thin boxes by their extent
+    expect(default_config(3, false, mesh(3, 400, 400, 1)).tile[2] == 2, "thin z", 3, mesh(3, 400, 400, 1), default_config(3, false, mesh(3, 400, 400, 1)));
+    expect(default_config(3, false, mesh(3, 1, 200, 200)).tile[0] == 4, "thin x", 3, mesh(3, 1, 200, 200), default_config(3, false, mesh(3, 1, 200, 200)));
+    expect(default_config(2, true, mesh(2, 1, 300, 300)).tile[0] == 8, "thin x", 2, mesh(2, 1, 300, 300), default_config(2, true, mesh(2, 1, 300, 300)));
+    expect(reinit_config(2, mesh(2, 1, 300, 300)).variant == 0, "cells", 2, mesh(2, 1, 300, 300), reinit_config(2, mesh(2, 1, 300, 300)));
     // the reinitialization operator where not even its shallow tiles reach
     expect(reinit_config(2, mesh(2, 8200, 8200, 3)).variant == 0, "cells", 2, mesh(2, 8200, 8200, 3), reinit_config(2, mesh(2, 8200, 8200, 3)));
     // random boxes up to 2^31 - 1 nodes, 2^20 - 1 per direction

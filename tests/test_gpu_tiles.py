@@ -108,3 +108,47 @@ def test_default_configuration_with_the_mass_shift(k, ncells):
         assert float((z - y).norm() / y.norm()) < 1e-12, cfg
         assert float((z32 - y32).norm() / y32.norm()) < 2e-6, cfg
     assert count >= 2
+
+
+def _thin(k, ncells):
+    h = 1.0 / max(ncells)
+    return W.Mesh(ncells=ncells, degree=k, bc=(0, 1, 1, 0, 0, 1), extent=tuple(h * n for n in ncells), rho_l=1000.0,
+                  rho_g=1.0)
+
+
+# thin boxes, whose defaults go by the extent: in FP64 4x4x2, 4x2x2, 2x2x2 and 4x4x1,
+# in FP32 8x8x4 (k = 2) and 4x3x2 (k = 4)
+@pytest.mark.parametrize("k,ncells,tile", [(2, (1, 231, 230), (8, 8, 4)), (3, (141, 139, 1), (4, 4, 2)),
+                                           (3, (151, 1, 149), (4, 2, 2)), (4, (1, 101, 99), (2, 2, 2)),
+                                           (4, (101, 99, 1), (4, 4, 1))])
+def test_default_config_of_thin_boxes(k, ncells, tile):
+    m = _thin(k, ncells)
+    phi = W.uniform_vectors(3, 1, m.ndofs)[0]
+    x = W.uniform_vectors(5, 1, m.ndofs)[0]
+    rows = np.random.default_rng(1).choice(m.ndofs, 2000, replace=False)
+    ref = oracle.apply_rows(m, phi, x, rows)
+    p = vpp.Problem.from_mesh(m)
+    p.set_phi(dev(phi))
+    say("thin box", k, ncells, p.config_for("fp64"), p.config_for("fp32"))
+    assert p.config_for("fp64")["tile"] == tile
+    assert rel(host(p.apply(dev(x)))[rows], ref) < 1e-12
+    assert rel(host(p.apply(dev(x).float()).double())[rows], ref) < 2e-6
+
+
+# thin boxes on which the reinitialization operator runs one cell per thread
+@pytest.mark.parametrize("k,ncells", [(2, (1, 201, 199)), (3, (1, 1, 20001))])
+def test_reinit_of_thin_boxes(k, ncells):
+    m = _thin(k, ncells)
+    normal = W.normal_field(m, (0.3 * m.extent[0], 0.47 * m.extent[1], 0.52 * m.extent[2]))
+    h = m.extent[2] / ncells[2]
+    x = W.uniform_vectors(7, 1, m.ndofs)[0]
+    rows = np.random.default_rng(2).choice(m.ndofs, 2000, replace=False)
+    ax, _, rb = oracle.reinit_rows(m, normal, 2 * h, 2 * h, x, x, rows)
+    p = vpp.Problem.from_mesh(m)
+    nd = [dev(c) for c in normal]
+    say("thin reinit", k, ncells)
+    assert rel(host(p.reinit_apply(dev(x), nd, 2 * h, 2 * h))[rows], ax) < 1e-12
+    new, info = p.reinit_step(dev(x), nd, 2 * h, 2 * h)
+    say("thin reinit step", info)
+    assert info["status"] == 0 and info["true_rel_residual"] < 1.01e-12
+    assert rel(host(p.reinit_apply(new, nd, 2 * h, 2 * h))[rows], rb) < 1e-9
