@@ -398,13 +398,14 @@ vpp_status vpp_batch_apply(vpp_batch b, const double* const* x, double* const* y
  * rhs, x: host arrays of sum(nrhs) device pointers, ordered problem-major; x
  * holds the initial guesses on entry and the solutions on return.
  * VPP_FP64: the systems of meshes below 2^20 unknowns iterate in lockstep,
- * one iteration being one batched apply and two batched vector
- * launches over every such system that has not stopped (systems that have
- * stopped are skipped), recorded in a hipGraph of check_every iterations; each
- * system's reductions are summed in a fixed order.  Systems of larger meshes fill the GPU on their own and are solved
- * one after another with vpp_cg_solve (and the problem's tuned kernels), after
- * the lockstep group.  VPP_MIXED: every system is solved with vpp_cg_solve, one
- * after another.  Synchronizes.
+ * one iteration being one batched apply and two batched vector launches over
+ * every such system that has not stopped (systems that have stopped are
+ * skipped), recorded in a hipGraph of check_every iterations; each system's
+ * reductions are summed in the order of a single solve on the batch's tiles,
+ * whatever else is in the batch.  Systems of larger meshes fill the GPU on their
+ * own and are solved one after another with vpp_cg_solve (and the problem's
+ * tuned kernels), after the lockstep group.  VPP_MIXED: every system is solved
+ * with vpp_cg_solve, one after another.  Synchronizes.
  * info: sum(nrhs) entries (may be NULL).  Returns the first non-OK status of
  * the systems (VPP_ERR_NOT_CONVERGED, VPP_ERR_BREAKDOWN) after all of them
  * have been solved; every x then holds its last iterate. */

@@ -2537,8 +2537,8 @@ static vpp_status batch_tune(vpp_batch b, const char* cache_path)
 // in lockstep, one iteration being the batched apply (tile kernel
 // with per-tile p.Ap partials) and the batched update and search-direction
 // update; a system that has stopped is skipped by all three.  Each lockstep
-// system's reductions have the workgroup count and summation order of a single
-// solve on the batch's tiles.
+// system's reductions have the partials and the summation order of a single solve
+// on the batch's tiles, so its bits do not depend on what else is in the batch.
 constexpr int64_t kLockstepMaxDofs = int64_t(1) << 20;
 
 static void batch_cg_free(vpp_batch b)
@@ -2607,15 +2607,16 @@ static vpp_status batch_cg_setup(vpp_batch b)
     }
     std::vector<double*> tx(S), tp(S), tq(S);
     std::vector<CgSystem<double>> sys(S);
-    // Packets per thread of the vector launches: enough that all their workgroups
-    // are resident at once (about five per CU; each spends some 4 us on its
-    // system's table, state and partial sums before its first packet: 7448
-    // workgroups of one packet per thread took 42 us for the update of 16 systems
-    // of 16^3-40^3 Q2 cells)
+    // Shares (workgroups of a single solve's update) per workgroup of the vector
+    // launches: enough that all their workgroups are resident at once (about five
+    // per CU; each spends some 4 us on its system's table, state and partial sums
+    // before its first packet: 7448 workgroups of one share took 42 us for the
+    // update of 16 systems of 16^3-40^3 Q2 cells).  A system's sums do not depend
+    // on it, so neither do they on what else is in the batch.
     int64_t all = 0;
-    for (const BatchProblem& P : tab) all += (int64_t)P.nrhs * P.m.nn[0] * P.m.nn[1] * P.m.nn[2];
-    const int64_t resident = (int64_t)5 * device_cu_count() * 256 * 2;
-    const int packets = (int)std::max<int64_t>(1, std::min<int64_t>(16, (all + resident - 1) / resident));
+    for (size_t t = 0; t < tab.size(); ++t) all += (int64_t)tab[t].nrhs * cg_update_blocks(b->probs[b->cg_prob[t]]->N);
+    const int64_t resident = (int64_t)5 * device_cu_count();
+    const int shares = (int)std::max<int64_t>(1, std::min<int64_t>(kMaxShares, (all + resident - 1) / resident));
     // shared-node maps, each starting on a 16-byte boundary
     std::vector<int64_t> map_off;
     int64_t map_n = 0;
@@ -2656,7 +2657,8 @@ static vpp_status batch_cg_setup(vpp_batch b)
             y.invd = prob->inv64;
             y.n = prob->N;
             y.blk_begin = blk;
-            y.nblk = cg_update_blocks(y.n, packets);
+            y.nsum = cg_update_blocks(y.n);
+            y.nblk = (y.nsum + shares - 1) / shares;
             blk += y.nblk;
         }
     b->cg_blocks = blk;

@@ -278,7 +278,8 @@ __global__ void __launch_bounds__((batch_threads<K, TX, TY, TZ>())) batch_apply_
     if (a.st && a.st[rhs].halt[a.par]) return;   // a system that has stopped
     const ApplyArgs<double> t{P.m, a.x[rhs], a.y[rhs], P.phi, a.part + P.part_begin + (int64_t)r * 8 * P.nshared,
                               P.nshared, dot ? a.dot_part + P.dot_begin : nullptr, nullptr, nullptr, true};
-    double* const dot_out = t.dot_part + r * P.ntiles + tile;
+    // a tile's partial where its single apply's workgroup puts it: the same sum
+    double* const dot_out = t.dot_part + r * P.ntiles + xcd_block(tile, P.ntiles);
     VPP_BC_BEGIN(t.x, t.y, t.phi, t.part, t.dot_part, slot, (int64_t)t.m.nn[0] * t.m.nn[1] * t.m.nn[2],
                  8 * t.nshared, (int64_t)P.nrhs * P.ntiles, LDS);
     if constexpr (K == 2) slot_tile<K, double, TX, TY, TZ, HV, dot, mass>(t, tile, slot, dot_out);

@@ -73,12 +73,15 @@ struct CgSystem {
     const T* invd;
     int64_t n;
     int blk_begin;            // first workgroup of this system in the batched launches
-    int nblk;                 // its workgroup count, cg_update_blocks
+    int nblk;                 // its workgroup count
+    int nsum;                 // partials of its reductions, cg_update_blocks(n): at most kMaxShares nblk
 };
 
-// Workgroups of a system of n unknowns in the batched vector launches, at
-// `packets` 16-byte packets per thread.
-int cg_update_blocks(int64_t n, int packets);
+// Workgroups, and so partials, of the update of a single system of n unknowns.
+// In the batched launches a workgroup stands for up to kMaxShares of them, one
+// after another, so that the sums do not depend on how many it stands for.
+constexpr int kMaxShares = 16;
+int cg_update_blocks(int64_t n);
 // The update and the search-direction update of every system of the device
 // table sys as two launches of total_blocks workgroups (owner[b]: system of
 // workgroup b).

@@ -159,12 +159,16 @@ __device__ __forceinline__ void assemble_packet(const SharedParts<T>& sp, const 
 }
 
 // Body of the update for workgroup bid of one system; the workgroup returns at
-// once when the system has stopped.
-template <typename T>
-__device__ __forceinline__ void assemble_update_body(int bid, int nblk, CgState* st, int par, double* red,
+// once when the system has stopped.  Share v of the nsum shares takes packets
+// v BT + tid + j nsum BT and gives one partial of each sum; a workgroup has one
+// share (nblk = nsum) or, with SHARES, shares bid, bid + nblk, ...: the partials
+// and the sums over them are those of one share per workgroup.
+template <typename T, bool SHARES>
+__device__ __forceinline__ void assemble_update_body(int bid, int nblk, int nsum, CgState* st, int par, double* red,
                                                      const SharedParts<T>& sp, T* __restrict__ r,
                                                      const T* __restrict__ q, const T* __restrict__ invd, int64_t n)
 {
+    __shared__ double share_a[SHARES ? kMaxShares : 1][BT / 64], share_b[SHARES ? kMaxShares : 1][BT / 64];
     float* hist = nullptr;
     int hit = 0, hcap = 0;
     int64_t hstride = 0;
@@ -184,46 +188,72 @@ __device__ __forceinline__ void assemble_update_body(int bid, int nblk, CgState*
     const int64_t np = n / W;
     // a packet's map entries are loaded one packet ahead (the first before the
     // reduction), so that its partials' addresses do not wait for them
-    const int64_t S = (int64_t)nblk * BT;
+    const int64_t S = (int64_t)nsum * BT;
     int64_t c = (int64_t)bid * BT + threadIdx.x;
     Map mp{};
     if (c < np) mp = reinterpret_cast<const Map*>(sp.map)[c];
     T alpha;
     if (!update_alpha(bid, st, par, sp.dot_part, sp.ndot, alpha)) return;
-    double rr = 0.0, rz = 0.0;
     T* hrec = nullptr;
     if constexpr (sizeof(T) == 4)
         if (hist && hit < hcap) hrec = hist + (size_t)hit * (size_t)hstride;
-    for (; c < np; c += S) {
-        P rv = reinterpret_cast<const P*>(r)[c];
-        const P dv = reinterpret_cast<const P*>(invd)[c];
-        P qv = reinterpret_cast<const P*>(q)[c];
-        const Map now = mp;
-        if (c + S < np) mp = reinterpret_cast<const Map*>(sp.map)[c + S];
-        assemble_packet<T, W>(sp, now.v, qv.v);
+    int share = 0;
+    for (int v = bid; v < nsum; v += nblk, ++share) {
+        double rr = 0.0, rz = 0.0;
+        c = (int64_t)v * BT + threadIdx.x;
+        const int64_t after = SHARES && v + nblk < nsum ? c + (int64_t)nblk * BT : np;   // the next share's first packet
+        for (; c < np; c += S) {
+            P rv = reinterpret_cast<const P*>(r)[c];
+            const P dv = reinterpret_cast<const P*>(invd)[c];
+            P qv = reinterpret_cast<const P*>(q)[c];
+            const Map now = mp;
+            const int64_t next = c + S < np ? c + S : after;
+            if (next < np) mp = reinterpret_cast<const Map*>(sp.map)[next];
+            assemble_packet<T, W>(sp, now.v, qv.v);
 #pragma unroll
-        for (int t = 0; t < W; ++t) {
-            const T ri = fma(-alpha, qv.v[t], rv.v[t]);
-            rv.v[t] = ri;
-            rr += (double)ri * (double)ri;
-            rz += (double)ri * (double)(ri * dv.v[t]);
+            for (int t = 0; t < W; ++t) {
+                const T ri = fma(-alpha, qv.v[t], rv.v[t]);
+                rv.v[t] = ri;
+                rr += (double)ri * (double)ri;
+                rz += (double)ri * (double)(ri * dv.v[t]);
+            }
+            reinterpret_cast<P*>(r)[c] = rv;
+            if (hrec) reinterpret_cast<P*>(hrec)[c] = rv;
         }
-        reinterpret_cast<P*>(r)[c] = rv;
-        if (hrec) reinterpret_cast<P*>(hrec)[c] = rv;
+        if (v == 0)
+            for (int64_t i = np * W + threadIdx.x; i < n; i += BT) {
+                const unsigned mi[1] = {sp.map[i]};
+                T qi[1] = {q[i]};
+                assemble_packet<T, 1>(sp, mi, qi);
+                const T ri = fma(-alpha, qi[0], r[i]);
+                r[i] = ri;
+                if (hrec) hrec[i] = ri;
+                rr += (double)ri * (double)ri;
+                rz += (double)ri * (double)(ri * invd[i]);
+            }
+        if constexpr (!SHARES) {
+            block_sum2<BT>(rr, rz);
+            write_partials(red, rr, rz, bid);
+            return;
+        }
+        wave_sum2(rr, rz);
+        if (threadIdx.x % 64 == 0) {
+            share_a[share][threadIdx.x / 64] = rr;
+            share_b[share][threadIdx.x / 64] = rz;
+        }
     }
-    if (bid == 0)
-        for (int64_t i = np * W + threadIdx.x; i < n; i += BT) {
-            const unsigned mp[1] = {sp.map[i]};
-            T qi[1] = {q[i]};
-            assemble_packet<T, 1>(sp, mp, qi);
-            const T ri = fma(-alpha, qi[0], r[i]);
-            r[i] = ri;
-            if (hrec) hrec[i] = ri;
-            rr += (double)ri * (double)ri;
-            rz += (double)ri * (double)(ri * invd[i]);
+    // the waves of every share in index order, as block_sum2 adds them
+    __syncthreads();
+    if ((int)threadIdx.x < share) {
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int i = 0; i < BT / 64; ++i) {
+            a += share_a[threadIdx.x][i];
+            b += share_b[threadIdx.x][i];
         }
-    block_sum2<BT>(rr, rz);
-    write_partials(red, rr, rz, bid);
+        red[bid + threadIdx.x * nblk] = a;
+        red[kMaxRedBlocks + bid + threadIdx.x * nblk] = b;
+    }
 }
 
 template <typename T>
@@ -231,7 +261,7 @@ __global__ void __launch_bounds__(BT) cg_assemble_update_kernel(CgState* st, int
                                                                 T* __restrict__ r, const T* __restrict__ q,
                                                                 const T* __restrict__ invd, int64_t n)
 {
-    assemble_update_body<T>(blockIdx.x, gridDim.x, st, par, red, sp, r, q, invd, n);
+    assemble_update_body<T, false>(blockIdx.x, gridDim.x, gridDim.x, st, par, red, sp, r, q, invd, n);
 }
 
 template <typename T>
@@ -245,21 +275,22 @@ __global__ void __launch_bounds__(BT) cg_pupdate_kernel(CgState* st, int par, co
 // ---------------------------------------------------------------------------
 // Batched PCG: the update and the search-direction update of every system of a
 // batch in one launch each.  System i owns workgroups [blk_begin, blk_begin +
-// nblk) of the grid (cg_update_blocks); owner[] gives the system of each.
+// nblk) of the grid; owner[] gives the system of each.
 
 template <typename T>
 __global__ void __launch_bounds__(BT) cg_batch_update_kernel(const CgSystem<T>* sys, const int* owner, int par)
 {
     const CgSystem<T>& y = sys[owner[blockIdx.x]];
     const SharedParts<T> sp{y.map, y.part, y.stride, y.dot_part, y.ndot};
-    assemble_update_body<T>((int)blockIdx.x - y.blk_begin, y.nblk, y.st, par, y.red, sp, y.r, y.q, y.invd, y.n);
+    assemble_update_body<T, true>((int)blockIdx.x - y.blk_begin, y.nblk, y.nsum, y.st, par, y.red, sp, y.r, y.q, y.invd,
+                                  y.n);
 }
 
 template <typename T>
 __global__ void __launch_bounds__(BT) cg_batch_pupdate_kernel(const CgSystem<T>* sys, const int* owner, int par)
 {
     const CgSystem<T>& y = sys[owner[blockIdx.x]];
-    pupdate_body<T>((int)blockIdx.x - y.blk_begin, y.nblk, y.st, par, y.red, y.nblk, y.x, y.r, y.p, y.invd, y.n);
+    pupdate_body<T>((int)blockIdx.x - y.blk_begin, y.nblk, y.st, par, y.red, y.nsum, y.x, y.r, y.p, y.invd, y.n);
 }
 
 // r = b - q in FP64 and partials of r.r (outer residual of the mixed solver and
@@ -370,11 +401,7 @@ hipError_t launch_cg_pupdate(CgState* st, int par, const double* red, T* x, cons
     return hipGetLastError();
 }
 
-int cg_update_blocks(int64_t n, int packets)
-{
-    const int64_t per = (int64_t)packets * BT * Pack<double>::W;
-    return (int)std::min<int64_t>(kMaxRedBlocks, std::max<int64_t>(1, (n + per - 1) / per));
-}
+int cg_update_blocks(int64_t n) { return grid_update<double>(n); }
 
 hipError_t launch_cg_batch_step(const CgSystem<double>* sys, const int* owner, int total_blocks, int par, hipStream_t s)
 {

@@ -14,17 +14,23 @@ struct alignas(16) Pack {
     T v[W];
 };
 
-// Workgroup sums of two doubles in a fixed order (butterfly inside each wave,
-// then the waves in index order); every thread receives the totals.
-template <int NT>
-__device__ __forceinline__ void block_sum2(double& a, double& b)
+// Wave sums of two doubles (butterfly); every lane receives the totals.
+__device__ __forceinline__ void wave_sum2(double& a, double& b)
 {
-    static_assert(NT % 64 == 0, "whole waves only");
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         a += __shfl_xor(a, o);
         b += __shfl_xor(b, o);
     }
+}
+
+// Workgroup sums of two doubles in a fixed order (wave_sum2, then the waves in
+// index order); every thread receives the totals.
+template <int NT>
+__device__ __forceinline__ void block_sum2(double& a, double& b)
+{
+    static_assert(NT % 64 == 0, "whole waves only");
+    wave_sum2(a, b);
     __shared__ double pa[NT / 64], pb[NT / 64];
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {

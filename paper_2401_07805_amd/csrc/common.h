@@ -343,7 +343,7 @@ __device__ __forceinline__ void coef_weights3(const MeshArgs& m, T (&v)[(K + 1) 
 // x-fastest.  Workgroups are dispatched round-robin over the 8 XCDs, so block b
 // runs on XCD b % 8; remapping b -> (b % 8) * chunk + b / 8 gives every XCD a
 // contiguous run of tiles, whose shared faces then meet in the same L2.
-__device__ __forceinline__ int xcd_tile(int b, int nblocks)
+__host__ __device__ __forceinline__ int xcd_tile(int b, int nblocks)
 {
     const int chunk = (nblocks + 7) / 8;
     const int x = b % 8, r = b / 8;
@@ -352,6 +352,15 @@ __device__ __forceinline__ int xcd_tile(int b, int nblocks)
     if (x < full) t = x * chunk + r;
     else t = full * chunk + (x - full) * (chunk - 1) + r;
     return t;
+}
+
+// The workgroup that xcd_tile gives tile t.
+__host__ __device__ __forceinline__ int xcd_block(int t, int nblocks)
+{
+    const int chunk = (nblocks + 7) / 8, full = nblocks - 8 * (chunk - 1);
+    if (t < full * chunk) return t / chunk + 8 * (t % chunk);
+    t -= full * chunk;
+    return full + t / (chunk - 1) + 8 * (t % (chunk - 1));
 }
 
 }  // namespace vpp

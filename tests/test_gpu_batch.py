@@ -1,5 +1,7 @@
 """Batched persistent apply == unbatched applies; tuning candidates agree;
 batched PCG reaches the oracle's solutions."""
+import json
+
 import numpy as np
 import pytest
 import scipy.sparse.linalg as spla
@@ -378,3 +380,48 @@ def test_q3_batch_bench_workload_against_oracle():
             say("q3 bench mesh", m.ncells[0], "rhs", r, f"err {err:.2e} max {errm:.2e}")
             assert err < 1e-12 and errm < 1e-12
             i += 1
+
+
+def _batch_with_tile(probs, nrhs, tile, cache):
+    """A batch whose kernel configuration is `tile`: the cached choice, overwritten."""
+    vpp.Batch(probs, nrhs, tune_cache=str(cache)).close()
+    d = json.loads(cache.read_text())
+    for e in d["entries"]:
+        e["tile"] = list(tile)
+    cache.write_text(json.dumps(d))
+    bt = vpp.Batch(probs, nrhs, tune_cache=str(cache))
+    assert bt.config == {"variant": 4, "tile": tuple(tile)}
+    return bt
+
+
+@pytest.mark.parametrize("k,sizes,tile", [(2, (37, 9, 16), (8, 8, 4)), (3, (21, 5, 11), (4, 4, 4))])
+def test_batch_cg_bits_do_not_depend_on_the_batch(k, sizes, tile, tmp_path):
+    """A lockstep system gives the same bits in a batch of its own, among enough
+    others that the workgroups of the vector launches each stand for several of a
+    single solve's (its first mesh has more than one packet per thread), and in a
+    single solve on the same tiles."""
+    wls = W.batch_meshes(sizes=sizes, nrhs=1, k=k)
+    probs, bs = [], []
+    for wl in wls:
+        p = vpp.Problem.from_mesh(wl.mesh)
+        p.set_phi(dev(wl.phi))
+        p.set_config(4, tile)
+        probs.append(p)
+        bs.append(dev(wl.vectors[0]))
+    say("batch bits: all", k, sizes)
+    nrhs = [4, 1, 2]
+    many = [t for b, n in zip(bs, nrhs) for t in [b] * n]
+    xs = [torch.zeros_like(b) for b in many]
+    infos = _batch_with_tile(probs, nrhs, tile, tmp_path / "all.json").cg_solve(many, xs, rtol=1e-10)
+    i = 0
+    for p, b, n in zip(probs, bs, nrhs):
+        say("batch bits: alone", p.n)
+        xa = [torch.zeros_like(b)]
+        ia = _batch_with_tile([p], [1], tile, tmp_path / f"{p.n}.json").cg_solve([b], xa, rtol=1e-10)
+        x1, i1 = p.cg_solve(b, rtol=1e-10)
+        assert ia[0]["status"] == 0
+        for j in range(i, i + n):
+            assert infos[j]["iterations"] == ia[0]["iterations"] == i1["iterations"]
+            assert torch.equal(xs[j], xa[0])
+            assert torch.equal(xs[j], x1)
+        i += n
