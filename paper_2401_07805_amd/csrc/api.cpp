@@ -454,7 +454,8 @@ static vpp_status build_cg_graph(vpp_problem p, int iters, hipGraphExec_t* out)
             err = launch_apply_f64(p->cfg, p->k, a, s);
             if (err == hipSuccess)
                 err = launch_cg_assemble_update<double>(w.st, par, w.red, p->dot_part, tile_count(p->m), w.map64,
-                                                        p->part, stride, w.r, w.q, p->inv64, p->N, s);
+                                                        shared_enum(p->m, p->k, p->cfg.tile), p->m.bcmask, p->part,
+                                                        stride, w.r, w.q, p->inv64, p->N, s);
             if (err == hipSuccess)
                 err = launch_cg_pupdate<double>(w.st, par, w.red, w.x, w.r, w.p, p->inv64, p->N, s);
         } else {
@@ -465,7 +466,8 @@ static vpp_status build_cg_graph(vpp_problem p, int iters, hipGraphExec_t* out)
             err = launch_apply_f32(p->cfg32, p->k, a, s);
             if (err == hipSuccess)
                 err = launch_cg_assemble_update<float>(w.st32, par, w.red, p->dot_part, tile_count(p->m32), w.map32,
-                                                       part, stride, w.r32, w.q32, p->inv32, p->N, s);
+                                                       shared_enum(p->m32, p->k, p->cfg32.tile), p->m32.bcmask, part,
+                                                       stride, w.r32, w.q32, p->inv32, p->N, s);
             if (err == hipSuccess)
                 err = launch_cg_pupdate<float>(w.st32, par, w.red, w.x32, w.r32, w.p32, p->inv32, p->N, s);
         }
@@ -500,13 +502,17 @@ static vpp_status ensure_graphs(vpp_problem p, int iters, bool mixed)
     }
     vpp_status s;
     if (!w.g64) {
-        if (!w.map64 && (s = dev_alloc(&w.map64, (size_t)p->N, "cg shared-node map"))) return s;
-        VPP_HIP(launch_shared_map(shared_enum(p->m, p->k, p->cfg.tile), p->m.bcmask, w.map64, p->stream));
+        if (shared_map_pays(p->N, sizeof(double))) {
+            if (!w.map64 && (s = dev_alloc(&w.map64, (size_t)p->N, "cg shared-node map"))) return s;
+            VPP_HIP(launch_shared_map(shared_enum(p->m, p->k, p->cfg.tile), p->m.bcmask, w.map64, p->stream));
+        }
         if ((s = build_cg_graph<double>(p, iters, &w.g64))) return s;
     }
     if (mixed && !w.g32) {
-        if (!w.map32 && (s = dev_alloc(&w.map32, (size_t)p->N, "cg shared-node map"))) return s;
-        VPP_HIP(launch_shared_map(shared_enum(p->m32, p->k, p->cfg32.tile), p->m32.bcmask, w.map32, p->stream));
+        if (shared_map_pays(p->N, sizeof(float))) {
+            if (!w.map32 && (s = dev_alloc(&w.map32, (size_t)p->N, "cg shared-node map"))) return s;
+            VPP_HIP(launch_shared_map(shared_enum(p->m32, p->k, p->cfg32.tile), p->m32.bcmask, w.map32, p->stream));
+        }
         if ((s = build_cg_graph<float>(p, iters, &w.g32))) return s;
     }
     return VPP_OK;
@@ -1462,11 +1468,11 @@ static vpp_status ensure_reinit_work(vpp_problem p)
     MeshArgs m = p->m;
     const LaunchCfg c = reinit_config(p->k, m);
     set_tiles(m, c);
-    if ((st = dev_alloc(&w->map, n, "reinit shared-node map"))) {
+    if (shared_map_pays(p->N, sizeof(double)) && (st = dev_alloc(&w->map, n, "reinit shared-node map"))) {
         free_reinit(w);
         return st;
     }
-    if (launch_shared_map(shared_enum(m, p->k, c.tile), 0, w->map, p->stream) != hipSuccess) {
+    if (w->map && launch_shared_map(shared_enum(m, p->k, c.tile), 0, w->map, p->stream) != hipSuccess) {
         free_reinit(w);
         return fail(VPP_ERR_HIP, "reinit shared-node map");
     }
@@ -1508,6 +1514,7 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
     const ReinitArgs ra = reinit_geometry(p, n0, n1, n2, o);
     const int64_t stride = shared_stride(ra.g.m);
     const int ndot = reinit_dot_partials(p->k, ra.g.m);
+    const SharedEnum tiles = shared_enum(ra.g.m, p->k, reinit_config(p->k, ra.g.m).tile);
     double* cv;
     if ((st = scratch_begin(p, std::max((size_t)cell_values(p->k, p->m), reinit_scratch(p->k, ra.g.m)), s, &cv)))
         return st;
@@ -1554,7 +1561,7 @@ vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, c
                 // tile kernel (with p.q partials); the update assembles the shared nodes
                 const ReinitApplyArgs a{ra, w.p, w.q, cv, stride, dot_part, &w.st->halt[par], true};
                 VPP_HIP(launch_reinit_apply(p->k, a, s));
-                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, dot_part, ndot, w.map, cv, stride, w.r,
+                VPP_HIP(launch_cg_assemble_update<double>(w.st, par, w.red, dot_part, ndot, w.map, tiles, 0, cv, stride, w.r,
                                                           w.q, w.invd, n, s));
                 VPP_HIP(launch_cg_pupdate<double>(w.st, par, w.red, w.x, w.r, w.p, w.invd, n, s));
             }

@@ -38,19 +38,20 @@ template <typename T>
 hipError_t launch_cg_init(CgState* st, double* red, const T* b, const T* q, T* r, T* p, const T* invd, int64_t n,
                           hipStream_t s);
 // Map of the shared nodes for the CG update, one entry per node (n = prod e.nn):
-// built once per tile configuration, so that the update finds a node's partials
-// by one 4-byte load.  (Decoding the position per packet instead, by reciprocal
-// divisions, took 240 vector instructions per 16 bytes: 18.3 us per update at
-// 64^3 Q2 against 16.8.)
+// built once per tile configuration where shared_map_pays, so that the update
+// finds a node's partials by one 4-byte load.  (Decoding the position per packet
+// instead, by reciprocal divisions, takes 240 vector instructions per 16 bytes.)
 hipError_t launch_shared_map(const SharedEnum& e, int bcmask, unsigned* map, hipStream_t s);
+bool shared_map_pays(int64_t n, size_t value_bytes);
 // CG update after a tiles-only apply q = A p: p.Ap from the ndot per-workgroup
 // partials dot_part; the values of q on shared nodes assembled from the partial
-// array part (at least one entry; stride `stride`, positions by map); alpha =
+// array part (at least one entry; stride `stride`, positions by map, or where it
+// is null by e and bcmask); alpha =
 // rz / pAp, r -= alpha q, and per-workgroup partials of r.r and r.(D^-1 r).
 template <typename T>
 hipError_t launch_cg_assemble_update(CgState* st, int par, double* red, const double* dot_part, int ndot,
-                                     const unsigned* map, const T* part, int64_t stride, T* r, const T* q,
-                                     const T* invd, int64_t n, hipStream_t s);
+                                     const unsigned* map, const SharedEnum& e, int bcmask, const T* part,
+                                     int64_t stride, T* r, const T* q, const T* invd, int64_t n, hipStream_t s);
 // Stop decision, x += alpha p (alpha as in the update) and p = D^-1 r + beta p.
 template <typename T>
 hipError_t launch_cg_pupdate(CgState* st, int par, const double* red, T* x, const T* r, T* p, const T* invd,

@@ -40,26 +40,40 @@ static int grid_for(int64_t n)
     return (int)(want < 1 ? 1 : (want > kMaxRedBlocks ? kMaxRedBlocks : want));
 }
 
+// Whether the update reads a shared-node map (4 bytes a node) or looks its
+// nodes up by index arithmetic, which hides behind the memory traffic once the
+// vectors are large: update in us, map / lookup, same tiles: FP64 56^3 Q2 12.1 /
+// 12.4, 64^3 Q2 17.6 / 17.8, 43^3 Q3 19.8 / 18.8, 72^3 Q2 22.9 / 21.9, 96^3 Q2 55.0 /
+// 47.6, 96^3 Q3 261 / 233; FP32 64^3 Q3 37.1 / 39.8, 112^3 Q2 47.5 / 51.0, 80^3 Q3
+// 74.2 / 71.1, 96^3 Q3 148 / 123.
+bool shared_map_pays(int64_t n, size_t value_bytes)
+{
+    return n <= (value_bytes == 8 ? int64_t(1) << 21 : int64_t(12000000));
+}
+
 // Workgroups of the update: one packet per thread up to three workgroups per
-// CU (48^3 Q2 9.2 us, 64^3 16.8, 80^3 27.6; with four 9.7, 16.9, 29.0).
+// CU (48^3 Q2 9.2 us, 64^3 16.8, 80^3 27.6; with four 9.7, 16.9, 29.0), four for the
+// FP32 update without a map (80^3 Q3 71 us against 76; FP64 72^3 Q2 22.2 against 21.9).
 template <typename T>
 static int grid_update(int64_t n)
 {
     const int64_t per = (int64_t)BT * Pack<T>::W;
-    return (int)std::min<int64_t>(768, std::max<int64_t>(1, (n + per - 1) / per));
+    const int64_t cap = sizeof(T) == 4 && !shared_map_pays(n, sizeof(T)) ? kMaxRedBlocks : 768;
+    return (int)std::min<int64_t>(cap, std::max<int64_t>(1, (n + per - 1) / per));
 }
 
 // Workgroups of the search-direction update, whose threads take their packets
 // in batches of kBatch: two per CU while a batch covers the vector (48^3 Q2 8.3
-// us, with four 8.7), then four (64^3 15.9 us, with two 17.2), in whole batches
-// once there are two per thread (64^3 Q3 FP32 25.6 us against 27.3).
+// us, with four 8.7), then four (64^3 15.9 us, with two 17.2), above 2 10^7
+// unknowns in whole batches (96^3 Q3 245 us against 266, FP32 93 against 97; below,
+// 88^3 Q2 43.3 against 41.4 and 128^3 Q2 FP32 68 against 64).
 template <typename T>
 static int grid_pupdate(int64_t n)
 {
     const int64_t per = (int64_t)BT * Pack<T>::W;
     const int64_t all = std::max<int64_t>(1, (n + per - 1) / per);   // workgroups at one packet per thread
     if (all <= 512 * kBatch) return (int)std::min<int64_t>(all, 512);
-    if (all <= 1024 * (kBatch + 1)) return 1024;
+    if (n <= 20000000) return (int)std::min<int64_t>(all, 1024);
     const int64_t its = ((all + 1023) / 1024 + kBatch - 1) / kBatch * kBatch;
     return (int)((all + its - 1) / its);
 }
@@ -102,11 +116,13 @@ __global__ void __launch_bounds__(BT) cg_init_finish_kernel(CgState* st, const d
 // the same fixed order by every workgroup.
 template <typename T>
 struct SharedParts {
-    const unsigned* map;   // per node: 0, or where its partials are (shared_map_entry)
+    const unsigned* map;   // per node: 0, or where its partials are (shared_map_entry); null: looked up by e
     const T* part;
     int64_t stride;
     const double* dot_part;
     int ndot;
+    SharedEnum e;
+    int bcmask;
 };
 
 // Entry of the shared-node map: f << 2 | log2 of the number of partials (1, 2, 3;
@@ -158,12 +174,59 @@ __device__ __forceinline__ void assemble_packet(const SharedParts<T>& sp, const 
         if (mp[t]) qv[t] = s[t];
 }
 
+// The map entries of the W nodes from g0 on, by index arithmetic (reciprocal
+// divisions, the row's part once unless the packet wraps a row).
+template <int W>
+__device__ __forceinline__ void lookup_packet(const SharedEnum& e, int bcmask, int g0, unsigned (&mp)[W])
+{
+    int f[W], cnt[W];
+    bool sh[W];
+    const int rw = qdiv(g0, e.nn[0], e.inv_nn[0]), i0 = g0 - rw * e.nn[0];
+    if (i0 + W <= e.nn[0]) {
+        const int l = qdiv(rw, e.nn[1], e.inv_nn[1]);
+        const SharedRow w = shared_row(e, bcmask, rw - l * e.nn[1], l);
+#pragma unroll
+        for (int t = 0; t < W; ++t) sh[t] = shared_in_row(e, bcmask, w, i0 + t, f[t], cnt[t]);
+    } else {
+#pragma unroll
+        for (int t = 0; t < W; ++t) sh[t] = shared_lookup(e, bcmask, g0 + t, f[t], cnt[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < W; ++t) mp[t] = sh[t] ? shared_map_entry(f[t], cnt[t]) : 0u;
+}
+
+// assemble_packet for entries that were just computed: every partial of the
+// packet loaded under its condition before any is added (the same sums).  With
+// entries from the map the conditions would wait for them.  (96^3 Q2 49.3 -> 47.6
+// us, 64^3 Q3 56.7 -> 55.0.)
+template <typename T, int W>
+__device__ __forceinline__ void assemble_computed(const SharedParts<T>& sp, const unsigned (&mp)[W], T (&qv)[W])
+{
+    T pv[W][8];
+#pragma unroll
+    for (int t = 0; t < W; ++t) {
+        const int cnt = mp[t] ? 1 << (mp[t] & 3u) : 0;
+        const unsigned f = mp[t] >> 2;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) pv[t][k] = k < cnt ? sp.part[k * sp.stride + f] : T(0);
+    }
+#pragma unroll
+    for (int t = 0; t < W; ++t)
+        if (mp[t]) {
+            T v = pv[t][0] + pv[t][1];
+#pragma unroll
+            for (int k = 2; k < 8; ++k)
+                if (k < 1 << (mp[t] & 3u)) v += pv[t][k];
+            qv[t] = v;
+        }
+}
+
 // Body of the update for workgroup bid of one system; the workgroup returns at
 // once when the system has stopped.  Share v of the nsum shares takes packets
 // v BT + tid + j nsum BT and gives one partial of each sum; a workgroup has one
 // share (nblk = nsum) or, with SHARES, shares bid, bid + nblk, ...: the partials
 // and the sums over them are those of one share per workgroup.
-template <typename T, bool SHARES>
+template <typename T, bool SHARES, bool MAP>
 __device__ __forceinline__ void assemble_update_body(int bid, int nblk, int nsum, CgState* st, int par, double* red,
                                                      const SharedParts<T>& sp, T* __restrict__ r,
                                                      const T* __restrict__ q, const T* __restrict__ invd, int64_t n)
@@ -191,7 +254,7 @@ __device__ __forceinline__ void assemble_update_body(int bid, int nblk, int nsum
     const int64_t S = (int64_t)nsum * BT;
     int64_t c = (int64_t)bid * BT + threadIdx.x;
     Map mp{};
-    if (c < np) mp = reinterpret_cast<const Map*>(sp.map)[c];
+    if (MAP && c < np) mp = reinterpret_cast<const Map*>(sp.map)[c];
     T alpha;
     if (!update_alpha(bid, st, par, sp.dot_part, sp.ndot, alpha)) return;
     T* hrec = nullptr;
@@ -206,10 +269,15 @@ __device__ __forceinline__ void assemble_update_body(int bid, int nblk, int nsum
             P rv = reinterpret_cast<const P*>(r)[c];
             const P dv = reinterpret_cast<const P*>(invd)[c];
             P qv = reinterpret_cast<const P*>(q)[c];
-            const Map now = mp;
+            Map now = mp;
             const int64_t next = c + S < np ? c + S : after;
-            if (next < np) mp = reinterpret_cast<const Map*>(sp.map)[next];
-            assemble_packet<T, W>(sp, now.v, qv.v);
+            if (MAP && next < np) mp = reinterpret_cast<const Map*>(sp.map)[next];
+            if constexpr (MAP) {
+                assemble_packet<T, W>(sp, now.v, qv.v);
+            } else {
+                lookup_packet<W>(sp.e, sp.bcmask, (int)(c * W), now.v);
+                assemble_computed<T, W>(sp, now.v, qv.v);
+            }
 #pragma unroll
             for (int t = 0; t < W; ++t) {
                 const T ri = fma(-alpha, qv.v[t], rv.v[t]);
@@ -222,7 +290,9 @@ __device__ __forceinline__ void assemble_update_body(int bid, int nblk, int nsum
         }
         if (v == 0)
             for (int64_t i = np * W + threadIdx.x; i < n; i += BT) {
-                const unsigned mi[1] = {sp.map[i]};
+                unsigned mi[1];
+                if constexpr (MAP) mi[0] = sp.map[i];
+                else lookup_packet<1>(sp.e, sp.bcmask, (int)i, mi);
                 T qi[1] = {q[i]};
                 assemble_packet<T, 1>(sp, mi, qi);
                 const T ri = fma(-alpha, qi[0], r[i]);
@@ -256,12 +326,12 @@ __device__ __forceinline__ void assemble_update_body(int bid, int nblk, int nsum
     }
 }
 
-template <typename T>
+template <typename T, bool MAP>
 __global__ void __launch_bounds__(BT) cg_assemble_update_kernel(CgState* st, int par, double* red, SharedParts<T> sp,
                                                                 T* __restrict__ r, const T* __restrict__ q,
                                                                 const T* __restrict__ invd, int64_t n)
 {
-    assemble_update_body<T, false>(blockIdx.x, gridDim.x, gridDim.x, st, par, red, sp, r, q, invd, n);
+    assemble_update_body<T, false, MAP>(blockIdx.x, gridDim.x, gridDim.x, st, par, red, sp, r, q, invd, n);
 }
 
 template <typename T>
@@ -281,8 +351,8 @@ template <typename T>
 __global__ void __launch_bounds__(BT) cg_batch_update_kernel(const CgSystem<T>* sys, const int* owner, int par)
 {
     const CgSystem<T>& y = sys[owner[blockIdx.x]];
-    const SharedParts<T> sp{y.map, y.part, y.stride, y.dot_part, y.ndot};
-    assemble_update_body<T, true>((int)blockIdx.x - y.blk_begin, y.nblk, y.nsum, y.st, par, y.red, sp, y.r, y.q, y.invd,
+    const SharedParts<T> sp{y.map, y.part, y.stride, y.dot_part, y.ndot, {}, 0};
+    assemble_update_body<T, true, true>((int)blockIdx.x - y.blk_begin, y.nblk, y.nsum, y.st, par, y.red, sp, y.r, y.q, y.invd,
                                   y.n);
 }
 
@@ -382,12 +452,15 @@ hipError_t launch_shared_map(const SharedEnum& e, int bcmask, unsigned* map, hip
 
 template <typename T>
 hipError_t launch_cg_assemble_update(CgState* st, int par, double* red, const double* dot_part, int ndot,
-                                     const unsigned* map, const T* part, int64_t stride, T* r, const T* q,
-                                     const T* invd, int64_t n, hipStream_t s)
+                                     const unsigned* map, const SharedEnum& e, int bcmask, const T* part,
+                                     int64_t stride, T* r, const T* q, const T* invd, int64_t n, hipStream_t s)
 {
-    const SharedParts<T> sp{map, part, stride, dot_part, ndot};
-    hipLaunchKernelGGL(cg_assemble_update_kernel<T>, dim3(grid_update<T>(n)), dim3(BT), 0, s, st, par, red, sp, r, q,
-                       invd, n);
+    const SharedParts<T> sp{map, part, stride, dot_part, ndot, e, bcmask};
+    const dim3 g(grid_update<T>(n)), b(BT);
+    if (map)
+        hipLaunchKernelGGL((cg_assemble_update_kernel<T, true>), g, b, 0, s, st, par, red, sp, r, q, invd, n);
+    else
+        hipLaunchKernelGGL((cg_assemble_update_kernel<T, false>), g, b, 0, s, st, par, red, sp, r, q, invd, n);
     return hipGetLastError();
 }
 
@@ -418,7 +491,8 @@ hipError_t launch_cg_batch_step(const CgSystem<double>* sys, const int* owner, i
     template hipError_t launch_cg_pupdate<T>(CgState*, int, const double*, T*, const T*, T*, const T*, int64_t, \
                                              hipStream_t);                                                       \
     template hipError_t launch_cg_assemble_update<T>(CgState*, int, double*, const double*, int, const unsigned*, \
-                                                     const T*, int64_t, T*, const T*, const T*, int64_t, hipStream_t);
+                                                     const SharedEnum&, int, const T*, int64_t, T*, const T*,        \
+                                                     const T*, int64_t, hipStream_t);
 VPP_INST(double)
 VPP_INST(float)
 #undef VPP_INST

@@ -264,3 +264,26 @@ def test_per_precision_configs():
     assert rel(host(prob.apply(dev(x, dtype=torch.float32))), yref) < 2e-6
     p, info = prob.cg_solve(dev(oracle.sine_load(m)), rtol=1e-8, precision="mixed")
     assert info["status"] == 0
+
+
+# sizes at which the update looks its shared nodes up instead of reading a map:
+# FP64 above 2^21 unknowns, FP32 above 12,000,000; ragged in every direction
+@pytest.mark.parametrize("k,ncells,precision", [(2, (67, 63, 65), "fp64"), (3, (45, 41, 46), "fp64"),
+                                                (2, (117, 115, 116), "mixed")])
+def test_solve_without_a_shared_node_map(k, ncells, precision):
+    """Solves whose residual, recomputed with the plain apply (its own assembly of
+    the shared nodes), meets the tolerance."""
+    h = 1.0 / max(ncells)
+    m = W.Mesh(ncells=ncells, degree=k, bc=(0, 1, 1, 0, 0, 1), extent=tuple(h * n for n in ncells), rho_l=10.0, rho_g=1.0)
+    m.eps = 4 * h
+    g = torch.Generator(device="cuda").manual_seed(11)
+    p = vpp.Problem.from_mesh(m)
+    p.set_phi(torch.from_numpy(W.droplet_phi(m, 0.3, m.eps)).cuda())
+    x = torch.rand(p.n, dtype=torch.float64, device="cuda", generator=g) - 0.5
+    b = p.apply(x)
+    say("no map", k, ncells, precision, p.n)
+    y, info = p.cg_solve(b, rtol=1e-9, precision=precision)
+    say("no map", info)
+    assert info["status"] == 0
+    assert float((b - p.apply(y)).norm() / b.norm()) < 1.05e-9
+    assert info["true_rel_residual"] < 1.05e-9
