@@ -420,7 +420,8 @@ int32_t vpp_abi_version(void);
 /* Bounds checks (no passage of the paper: a debugging aid for the index
  * arithmetic of the tile kernels).  The same sources also build
  * libvpp_debug.so with every global and LDS access of the apply tile kernels
- * (all variants, single and batched) and of the shared-node assembly checked
+ * (all variants, single and batched), of the reinitialization operator's tiles,
+ * of the refined mesh's cell kernels and of the shared-node assembly checked
  * against the extent of the buffer it belongs to; an access outside is
  * counted and dropped (a load yields zero), so kernels still complete.
  * Returns the count since the previous call and resets it (synchronizes the

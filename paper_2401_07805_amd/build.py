@@ -19,7 +19,7 @@ SOURCES = [*APPLY_UNITS, "apply_f64.hip", "apply_f32.hip", "apply_misc.hip", "bl
 # the sources whose code changes under VPP_BOUNDS_CHECK (the instrumented
 # kernels and the entry point that reads their counters); the debug library
 # links the release objects of the others
-DEBUG_SOURCES = [*APPLY_UNITS, "apply_misc.hip", "api.cpp"]
+DEBUG_SOURCES = [*APPLY_UNITS, "apply_misc.hip", "reinit.hip", "amr.hip", "api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-munsafe-fp-atomics",

@@ -108,6 +108,9 @@ __global__ void __launch_bounds__(256) amr_coef_kernel(AmrArgs a, const double* 
     using G = typename AmrGeo<K>::G;
     constexpr int N = G::N, N2 = N * N;
     __shared__ double buf[G::NG * G::GB];
+    // a.coef stands in the partials' place of the table
+    VPP_BC_BEGIN((const double*)nullptr, (const double*)nullptr, phi, a.coef, (const double*)nullptr, buf, a.n,
+                 (int64_t)gridDim.x * N2 * 256, 0, G::NG * G::GB);
     const AmrThread<K> th;
     double cw[N2];
     const bool in = th.e < a.ncells;
@@ -119,7 +122,7 @@ __global__ void __launch_bounds__(256) amr_coef_kernel(AmrArgs a, const double* 
 #pragma unroll
         for (int l = 0; l < N; ++l)
 #pragma unroll
-            for (int j = 0; j < N; ++j) cw[j + N * l] = phi[base + nx * j + nxy * l];
+            for (int j = 0; j < N; ++j) cw[j + N * l] = VPP_LD(&phi[base + nx * j + nxy * l], BC_PHI);
     } else {
 #pragma unroll
         for (int q = 0; q < N2; ++q) cw[q] = 0.0;
@@ -137,7 +140,7 @@ __global__ void __launch_bounds__(256) amr_coef_kernel(AmrArgs a, const double* 
 #pragma unroll
     for (int q = 0; q < N2; ++q) {
         const double c = coef_scaled<HV>(m, cw[q]) * (wz * (Tab<K>::t.w[q % N] * Tab<K>::t.w[q / N]));
-        a.coef[((size_t)blockIdx.x * N2 + q) * 256 + threadIdx.x] = in ? c : 0.0;
+        VPP_ST(&a.coef[((size_t)blockIdx.x * N2 + q) * 256 + threadIdx.x], BC_PART, in ? c : 0.0);
     }
 }
 
@@ -150,6 +153,9 @@ __global__ void __launch_bounds__(256) amr_cells_kernel(AmrArgs a, const double*
     using G = typename AmrGeo<K>::G;
     constexpr int N = G::N, N2 = N * N;
     __shared__ double buf[G::NG * G::GB];
+    // the packed vector as x, the result slots in the partials' place
+    VPP_BC_BEGIN(ext, (const double*)nullptr, (const double*)nullptr, a.scratch, dot_part, buf,
+                 (int64_t)a.nfree + a.ncon + 2, (int64_t)gridDim.x * N2 * 256, (int64_t)gridDim.x, G::NG * G::GB);
     if (done && *done) return;
     const AmrThread<K> th;
     const size_t at = (size_t)blockIdx.x * N2 * 256 + threadIdx.x;
@@ -160,22 +166,22 @@ __global__ void __launch_bounds__(256) amr_cells_kernel(AmrArgs a, const double*
 #pragma unroll
     for (int q = 0; q < N2; ++q) cw[q] = a.coef[at + (size_t)q * 256];
 #pragma unroll
-    for (int q = 0; q < N2; ++q) u[q] = ext[idx[q]];
+    for (int q = 0; q < N2; ++q) u[q] = VPP_LD(&ext[idx[q]], BC_X);
     // the spacing ratios of both lattices are the same
     plane_operator<G, K, double, false>(a.mc, buf + th.offx, buf + th.offz, cw, 0.0, u);
     double d = 0.0;
     if (!th.spare) {
 #pragma unroll
-        for (int q = 0; q < N2; ++q) a.scratch[at + (size_t)q * 256] = u[q];
+        for (int q = 0; q < N2; ++q) VPP_ST(&a.scratch[at + (size_t)q * 256], BC_PART, u[q]);
         if constexpr (DOT) {
             // gathered again: held across the operator they cost a wave per SIMD
 #pragma unroll
-            for (int q = 0; q < N2; ++q) d = fma(ext[a.cidx[at + (size_t)q * 256]], u[q], d);
+            for (int q = 0; q < N2; ++q) d = fma(VPP_LD(&ext[a.cidx[at + (size_t)q * 256]], BC_X), u[q], d);
         }
     }
     if constexpr (DOT) {
         const double sum = block_sum<256>(d);
-        if (threadIdx.x == 0) dot_part[blockIdx.x] = sum;
+        if (threadIdx.x == 0) VPP_ST(&dot_part[blockIdx.x], BC_DOT, sum);
     }
 }
 
@@ -556,6 +562,8 @@ static int stream_blocks(int64_t n)
     case 19: hipLaunchKernelGGL((KERNEL<4, 3>), dim3(blocks), dim3(64), 0, s, a, __VA_ARGS__); break;   \
     default: return hipErrorInvalidValue;                                                                 \
     }
+
+unsigned long long bounds_count_amr() { return bc_count_here(); }
 
 int amr_cells_per_block(int k) { return k == 2 ? AmrGeo<2>::CB : (k == 3 ? AmrGeo<3>::CB : AmrGeo<4>::CB); }
 

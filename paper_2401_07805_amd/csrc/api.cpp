@@ -1074,10 +1074,10 @@ int64_t vpp_debug_bounds_violations(void)
 {
 #ifdef VPP_BOUNDS_CHECK
     if (hipDeviceSynchronize() != hipSuccess) return -2;
-    const unsigned long long c[7] = {bounds_count_apply_f64_k2(), bounds_count_apply_f64_k3(),
+    const unsigned long long c[9] = {bounds_count_apply_f64_k2(), bounds_count_apply_f64_k3(),
                                      bounds_count_apply_f64_k4(), bounds_count_apply_f32_k2(),
                                      bounds_count_apply_f32_k3(), bounds_count_apply_f32_k4(),
-                                     bounds_count_misc()};
+                                     bounds_count_misc(), bounds_count_reinit(), bounds_count_amr()};
     int64_t n = 0;
     for (unsigned long long v : c) {
         if (v == ~0ull) return -2;

@@ -7,7 +7,8 @@
 // to.  An access outside adds one to a device counter and is dropped (a load
 // yields zero), so the kernel still completes normally and the host reads the
 // count through vpp_debug_bounds_violations.  Instrumented: the tile kernels
-// of every apply variant and the shared-node assembly.
+// of every apply variant and of the reinitialization operator, the refined
+// mesh's cell kernels, and the shared-node assembly.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -16,9 +17,10 @@
 
 namespace vpp {
 
-// Buffers of the table; BC_IN accepts x or phi (the gathers serve both), BC_OUT
-// y or the partials (a write-out whose destination is chosen per node).
-enum BcBuf { BC_X = 0, BC_Y, BC_PHI, BC_PART, BC_DOT, BC_SLOT, BC_NBUF, BC_IN = BC_NBUF, BC_OUT };
+// Buffers of the table (BC_N0 - BC_N2: three more input fields, VPP_BC_FIELDS);
+// BC_IN accepts x or phi (the gathers serve both), BC_OUT y or the partials (a
+// write-out whose destination is chosen per node).
+enum BcBuf { BC_X = 0, BC_Y, BC_PHI, BC_PART, BC_DOT, BC_SLOT, BC_N0, BC_N1, BC_N2, BC_NBUF, BC_IN = BC_NBUF, BC_OUT };
 
 #ifdef VPP_BOUNDS_CHECK
 
@@ -68,6 +70,19 @@ __device__ __forceinline__ void bc_begin(const T* x, const T* y, const T* phi, c
     __syncthreads();
 }
 
+// The fields f0 - f2 (n values each), after bc_begin; every thread calls it.
+__device__ __forceinline__ void bc_fields(const double* f0, const double* f1, const double* f2, int64_t n)
+{
+    if (threadIdx.x == 0) {
+        const double* f[3] = {f0, f1, f2};
+        for (int d = 0; d < 3; ++d) {
+            bc_table.lo[BC_N0 + d] = reinterpret_cast<const char*>(f[d]);
+            bc_table.hi[BC_N0 + d] = reinterpret_cast<const char*>(f[d] + n);
+        }
+    }
+    __syncthreads();
+}
+
 // Count of dropped accesses of this translation unit's kernels since the last
 // call (the counter is reset).
 static inline unsigned long long bc_take_count()
@@ -90,6 +105,7 @@ static inline unsigned long long bc_count_here() { return bc_take_count(); }
     } while (0)
 #define VPP_BC_BEGIN(x, y, phi, part, dot, slot, n, npart, ndot, nslot) \
     ::vpp::bc_begin((x), (y), (phi), (part), (dot), (slot), (n), (npart), (ndot), (nslot))
+#define VPP_BC_FIELDS(f0, f1, f2, n) ::vpp::bc_fields((f0), (f1), (f2), (n))
 #define VPP_BC_SYNC() __syncthreads()
 
 #else
@@ -100,6 +116,7 @@ static inline unsigned long long bc_count_here() { return 0; }
 #define VPP_LD(p, b) (*(p))
 #define VPP_ST(p, b, v) (*(p) = (v))
 #define VPP_BC_BEGIN(x, y, phi, part, dot, slot, n, npart, ndot, nslot) ((void)0)
+#define VPP_BC_FIELDS(f0, f1, f2, n) ((void)0)
 #define VPP_BC_SYNC() ((void)0)
 
 #endif

@@ -71,6 +71,8 @@ unsigned long long bounds_count_apply_f32_k2();
 unsigned long long bounds_count_apply_f32_k3();
 unsigned long long bounds_count_apply_f32_k4();
 unsigned long long bounds_count_misc();
+unsigned long long bounds_count_reinit();
+unsigned long long bounds_count_amr();
 int list_apply_configs(int k, LaunchCfg* out, int cap);
 // Configurations instantiated with the mass shift (a problem with mu != 0 runs these only).
 bool mass_config_supported(const LaunchCfg& c, int k);

@@ -22,7 +22,7 @@ namespace vpp {
 namespace {
 
 // This thread's z-plane of the nodal field f at the Gauss points.
-template <int K, int TX, int TY, int TZ>
+template <BcBuf F, int K, int TX, int TY, int TZ>
 __device__ __forceinline__ void field_at_gauss(const PlaneThread<K, TX, TY, TZ>& th, const MeshArgs& m,
                                                const double* __restrict__ f, double* px, double* pz,
                                                double (&v)[(K + 1) * (K + 1)])
@@ -30,7 +30,7 @@ __device__ __forceinline__ void field_at_gauss(const PlaneThread<K, TX, TY, TZ>&
     using G = PlaneGeo<K, TX, TY, TZ>;
     constexpr int N2 = G::N * G::N;
     if (th.in) {
-        th.template load<BC_X>(m, f, v);
+        th.template load<F>(m, f, v);
     } else {
 #pragma unroll
         for (int q = 0; q < N2; ++q) v[q] = 0.0;
@@ -50,8 +50,11 @@ __global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) reinit_plane_k
     using G = PlaneGeo<K, TX, TY, TZ>;
     constexpr int N = G::N, N2 = N * N;
     __shared__ double buf[G::NG * G::GB];
-    if (a.done && *a.done) return;
     const MeshArgs& m = a.r.g.m;
+    VPP_BC_BEGIN(a.x, a.y, (const double*)nullptr, a.part, a.dot_part, buf, (int64_t)m.nn[0] * m.nn[1] * m.nn[2],
+                 8 * a.nshared, (int64_t)gridDim.x, G::NG * G::GB);
+    VPP_BC_FIELDS(a.r.n0, a.r.n1, a.r.n2, (int64_t)m.nn[0] * m.nn[1] * m.nn[2]);
+    if (a.done && *a.done) return;
     const PlaneThread<K, TX, TY, TZ> th(m, xcd_tile(blockIdx.x, gridDim.x));
     double* const px = buf + th.offx;
     double* const pz = buf + th.offz;
@@ -62,9 +65,9 @@ __global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) reinit_plane_k
     for (int i = 0; i < N; ++i)
         if (th.ip == i) wz = Tab<K>::t.w[i];
     double n0[N2], n1[N2], n2[N2];
-    field_at_gauss<K, TX, TY, TZ>(th, m, a.r.n0, px, pz, n0);
-    field_at_gauss<K, TX, TY, TZ>(th, m, a.r.n1, px, pz, n1);
-    field_at_gauss<K, TX, TY, TZ>(th, m, a.r.n2, px, pz, n2);
+    field_at_gauss<BC_N0, K, TX, TY, TZ>(th, m, a.r.n0, px, pz, n0);
+    field_at_gauss<BC_N1, K, TX, TY, TZ>(th, m, a.r.n1, px, pz, n1);
+    field_at_gauss<BC_N2, K, TX, TY, TZ>(th, m, a.r.n2, px, pz, n2);
 
     // u and its z derivative on the x-planes, both turned
     double u[N2], s[N2];
@@ -173,7 +176,7 @@ __global__ void __launch_bounds__((PlaneGeo<K, TX, TY, TZ>::NTH)) reinit_plane_k
     const double d = flush_plane<K, double, TX, TY, TZ>(m, th, buf, u, a.x, a.y, a.part, a.nshared, DOT);
     if constexpr (DOT) {
         const double sum = block_sum<G::NTH>(d);
-        if (threadIdx.x == 0) a.dot_part[blockIdx.x] = sum;
+        if (threadIdx.x == 0) VPP_ST(&a.dot_part[blockIdx.x], BC_DOT, sum);
     }
 }
 
@@ -188,6 +191,8 @@ hipError_t launch_reinit_tiles(const ReinitApplyArgs& a, hipStream_t s)
 }
 
 }  // namespace
+
+unsigned long long bounds_count_reinit() { return bc_count_here(); }
 
 int reinit_dot_partials(int k, const MeshArgs& m)
 {

@@ -150,3 +150,91 @@ def test_bounds_checked_kernels_stay_in_bounds():
     assert res["cases"] > 0
     assert res["violations"] == 0
     assert res["max_rel"] < 1e-13
+
+
+CHILD_TILES = r"""
+import json, sys
+import numpy as np
+import torch
+sys.path.insert(0, ROOT)
+import oracle
+import oracle.amr as amr
+import workloads as W
+import paper_2401_07805_amd as vpp
+from paper_2401_07805_amd import _lib as L
+
+lib = L.load()
+assert L.LIB_PATH.endswith("libvpp_debug.so"), L.LIB_PATH
+dev = torch.device("cuda", 0)
+out = {"cases": 0, "violations": 0, "max_rel": 0.0}
+
+def check(tag):
+    v = int(lib.vpp_debug_bounds_violations())
+    print(tag, "violations", v, flush=True)
+    assert v >= 0, v
+    out["violations"] += v
+    out["cases"] += 1
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+# reinitialization: one below, at and above the tiles 8x4x2, 4x4x2, 4x3x2, several
+# tiles, and the 4x4x4 tile of k = 3 meshes above 50,000 cells (too large for the matrix)
+for k, shape in [(2, (7, 3, 1)), (2, (8, 4, 2)), (2, (17, 9, 5)), (3, (5, 3, 1)), (3, (4, 4, 2)), (3, (9, 5, 3)),
+                 (3, (41, 37, 34)), (4, (3, 4, 1)), (4, (4, 3, 2)), (4, (9, 4, 5))]:
+    m = W.Mesh(ncells=shape, degree=k, bc=(0, 1, 0, 0, 1, 0), extent=(1.0, 0.9, 1.2))
+    normal = W.normal_field(m, (0.47, 0.52, 0.5))
+    x = W.uniform_vectors(6, 1, m.ndofs)[0]
+    p = vpp.Problem.from_mesh(m)
+    nd = [torch.from_numpy(c).to(dev) for c in normal]
+    xd = torch.from_numpy(x).to(dev)
+    y = p.reinit_apply(xd, nd, 0.08, 0.05).cpu().numpy()
+    check(f"reinit k={k} {shape} apply")
+    if m.ndofs < 100000:
+        out["max_rel"] = max(out["max_rel"], rel(y, oracle.reinit_matrix(m, normal, 0.08, 0.05) @ x))
+    p.reinit_step(xd, nd, 0.08, 0.05, max_iter=20, raise_on_failure=False)
+    check(f"reinit k={k} {shape} step")
+# refined meshes: cell counts below, at and above the cell groups, refined and not
+for k, nc, nref in [(2, (7, 4, 3), 0), (2, (7, 3, 2), 6), (2, (5, 4, 3), 60), (3, (4, 4, 4), 1), (3, (3, 2, 1), 6),
+                    (4, (4, 4, 3), 0), (4, (3, 3, 2), 5)]:
+    mask = np.zeros(int(np.prod(nc)), dtype=np.uint8)
+    mask[np.random.default_rng(3).permutation(mask.size)[:nref]] = 1
+    m = W.Mesh(ncells=nc, degree=k, bc=(0, 1, 1, 0, 1, 1), rho_l=1000.0, rho_g=1.0)
+    m.eps = 0.1
+    c = amr.node_coords(m)
+    phi = np.tanh((0.3 - np.sqrt(sum((a - .5) ** 2 for a in c))) / (2 * m.eps))
+    p = vpp.AmrProblem(m.ncells, m.degree, mask, m.origin, m.extent, m.bc, m.rho_l, m.rho_g)
+    p.set_phi(torch.from_numpy(phi).to(dev))
+    check(f"amr k={k} {nc} {nref} set_phi")
+    x = np.random.default_rng(4).uniform(-1, 1, p.n)
+    y = p.apply(torch.from_numpy(x).to(dev))
+    check(f"amr k={k} {nc} {nref} apply")
+    out["max_rel"] = max(out["max_rel"], rel(y.cpu().numpy(), amr.operator(m, mask, phi)[0] @ x))
+    p.cg_solve(y, rtol=1e-8, max_iter=20, raise_on_failure=False)
+    check(f"amr k={k} {nc} {nref} cg")
+print("RESULT", json.dumps(out), flush=True)
+"""
+
+
+def test_bounds_checked_reinitialization_and_refined_mesh():
+    """The tile kernels of the reinitialization operator and the cell kernels of the
+    refined mesh under the same checks, against the oracle (1e-12)."""
+    env = dict(os.environ, VPP_DEBUG_BOUNDS="1")
+    proc = subprocess.run([sys.executable, "-u", "-c", "ROOT = %r\n" % ROOT + CHILD_TILES], env=env,
+                          capture_output=True, text=True, timeout=600)
+    print(proc.stdout[-6000:], proc.stderr[-4000:])
+    assert proc.returncode == 0, proc.stderr[-4000:]
+    res = json.loads(proc.stdout.split("RESULT", 1)[1])
+    assert res["cases"] == 41 and res["violations"] == 0
+    assert res["max_rel"] < 1e-12
+
+
+def test_instrumented_sources_are_built_with_the_checks():
+    """Every source that reads the bounds counter of its kernels is compiled for
+    the debug library with the checks on."""
+    from paper_2401_07805_amd import build
+    src = os.path.join(ROOT, "paper_2401_07805_amd", "csrc")
+    counted = {f for f in os.listdir(src) if f.endswith(".hip") and "bc_count_here()" in open(os.path.join(src, f)).read()}
+    counted |= {f for f in os.listdir(src) if f.endswith(".hip") and "VPP_BC_BEGIN" in open(os.path.join(src, f)).read()}
+    assert {"reinit.hip", "amr.hip", "apply_misc.hip"} <= counted
+    assert counted <= set(build.DEBUG_SOURCES)
