@@ -2309,6 +2309,8 @@ static vpp_status tune_precision(vpp_problem p, int prec, const char* cache_path
     };
     for (int i = 0; i < n && !st; ++i) {
         if (!config_fits(p, prec, cands[i])) continue;
+        // 8x4x4 at k = 3 is listed as variants 4 and 1: timed once
+        if (std::any_of(cands, cands + i, [&](const LaunchCfg& c) { return same_kernel(p->k, c, cands[i]); })) continue;
         put_config(p, prec, cands[i]);
         if ((st = ensure_apply_scratch(p))) break;
         if ((st = one())) break;

@@ -51,8 +51,8 @@ namespace vpp {
     X(4, 1, 6, 4, 2)
 
 // Configurations also instantiated with the arithmetic density mean (laws 2
-// and 3 of coef_scaled; the contrast of App. D): one per degree, the default
-// configuration of a new problem.
+// and 3 of coef_scaled; the contrast of App. D): one per degree, which every
+// problem with that law runs.
 #define VPP_ARITH_CONFIGS(X) \
     X(2, 4, 8, 8, 4)         \
     X(3, 1, 4, 4, 2)         \

@@ -27,7 +27,7 @@ struct ApplyArgs {
 // Per-problem launch configuration.
 struct LaunchCfg {
     int variant;        // 0 cell per thread (LDS atomics), 1 plane per thread, 2 half cell per thread (k = 3),
-                        // 4 cell per thread (LDS slots)
+                        // 4 cell per thread (LDS slots), at k = 3 plane per thread as 1
     int tile[3];
 };
 

@@ -14,11 +14,21 @@ inline void set_tiles(MeshArgs& m, const LaunchCfg& c)
 
 inline int64_t tile_count64(const MeshArgs& m) { return (int64_t)m.ntile[0] * m.ntile[1] * m.ntile[2]; }
 
+// Whether c runs the plane-per-thread kernel (plane_per_thread in apply_configs.h).
+inline bool plane_variant(int k, const LaunchCfg& c) { return c.variant == 1 || (c.variant == 4 && k == 3); }
+
+// Whether two configurations of degree k are the same kernel under two names.
+inline bool same_kernel(int k, const LaunchCfg& a, const LaunchCfg& b)
+{
+    return a.tile[0] == b.tile[0] && a.tile[1] == b.tile[1] && a.tile[2] == b.tile[2] &&
+           (a.variant == b.variant || (plane_variant(k, a) && plane_variant(k, b)));
+}
+
 // Threads of a workgroup of configuration c.
 inline int tile_threads(int k, const LaunchCfg& c)
 {
     const int cells = c.tile[0] * c.tile[1] * c.tile[2];
-    if (c.variant == 1 || (c.variant == 4 && k == 3)) {   // plane per thread (PlaneGeo)
+    if (plane_variant(k, c)) {   // PlaneGeo
         if (k == 2) return 3 * cells;
         const int per_wave = 64 / (k + 1);
         return 64 * ((cells + per_wave - 1) / per_wave);

@@ -116,6 +116,11 @@ int main()
            default_config(3, true, mesh(3, 2576, 2576, 4)));
     expect(!tiles_fit(3, mesh(3, 2576, 2576, 4), {1, {8, 4, 4}}, 8), "8x4x4 refused", 3, mesh(3, 2576, 2576, 4), {1, {8, 4, 4}});
     expect(!tiles_fit(4, mesh(4, 2048, 2048, 3), {1, {4, 4, 3}}, 8), "4x4x3 refused", 4, mesh(4, 2048, 2048, 3), {1, {4, 4, 3}});
+    // one kernel under two names
+    expect(same_kernel(3, {4, {8, 4, 4}}, {1, {8, 4, 4}}), "same kernel", 3, mesh(3, 1, 1, 1), {1, {8, 4, 4}});
+    expect(!same_kernel(2, {4, {8, 4, 2}}, {1, {8, 4, 2}}), "not the same", 2, mesh(2, 1, 1, 1), {1, {8, 4, 2}});
+    expect(!same_kernel(3, {2, {8, 4, 4}}, {1, {8, 4, 4}}), "not the same", 3, mesh(3, 1, 1, 1), {2, {8, 4, 4}});
+    expect(!same_kernel(3, {1, {4, 4, 2}}, {1, {4, 4, 4}}), "not the same", 3, mesh(3, 1, 1, 1), {1, {4, 4, 4}});
     // thin boxes by their extent
     expect(default_config(3, false, mesh(3, 400, 400, 1)).tile[2] == 2, "thin z", 3, mesh(3, 400, 400, 1), default_config(3, false, mesh(3, 400, 400, 1)));
     expect(default_config(3, false, mesh(3, 1, 200, 200)).tile[0] == 4, "thin x", 3, mesh(3, 1, 200, 200), default_config(3, false, mesh(3, 1, 200, 200)));
