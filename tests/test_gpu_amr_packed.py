@@ -69,3 +69,27 @@ def test_solve_with_identity_rows(k, identity):
     _, it = amr.pcg(A, b, rtol=1e-10)
     _, i0 = p.cg_solve(dev(b), rtol=1e-10)
     assert abs(i0["iterations"] - it) <= 2
+
+
+@pytest.mark.parametrize("k,nc,most", [(2, (16, 14, 15), 1000), (3, (9, 8, 10), 1200)])
+def test_attained_residual(k, nc, most):
+    """The constrained values of the search direction follow their own recurrence for
+    the whole solve.  Run far past convergence, it leaves no more than rounding: the
+    residual of the returned solution within 64 units of 2^-53 (a row's products)
+    and the known solution within 1e-13."""
+    mask = np.zeros(int(np.prod(nc)), dtype=np.uint8)
+    c = [(np.arange(n) + 0.5) / n for n in nc]
+    z, y, x = np.meshgrid(c[2], c[1], c[0], indexing="ij")
+    mask[np.abs(np.sqrt((x - .5) ** 2 + (y - .5) ** 2 + (z - .5) ** 2) - 0.3).ravel() < 0.15] = 1
+    m = W.Mesh(ncells=nc, degree=k, bc=(0,) * 6, rho_l=1000.0, rho_g=1.0)
+    m.eps = 0.1
+    g = amr.node_coords(m)
+    p = vpp.AmrProblem(m.ncells, m.degree, mask, m.origin, m.extent, m.bc, m.rho_l, m.rho_g)
+    p.set_phi(dev(np.tanh((0.3 - np.sqrt(sum((a - .5) ** 2 for a in g))) / (2 * m.eps))))
+    xs = np.random.default_rng(6).uniform(-1, 1, p.n)
+    b = p.apply(dev(xs))
+    say("amr attained", k, nc, p.n, p.nfree)
+    u, info = p.cg_solve(b, rtol=1e-200, max_iter=most, raise_on_failure=False)
+    say("amr attained", info)
+    assert info["true_rel_residual"] < 64 * 2.0 ** -53
+    assert rel(host(u), xs) < 1e-13
