@@ -151,15 +151,24 @@ inline LaunchCfg default_config(int k, bool f32, const MeshArgs& m)
 }
 
 // The same with the mass shift, where the configuration in use has no kernel with
-// it.  PCG iteration, us: k = 2, 16^3 cells 16.9 with 8x4x4 against 18.9 with
-// 16x8x4, 32^3 20.7 against 23.1, 40^3 27.5 against 27.1, 48^3 33.6 against 31.5;
+// it.  PCG iteration, us: k = 2, 8x4x4 while its tiles are about one a CU (16^3
+// cells 16.9 against 18.9 with 16x8x4, 32^3 19.6 against 22.0, 50x12x50 22.3 against
+// 27.3), then 16x8x4 (33^3 24.4 and 23.7, 100x2x100 22.5 and 21.1, 48^3 33.6 and
+// 31.5), except on a thin box that it pads a quarter more with several tiles a CU
+// (1x190x190 43.1 against 74.1, 300x2x300 66.4 against 89.8, 24x90x90 52.2 against
+// 62.9; 190x190x1, as many slots either way, 30.4 and 29.4);
 // k = 3, 4x4x4 until 64^3 cells (8^3 19.2 against 21.8 with 8x4x4, 24^3 25.0 against
 // 27.8, 48^3 83.4 against 86.5, 64^3 202 against 200).  k = 4 as without: its tiles
 // have both kernels (32^3: 4x4x3 65.6 against 71.8 with 4x3x2).
 inline LaunchCfg mass_default_config(int k, bool f32, const MeshArgs& m)
 {
     const int64_t ncell = cell_count(m);
-    if (k == 2) return ncell <= 40000 ? LaunchCfg{4, {8, 4, 4}} : LaunchCfg{4, {16, 8, 4}};
+    if (k == 2) {
+        const LaunchCfg small{4, {8, 4, 4}}, wide{4, {16, 8, 4}};
+        const int64_t pad = padded_cells(m, small), wide_pad = padded_cells(m, wide);
+        const bool thin = wide_pad > 256 * 16 * 8 * 4 && 4 * wide_pad > 5 * pad;
+        return pad <= 300 * 8 * 4 * 4 || thin || !tiles_fit(k, m, wide, f32 ? 4 : 8) ? small : wide;
+    }
     if (k == 3) return ncell <= 200000 ? LaunchCfg{4, {4, 4, 4}} : LaunchCfg{4, {8, 4, 4}};
     const LaunchCfg c[3] = {default_config(k, f32, m), {1, {4, 3, 2}}, {1, {4, 2, 2}}};
     const int first = c[0].tile[2] == 1 ? 1 : 0;   // 4x4x1 has no kernel with the mass shift

@@ -116,6 +116,11 @@ int main()
            default_config(3, true, mesh(3, 2576, 2576, 4)));
     expect(!tiles_fit(3, mesh(3, 2576, 2576, 4), {1, {8, 4, 4}}, 8), "8x4x4 refused", 3, mesh(3, 2576, 2576, 4), {1, {8, 4, 4}});
     expect(!tiles_fit(4, mesh(4, 2048, 2048, 3), {1, {4, 4, 3}}, 8), "4x4x3 refused", 4, mesh(4, 2048, 2048, 3), {1, {4, 4, 3}});
+    // mass shift at k = 2: by the tiles of 8x4x4, thin boxes by padding
+    expect(mass_default_config(2, false, mesh(2, 32, 32, 32)).tile[0] == 8, "mass", 2, mesh(2, 32, 32, 32), mass_default_config(2, false, mesh(2, 32, 32, 32)));
+    expect(mass_default_config(2, false, mesh(2, 48, 48, 48)).tile[0] == 16, "mass", 2, mesh(2, 48, 48, 48), mass_default_config(2, false, mesh(2, 48, 48, 48)));
+    expect(mass_default_config(2, false, mesh(2, 190, 190, 1)).tile[0] == 16, "mass", 2, mesh(2, 190, 190, 1), mass_default_config(2, false, mesh(2, 190, 190, 1)));
+    expect(mass_default_config(2, false, mesh(2, 1, 190, 190)).tile[0] == 8, "mass", 2, mesh(2, 1, 190, 190), mass_default_config(2, false, mesh(2, 1, 190, 190)));
     // one kernel under two names
     expect(same_kernel(3, {4, {8, 4, 4}}, {1, {8, 4, 4}}), "same kernel", 3, mesh(3, 1, 1, 1), {1, {8, 4, 4}});
     expect(!same_kernel(2, {4, {8, 4, 2}}, {1, {8, 4, 2}}), "not the same", 2, mesh(2, 1, 1, 1), {1, {8, 4, 2}});
