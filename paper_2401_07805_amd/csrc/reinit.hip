@@ -8,8 +8,9 @@
 //
 // What bounds it: vector instructions (four fields interpolated per apply) at
 // two waves per SIMD (k = 3: 96 values per thread live).  The one-cell-per-
-// thread kernel it replaces kept 4 (k+1)^3 values per lane, spilled at k = 3
-// and 4, and wrote (k+1)^3 results per cell to memory for a second kernel to
+// thread kernel (levelset.hip, kept for meshes that the tiles would mostly pad
+// or not address: reinit_config) holds 4 (k+1)^3 values per lane, spills at k = 3
+// and 4, and writes (k+1)^3 results per cell to memory for a second kernel to
 // sum; here the cells of a tile are summed in LDS and only the tile faces go
 // through partials, which the CG update assembles.  Operator per iteration of
 // the step, both launches before, us: 40x36x27 Q3 133 -> 28, 64^3 Q2 75 -> 45;
