@@ -260,9 +260,6 @@ static MeshArgs make_mesh_args(const vpp_desc& d)
     return m;
 }
 
-// Scratch of the apply for the current configurations of both precisions: the
-// partials of shared-face nodes (8 ranks x shared nodes, FP64-sized) and one
-// partial dot product per tile.
 // Scratch of `need` doubles: the cell-major arrays (cell_values entries each) of
 // the kernels that sum per-cell contributions into the nodes (dJ/dphi, the
 // filter right-hand sides, the reinitialization's diagonal and right-hand side)
@@ -298,6 +295,9 @@ static vpp_status cell_scratch_end(vpp_problem p, hipStream_t s)
     return VPP_OK;
 }
 
+// Scratch of the apply for the current configurations of both precisions: the
+// partials of shared-face nodes (8 ranks x shared nodes, FP64-sized) and one
+// partial dot product per tile.
 static vpp_status ensure_apply_scratch(vpp_problem p)
 {
     const int64_t ns = std::max(shared_stride(p->m), shared_stride(p->m32));
@@ -1493,8 +1493,15 @@ static ReinitArgs reinit_geometry(vpp_problem p, const double* n0, const double*
 
 // Doubles of scratch of the operator: partials of the shared nodes, or the cells'
 // results where it runs one cell per thread; then the partials of x . y.
-static int64_t reinit_parts(int k, const MeshArgs& m) { return reinit_config(k, m).variant == 1 ? 8 * shared_stride(m) : cell_values(k, m); }
-static size_t reinit_scratch(int k, const MeshArgs& m) { return (size_t)(reinit_parts(k, m) + reinit_dot_partials(k, m)); }
+static int64_t reinit_parts(int k, const MeshArgs& m)
+{
+    return reinit_config(k, m).variant == 1 ? 8 * shared_stride(m) : cell_values(k, m);
+}
+
+static size_t reinit_scratch(int k, const MeshArgs& m)
+{
+    return (size_t)(reinit_parts(k, m) + reinit_dot_partials(k, m));
+}
 
 vpp_status vpp_reinit_step(vpp_problem p, const double* psi, const double* n0, const double* n1, const double* n2,
                            const vpp_reinit_opts* o, double* psi_out, vpp_cg_info* info, void* stream)
@@ -2494,7 +2501,8 @@ static vpp_status batch_tune(vpp_batch b, const char* cache_path)
     int nc = 0;
     for (int i = 0; i < na; ++i)
         if (batch_fits(b, all[i])) cands[nc++] = all[i];
-    if (nc == 0) st = na == 0 ? fail(VPP_ERR_UNSUPPORTED, "no batch kernel configuration for this degree") : tiles_out_of_reach();
+    if (na == 0) st = fail(VPP_ERR_UNSUPPORTED, "no batch kernel configuration for this degree");
+    else if (nc == 0) st = tiles_out_of_reach();
     double best = 1e300;
     LaunchCfg best_cfg = nc ? cands[0] : LaunchCfg{4, {8, 8, 4}};
     hipEvent_t e0 = nullptr, e1 = nullptr;

@@ -64,16 +64,16 @@ static int grid_update(int64_t n)
 
 // Workgroups of the search-direction update, whose threads take their packets
 // in batches of kBatch: two per CU while a batch covers the vector (48^3 Q2 8.3
-// us, with four 8.7), then four (64^3 15.9 us, with two 17.2), above 2 10^7
-// unknowns in whole batches (96^3 Q3 245 us against 266, FP32 93 against 97; below,
-// 88^3 Q2 43.3 against 41.4 and 128^3 Q2 FP32 68 against 64).
+// us, with four 8.7), then four (64^3 15.9 us, with two 17.2); above 2 10^7
+// unknowns as many as give every thread whole batches (96^3 Q3 245 us, FP32 93, against
+// 266 and 97 with four; 88^3 Q2 43.3 against 41.4, 128^3 Q2 FP32 68 against 64).
 template <typename T>
 static int grid_pupdate(int64_t n)
 {
     const int64_t per = (int64_t)BT * Pack<T>::W;
     const int64_t all = std::max<int64_t>(1, (n + per - 1) / per);   // workgroups at one packet per thread
     if (all <= 512 * kBatch) return (int)std::min<int64_t>(all, 512);
-    if (n <= 20000000) return (int)std::min<int64_t>(all, 1024);
+    if (n <= 20000000) return 1024;
     const int64_t its = ((all + 1023) / 1024 + kBatch - 1) / kBatch * kBatch;
     return (int)((all + its - 1) / its);
 }

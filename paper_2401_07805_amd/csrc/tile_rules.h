@@ -192,7 +192,8 @@ inline LaunchCfg mass_default_config(int k, bool f32, const MeshArgs& m)
 inline LaunchCfg reinit_config(int k, const MeshArgs& m)
 {
     const LaunchCfg cells{0, {m.nc[0], m.nc[1], m.nc[2]}};
-    const LaunchCfg c[2] = {{1, {4, 4, 4}}, k == 2 ? LaunchCfg{1, {8, 4, 2}} : (k == 3 ? LaunchCfg{1, {4, 4, 2}} : LaunchCfg{1, {4, 3, 2}})};
+    const LaunchCfg small[3] = {{1, {8, 4, 2}}, {1, {4, 4, 2}}, {1, {4, 3, 2}}};
+    const LaunchCfg c[2] = {{1, {4, 4, 4}}, small[k - 2]};
     const int first = k == 3 && cell_count(m) > 50000 ? 0 : 1;
     const LaunchCfg t = pick_config(k, m, c + first, 2 - first, 8);
     if (!tiles_fit(k, m, t, 8)) return cells;
