@@ -152,3 +152,25 @@ def test_reinit_of_thin_boxes(k, ncells):
     say("thin reinit step", info)
     assert info["status"] == 0 and info["true_rel_residual"] < 1.01e-12
     assert rel(host(p.reinit_apply(new, nd, 2 * h, 2 * h))[rows], rb) < 1e-9
+
+
+# k = 2 defaults change from the plane to the cell kernels with the mesh's size: in
+# FP32 the planes' error relative to FP64 is, over meshes and laws, no larger than
+# the cells' (both round each factor once, so single meshes differ by chance only)
+def test_plane_f32_error_not_above_the_cell_kernels():
+    ratio = []
+    for nc in [(8, 8, 8), (13, 11, 9), (16, 12, 10), (20, 20, 20), (24, 24, 24), (32, 32, 32)]:
+        for law in (0, 1):
+            for rho_l in (1000.0, 10.0):
+                m = W.Mesh(ncells=nc, degree=2, bc=(0, 0, 0, 0, 0, 0), extent=tuple(n / max(nc) for n in nc), rho_l=rho_l,
+                           rho_g=1.0, heaviside=law)
+                p = vpp.Problem.from_mesh(m)
+                p.set_phi(dev(W.droplet_phi(m, 0.3, 4.0 / max(nc))))
+                x = [dev(W.uniform_vectors(s, 1, m.ndofs)[0]).float() for s in (11, 12, 13)]
+                err = []
+                for cfg in [(1, (8, 4, 2)), (4, (8, 8, 4))]:
+                    p.set_config(*cfg, "fp32")
+                    err.append(np.mean([rel(host(p.apply(v).double()), host(p.apply(v.double()))) for v in x]))
+                ratio.append(err[0] / err[1])
+    say("FP32 error, planes over cells", float(np.mean(ratio)), max(ratio))
+    assert np.mean(ratio) <= 1.0
