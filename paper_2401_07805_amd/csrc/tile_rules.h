@@ -82,10 +82,9 @@ inline int slot_cost(int k, const LaunchCfg& c)
 // unless it fills the GPU (a tile per CU) and its slots cost a quarter more than a
 // later one's.  Below a quarter the larger tile's fewer shared nodes win
 // (43x37x29 Q3, FP64 / FP32 us: 8x4x4 26.2 / 19.5 at 1.17 times the slots of 4x4x2,
-// 26.8 / 21.0; 26^3 at 1.23 times 18.8 / 14.4 and 18.5 / 14.6), above it they do
-// not (150x150x5 at 1.33 times 55.7 / 38.0 against 48.7 / 33.7, 400x400x1 at 2 times
-// 116.5 / 76.1 against 72.8 / 47.6; Q4 200x200x2, 4x4x3 at 1.5 times 73.7 against
-// 65.3 with 4x3x2).
+// 26.8 / 21.0), above it they do not (150x150x5 at 1.33 times 55.7 / 38.0 against
+// 48.7 / 33.7, 400x400x1 at 2 times 116.5 / 76.1 against 72.8 / 47.6; Q4 200x200x2,
+// 4x4x3 at 1.5 times 73.7 against 65.3 with 4x3x2).
 inline LaunchCfg pick_config(int k, const MeshArgs& m, const LaunchCfg* c, int n, size_t value_bytes)
 {
     auto cost = [&](int i) { return padded_cells(m, c[i]) * slot_cost(k, c[i]); };
@@ -111,8 +110,15 @@ inline LaunchCfg pick_config(int k, const MeshArgs& m, const LaunchCfg* c, int n
 //    latter's fewer LDS accesses (32^3: 12.9 against 13.1 in FP64 but still 11.1
 //    against 13.0 in FP32; 48^3: 17.9 against 22.5 / 14.9 against 16.6).
 //  k = 3: small tiles until there are enough of them for every CU (20^3: 4x4x2
-//    13.6 against 17.3 with 8x4x4), then the fewer shared nodes of 8x4x4 (32^3:
-//    19.7 against 20.5, 64^3: 80 against 88 / 52 against 56).
+//    13.6 against 17.3 with 8x4x4; 24x88x8 16.5 against 17.8, with the sine ramp
+//    24.7 against 29.1), then the fewer shared nodes of 8x4x4 (32^3: 19.7 against
+//    20.5, 64^3: 80 against 88 / 52 against 56).  A CU holds one workgroup of
+//    8x4x4 or the same 128 cells of smaller tiles: while the second round of 8x4x4
+//    is less than two thirds full, 4x4x4 fills it better (with the sine ramp,
+//    33x30x28: 44.8 / 23.3 with 8x4x4, 30.8 / 18.9 with 4x4x4; 32x36x32: 45.2 /
+//    22.2 and 37.8 / 20.7; 36^3: 45.9 / 24.1 and 39.2 / 22.0; but 43x37x29, 1.9
+//    rounds: 45.9 / 24.5 and 46.5 / 25.4), and a tile that needs one round only
+//    does without it (33x26x34: 4x2x2 31.1, 4x4x4 38.0).
 //  k = 4: the same, in multiples of the 12 cells of a wave (16^3: 4x3x2 16.1
 //    against 17.6 with 4x4x3; 32^3: 35.4 against 38.9; in FP32 6x4x2 23.1
 //    against 24.1 with 4x4x3).
@@ -121,9 +127,9 @@ inline LaunchCfg pick_config(int k, const MeshArgs& m, const LaunchCfg* c, int n
 // beyond twice the size (1x300x300 in FP64 / FP32: 70.6 / 42.1 against 57.0 / 32.0
 // with 8x8x4; 1x1x2000, half the slots: 13.7 against 17.5), and FP32 takes 16x8x4
 // up to 1.1 times the slots of 8x8x4 (64^3 18.2 against 20.1; 88^3 at 1.09 times 39.3
-// against 39.8, 72^3 at 1.11 28.1 against 26.2, 40x80x80 at 1.2 23.3 against 19.7).  A wide and shallow box
-// whose lane offsets would pass 32 bits (2576 x 2576 x 4 cells at k = 3, 2048 x
-// 2048 x 3 at k = 4) takes a shallower tile.
+// against 39.8, 72^3 at 1.11 28.1 against 26.2, 40x80x80 at 1.2 23.3 against 19.7).
+// A wide and shallow box whose lane offsets would pass 32 bits (2576 x 2576 x 4
+// cells at k = 3, 2048 x 2048 x 3 at k = 4) takes a shallower tile.
 inline LaunchCfg default_config(int k, bool f32, const MeshArgs& m)
 {
     const size_t vb = f32 ? 4 : 8;
@@ -137,8 +143,15 @@ inline LaunchCfg default_config(int k, bool f32, const MeshArgs& m)
         return tiles_fit(k, m, slot, vb) ? slot : plane;
     }
     if (k == 3) {
-        if (ncell <= 16000) return LaunchCfg{1, {4, 4, 2}};
-        const LaunchCfg c[3] = {{1, {8, 4, 4}}, {1, {4, 4, 2}}, {1, {4, 2, 2}}};
+        if (ncell <= 18000) return LaunchCfg{1, {4, 4, 2}};
+        LaunchCfg c[3] = {{1, {8, 4, 4}}, {1, {4, 4, 2}}, {1, {4, 2, 2}}};
+        const int64_t round = 256 * 8 * 4 * 4, wide = padded_cells(m, c[0]);
+        if (wide > round && 3 * wide <= 5 * round) {
+            c[0] = LaunchCfg{4, {4, 4, 4}};
+            if (padded_cells(m, c[0]) > round)
+                for (int i = 1; i < 3; ++i)
+                    if (padded_cells(m, c[i]) <= round) return c[i];
+        }
         return pick_config(k, m, c, 3, vb);
     }
     if (ncell <= 8000) {

@@ -1,6 +1,7 @@
 // Host-side check of the tile rules (tile_rules.h): every configuration that a
 // rule picks addresses the mesh with 32-bit lane offsets, shown by walking the
 // offsets the kernels form (compiled with hipcc, runs on the CPU only).
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <random>
@@ -130,6 +131,21 @@ int main()
     expect(default_config(3, false, mesh(3, 400, 400, 1)).tile[2] == 2, "thin z", 3, mesh(3, 400, 400, 1), default_config(3, false, mesh(3, 400, 400, 1)));
     expect(default_config(3, false, mesh(3, 1, 200, 200)).tile[0] == 4, "thin x", 3, mesh(3, 1, 200, 200), default_config(3, false, mesh(3, 1, 200, 200)));
     expect(default_config(2, true, mesh(2, 1, 300, 300)).tile[0] == 8, "thin x", 2, mesh(2, 1, 300, 300), default_config(2, true, mesh(2, 1, 300, 300)));
+    // k = 3: 8x4x4 would leave CUs idle, in its only round or in the second
+    for (int f32 = 0; f32 < 2; ++f32) {
+        auto tile = [&](int x, int y, int z, LaunchCfg want) {
+            const MeshArgs m = mesh(3, x, y, z);
+            const LaunchCfg c = default_config(3, f32, m);
+            expect(c.variant == want.variant && std::equal(c.tile, c.tile + 3, want.tile), "rounds", 3, m, c);
+        };
+        tile(24, 88, 8, {1, {4, 4, 2}});
+        tile(32, 32, 32, {1, {8, 4, 4}});
+        tile(33, 30, 28, {4, {4, 4, 4}});
+        tile(40, 32, 28, {4, {4, 4, 4}});
+        tile(36, 36, 36, {4, {4, 4, 4}});
+        tile(33, 26, 34, {1, {4, 2, 2}});
+        tile(43, 37, 29, {1, {8, 4, 4}});
+    }
     expect(reinit_config(2, mesh(2, 1, 300, 300)).variant == 0, "cells", 2, mesh(2, 1, 300, 300), reinit_config(2, mesh(2, 1, 300, 300)));
     // the reinitialization operator where not even its shallow tiles reach
     expect(reinit_config(2, mesh(2, 8200, 8200, 3)).variant == 0, "cells", 2, mesh(2, 8200, 8200, 3), reinit_config(2, mesh(2, 8200, 8200, 3)));

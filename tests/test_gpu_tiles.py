@@ -174,3 +174,19 @@ def test_plane_f32_error_not_above_the_cell_kernels():
                 ratio.append(err[0] / err[1])
     say("FP32 error, planes over cells", float(np.mean(ratio)), max(ratio))
     assert np.mean(ratio) <= 1.0
+
+
+# Q3 boxes that 8x4x4 would leave CUs idle on: 4x4x2, 4x4x4 and 4x2x2
+@pytest.mark.parametrize("ncells,tile", [((24, 88, 8), (4, 4, 2)), ((33, 30, 28), (4, 4, 4)), ((33, 26, 34), (4, 2, 2))])
+def test_default_config_by_rounds(ncells, tile):
+    m = _thin(3, ncells)
+    phi = W.uniform_vectors(3, 1, m.ndofs)[0]
+    x = W.uniform_vectors(5, 1, m.ndofs)[0]
+    rows = np.random.default_rng(1).choice(m.ndofs, 2000, replace=False)
+    ref = oracle.apply_rows(m, phi, x, rows)
+    p = vpp.Problem.from_mesh(m)
+    p.set_phi(dev(phi))
+    say("rounds", ncells, p.config_for("fp64"), p.config_for("fp32"))
+    assert p.config_for("fp64")["tile"] == p.config_for("fp32")["tile"] == tile
+    assert rel(host(p.apply(dev(x)))[rows], ref) < 1e-12
+    assert rel(host(p.apply(dev(x).float()).double())[rows], ref) < 2e-6
